@@ -156,71 +156,9 @@ struct MultiProb {
 };
 
 // ---------------------------------------------------------------------------
-// Adjoint.  Pass 1 (left to right): run sums of g in FP64; at the end of each
-// run its mean goes to grad_y at the run's last node, and the boundary edge
-// that closed the previous run gets s_e (mean_prev - mean) in grad_w; edges
-// inside runs get 0.  Pass 2 (right to left): spread each run's mean over the
-// run.  Runs are detected by exact equality of consecutive x.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(64) void k_chain_adjoint(ChainBatch b, const T *__restrict__ x,
-                                                      const T *__restrict__ g, T *__restrict__ gy,
-                                                      T *__restrict__ gw, int w_per_edge) {
-    const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    if (c >= b.num_chains) return;
-    const ChainSpan a = PlainProb<T, false>::span(
-        typename PlainProb<T, false>::Params{nullptr, nullptr, (T)0, nullptr, b.es, b.cs, b.offsets}, c, b.n);
-    const int64_t n = a.n;
-    if (n <= 0) {
-        if (gw && !w_per_edge) gw[c] = (T)0;
-        return;
-    }
-    double run_sum = 0.0, prev_mean = 0.0, wsum = 0.0;
-    int64_t run_len = 0, prev_end = -1;
-    T xprev_end_val = (T)0, xi = x[a.base];
-    for (int64_t i = 0; i < n; ++i) {
-        const T xn = (i + 1 < n) ? x[a.base + (i + 1) * a.es] : xi;
-        run_sum += (double)g[a.base + i * a.es];
-        ++run_len;
-        const bool end = (i + 1 == n) || (xn != xi);
-        if (end) {
-            const double mean = run_sum / (double)run_len;
-            if (gy) gy[a.base + i * a.es] = (T)mean;
-            if (prev_end >= 0) {
-                // boundary edge prev_end: sign of the jump from the previous run
-                const double sgn = (xi > xprev_end_val) ? 1.0 : -1.0;
-                const double d = sgn * (prev_mean - mean);
-                if (gw && w_per_edge) gw[a.base + prev_end * a.es] = (T)d;
-                wsum += d;
-            }
-            prev_mean = mean;
-            prev_end = i;
-            xprev_end_val = xi;
-            run_sum = 0.0;
-            run_len = 0;
-        } else if (gw && w_per_edge) {
-            gw[a.base + i * a.es] = (T)0;
-        }
-        xi = xn;
-    }
-    if (gw) {
-        if (w_per_edge) gw[a.base + (n - 1) * a.es] = (T)0;
-        else gw[c] = (T)wsum;
-    }
-    if (!gy) return;
-    T cur = gy[a.base + (n - 1) * a.es];
-    T xr = x[a.base + (n - 1) * a.es];
-    for (int64_t i = n - 2; i >= 0; --i) {
-        const int64_t o = a.base + i * a.es;
-        const T xv = x[o];
-        if (xv != xr) cur = gy[o];  // node i closes a run: its mean was stored here
-        else gy[o] = cur;
-        xr = xv;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Adjoint for unit-stride chains (rows, CSR): one wave per chain.  The chain
+// Adjoint.  Runs are detected by exact equality of consecutive x: grad_y is
+// the mean of g over a node's run, grad_w the signed difference of the means
+// at a run boundary.  One wave per chain.  The chain
 // is processed in chunks of 64 * kAdjV nodes held in registers, lane l owning
 // the kAdjV consecutive nodes [c0 + l kAdjV, c0 + (l + 1) kAdjV), so every
 // load and store of the wave covers contiguous memory.  Per chunk:
@@ -236,29 +174,59 @@ __global__ __launch_bounds__(64) void k_chain_adjoint(ChainBatch b, const T *__r
 // boundary edge before it are written then.  Every output element is
 // written once.  Eight nodes per lane keep the kernel at 152 VGPRs, three
 // waves per SIMD (sixteen took 240 VGPRs, two waves, and 10% longer).
+//
+// Strided chains (columns, kCpb > 0): a block takes kCpb neighbouring chains
+// and passes each chunk through LDS, reading and writing kCpb consecutive
+// elements per node, so the same wave-per-chain scan runs on columns.  Rows of
+// the tile are padded by 64 / kCpb elements: the staging accesses of a wave
+// (kCpb chains x 64 / kCpb nodes) fall into distinct banks.  (A lane per chain
+// walking its column twice, the kernel this replaces, is a serial chain of
+// memory accesses on few waves: 2655 us for 1,111 columns of 3,001 FP32
+// nodes.)
 // ---------------------------------------------------------------------------
 constexpr int kAdjV = 8;
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_chain_adjoint_rows(ChainBatch b, const T *__restrict__ x,
-                                                           const T *__restrict__ g, T *__restrict__ gy,
-                                                           T *__restrict__ gw, int w_per_edge) {
-    const int lane = threadIdx.x & 63;
-    const int64_t c = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (c >= b.num_chains) return;  // whole waves
+// Waves (chains) per block of the unit-stride form.
+constexpr int kAdjWaves = 4;
+
+template <typename T, int kCpb>
+__global__ __launch_bounds__(64 * (kCpb ? kCpb : kAdjWaves)) void k_chain_adjoint(
+    ChainBatch b, const T *__restrict__ x, const T *__restrict__ g, T *__restrict__ gy, T *__restrict__ gw,
+    int w_per_edge) {
+    constexpr bool kStr = kCpb > 0;
+    constexpr int kWaves = kStr ? kCpb : kAdjWaves;
+    constexpr int64_t CH = 64 * kAdjV;
+    constexpr int kPitch = kStr ? (int)CH + 64 / kWaves : 1;
+    __shared__ __align__(16) T s_x[kStr ? kWaves * kPitch : 1];  // x, then grad_y of the chunk
+    __shared__ __align__(16) T s_g[kStr ? kWaves * kPitch : 1];  // g, then grad_w
+    __shared__ int s_last[kWaves];                               // last run end of the chunk (-1: none)
+    __shared__ int s_hole[kWaves];                               // boundary edge still pending (-1: none)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    // neighbouring strided blocks share cache lines: keep them on one XCD (blocks
+    // go round the eight XCDs in turn; the grid is a multiple of eight)
+    const int64_t blk = kStr ? (int64_t)(blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const int64_t c = blk * kWaves + wave;
+    const bool live = c < b.num_chains;
+    if (!kStr && !live) return;  // whole waves
     const ChainSpan a = PlainProb<T, false>::span(
-        typename PlainProb<T, false>::Params{nullptr, nullptr, (T)0, nullptr, 1, b.cs, b.offsets}, c, b.n);
+        typename PlainProb<T, false>::Params{nullptr, nullptr, (T)0, nullptr, kStr ? b.es : 1, b.cs, b.offsets},
+        live ? c : b.num_chains - 1, b.n);
     const int64_t n = a.n;
     if (n <= 0) {
         if (gw && !w_per_edge && lane == 0) gw[c] = (T)0;
         return;
     }
+    const int64_t es = kStr ? a.es : 1;
     const T *__restrict__ xr = x + a.base;
     const T *__restrict__ gr = g + a.base;
     T *__restrict__ yr = gy ? gy + a.base : nullptr;
     T *__restrict__ wr = (gw && w_per_edge) ? gw + a.base : nullptr;
-    const bool vec = elem_aligned(xr) && elem_aligned(gr) && (!yr || elem_aligned(yr)) && (!wr || elem_aligned(wr));
-    constexpr int64_t CH = 64 * kAdjV;
+    const bool vec = kStr || (elem_aligned(xr) && elem_aligned(gr) && (!yr || elem_aligned(yr)) &&
+                              (!wr || elem_aligned(wr)));
+    // staging: thread t moves chain t % kWaves at nodes t / kWaves, + 64, ... of the chunk
+    const int q_st = threadIdx.x % kWaves, i_st = threadIdx.x / kWaves;
+    const int64_t c_st = blk * kWaves + q_st;
+    const int64_t b_st = c_st * b.cs;
     // run open at the start of the chunk (identical in every lane)
     double o_sum = 0.0;
     int64_t o_cnt = 0, o_start = 0;
@@ -269,8 +237,35 @@ __global__ __launch_bounds__(256) void k_chain_adjoint_rows(ChainBatch b, const 
     for (int64_t c0 = 0; c0 < n; c0 += CH) {
         const int64_t i0 = c0 + lane * kAdjV;
         T xv[kAdjV], gv[kAdjV];
-        const bool full = i0 + kAdjV <= n;
-        if (vec && full) {
+        const bool full = kStr || i0 + kAdjV <= n;
+        if constexpr (kStr) {
+            T tx[kAdjV], tg[kAdjV];
+#pragma unroll
+            for (int k = 0; k < kAdjV; ++k) {
+                const int64_t i = c0 + i_st + 64 * k;
+                const bool on = i < n && c_st < b.num_chains;
+                tx[k] = on ? x[b_st + i * es] : (T)0;
+                tg[k] = on ? g[b_st + i * es] : (T)0;
+            }
+            if (c0 > 0) __syncthreads();  // the last chunk's outputs have been read
+#pragma unroll
+            for (int k = 0; k < kAdjV; ++k) {
+                s_x[q_st * kPitch + i_st + 64 * k] = tx[k];
+                s_g[q_st * kPitch + i_st + 64 * k] = tg[k];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kAdjV; q += 4) {
+                T t[4], u[4];
+                vload4(s_x + wave * kPitch + lane * kAdjV + q, t);
+                vload4(s_g + wave * kPitch + lane * kAdjV + q, u);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    xv[q + m] = t[m];
+                    gv[q + m] = u[m];
+                }
+            }
+        } else if (vec && full) {
 #pragma unroll
             for (int q = 0; q < kAdjV; q += 4) {
                 T t[4], u[4];
@@ -291,7 +286,7 @@ __global__ __launch_bounds__(256) void k_chain_adjoint_rows(ChainBatch b, const 
             }
         }
         T xnext_lane = __shfl_down(xv[0], 1, 64);
-        if (lane == 63) xnext_lane = (c0 + CH < n) ? xr[c0 + CH] : (T)0;
+        if (lane == 63) xnext_lane = (c0 + CH < n) ? xr[(c0 + CH) * es] : (T)0;
         bool end[kAdjV];
         T xn[kAdjV];
 #pragma unroll
@@ -400,18 +395,24 @@ __global__ __launch_bounds__(256) void k_chain_adjoint_rows(ChainBatch b, const 
         // the run open before this chunk closes at the chunk's first end
         if ((o_cnt > 0 || p_edge >= 0) && chunk_has_end) {
             const T m = (T)chunk_first_mean;
-            if (yr)
-                for (int64_t i = o_start + lane; i < c0; i += 64) yr[i] = m;
+            if (yr && live)
+                for (int64_t i = o_start + lane; i < c0; i += 64) yr[i * es] = m;
             if (p_edge >= 0 && lane == 0) {
                 const double d = p_sgn * (p_mean - chunk_first_mean);
-                if (wr) wr[p_edge] = (T)d;
+                if (wr && live) wr[p_edge * es] = (T)d;
                 wsum += d;
             }
             o_cnt = 0;
             p_edge = -1;
         }
         // grad_y of nodes whose run closes in this chunk
-        if (yr) {
+        if (kStr && yr) {
+#pragma unroll
+            for (int q = 0; q < kAdjV; q += 4) {
+                const T t[4] = {(T)val[q], (T)val[q + 1], (T)val[q + 2], (T)val[q + 3]};
+                vstore4(s_x + wave * kPitch + lane * kAdjV + q, t);
+            }
+        } else if (yr) {
             bool all = full && vec;
 #pragma unroll
             for (int k = 0; k < kAdjV; ++k) all = all && known[k];
@@ -463,7 +464,38 @@ __global__ __launch_bounds__(256) void k_chain_adjoint_rows(ChainBatch b, const 
 #pragma unroll
         for (int k = 0; k < kAdjV; ++k)
             if (dw_ok[k]) wsum += dw[k];
-        if (wr) {
+        if constexpr (kStr) {
+            // the tile's outputs go to memory the way its inputs came: grad_y up to
+            // the chunk's last run end, grad_w except the boundary edge left pending
+            if (wr) {
+#pragma unroll
+                for (int q = 0; q < kAdjV; q += 4) {
+                    const T t[4] = {(T)dw[q], (T)dw[q + 1], (T)dw[q + 2], (T)dw[q + 3]};
+                    vstore4(s_g + wave * kPitch + lane * kAdjV + q, t);
+                }
+            }
+            int last = -1;
+#pragma unroll
+            for (int k = 0; k < kAdjV; ++k) last = end[k] ? lane * kAdjV + k : last;
+            const unsigned long long em = __ballot(last >= 0), hm = __ballot(pend_i >= 0);
+            last = __shfl(last, em ? 63 - __clzll(em) : 0, 64);
+            const int hole = __shfl((int)(pend_i - c0), hm ? 63 - __clzll(hm) : 0, 64);
+            if (lane == 0) {
+                s_last[wave] = em ? last : -1;
+                s_hole[wave] = hm ? hole : -1;
+            }
+            __syncthreads();
+            const int ql = s_last[q_st], qh = s_hole[q_st];
+#pragma unroll
+            for (int k = 0; k < kAdjV; ++k) {
+                const int j = i_st + 64 * k;
+                const int64_t i = c0 + j;
+                if (i < n && c_st < b.num_chains) {
+                    if (gy && j <= ql) gy[b_st + i * es] = s_x[q_st * kPitch + j];
+                    if (gw && w_per_edge && j != qh) gw[b_st + i * es] = s_g[q_st * kPitch + j];
+                }
+            }
+        } else if (wr) {
             bool all = full && vec;
 #pragma unroll
             for (int k = 0; k < kAdjV; ++k) all = all && dw_ok[k];
@@ -507,9 +539,9 @@ __global__ __launch_bounds__(256) void k_chain_adjoint_rows(ChainBatch b, const 
     if (gw && !w_per_edge) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) wsum += __shfl_xor(wsum, off, 64);
-        if (lane == 0) gw[c] = (T)wsum;
+        if (lane == 0 && live) gw[c] = (T)wsum;
     }
-    if (wr && lane == 0) wr[n - 1] = (T)0;
+    if (!kStr && wr && lane == 0) wr[n - 1] = (T)0;
 }
 
 // ---------------------------------------------------------------------------
@@ -650,16 +682,21 @@ template <typename T>
 hipError_t launch_chain_adjoint(const ChainBatch &b, const T *x, const T *g, T *gy, T *gw,
                                 int w_per_edge, hipStream_t stream) {
     if (b.num_chains <= 0) return hipSuccess;
-    if (b.offsets || b.es == 1) {  // unit-stride chains: one wave per chain, contiguous accesses
-        const unsigned blocks = (unsigned)((b.num_chains + 3) / 4);
-        hipLaunchKernelGGL((k_chain_adjoint_rows<T>), dim3(blocks), dim3(256), 0, stream, b, x, g, gy, gw,
+    if (b.offsets || b.es == 1) {  // unit-stride chains: contiguous accesses
+        const unsigned blocks = (unsigned)((b.num_chains + kAdjWaves - 1) / kAdjWaves);
+        hipLaunchKernelGGL((k_chain_adjoint<T, 0>), dim3(blocks), dim3(64 * kAdjWaves), 0, stream, b, x, g, gy, gw,
                            w_per_edge);
         return hipGetLastError();
     }
-    // strided chains (columns): one lane per chain, lanes read consecutive chains
-    const unsigned blocks = (unsigned)((b.num_chains + 63) / 64);
-    hipLaunchKernelGGL((k_chain_adjoint<T>), dim3(blocks), dim3(64), 0, stream, b, x, g, gy, gw,
-                       w_per_edge);
+    // Strided chains: eight per block read a 32-byte sector per node (FP32; 4096 x 4096:
+    // 0.13 ms, 2.1 TB/s); with fewer than 2048 chains that leaves compute units without
+    // a block, and four do better (1,111 chains of 3,001: 72 us against 80-100).
+    const int cpb = b.num_chains >= 2048 ? 8 : 4;
+    const unsigned blocks = (unsigned)(((b.num_chains + cpb - 1) / cpb + 7) / 8 * 8);
+    if (cpb == 8)
+        hipLaunchKernelGGL((k_chain_adjoint<T, 8>), dim3(blocks), dim3(512), 0, stream, b, x, g, gy, gw, w_per_edge);
+    else
+        hipLaunchKernelGGL((k_chain_adjoint<T, 4>), dim3(blocks), dim3(256), 0, stream, b, x, g, gy, gw, w_per_edge);
     return hipGetLastError();
 }
 

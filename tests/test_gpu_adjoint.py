@@ -221,3 +221,29 @@ def test_rows_adjoint_csr_chains():
         dyo, dwo = oracle.chain_adjoint(x[sl][None], g[sl][None])
         assert np.abs(dyv[sl] - dyo[0]).max() < 1e-12
         assert np.abs(dwv[sl][:-1] - dwo[0][:-1]).max(initial=0.0) < 1e-12
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n,C", [(1, 3), (7, 1), (511, 5), (512, 4), (513, 9), (1025, 33), (1400, 2051)])
+def test_strided_chains_equal_unit_stride(n, C, dtype):
+    """Columns pass through LDS tiles of 512 nodes and 4 or 8 chains: at the edges of both
+    the gradients are those of the same chains laid out as rows (the same FP64 sums, so
+    the same bits), with per-edge, scalar and single outputs.  Few-valued x makes runs of
+    every length, some across several tiles."""
+    rng = np.random.default_rng(n * 131 + C)
+    x = np.where(rng.random((C, n)) < 0.02, 1.0, 0.0).cumsum(1)
+    x[::3] = rng.integers(0, 2, (len(x[::3]), n))
+    if C > 2:
+        x[2] = 0.0
+    g = rng.normal(size=(C, n))
+    xr, gr = _dev(x, dtype), _dev(g, dtype)
+    xc, gc = xr.t().contiguous(), gr.t().contiguous()
+    for kw in (dict(per_edge_w=True), dict(per_edge_w=False), dict(per_edge_w=True, need_y=False),
+               dict(per_edge_w=True, need_w=False)):
+        yr, wr = binding.chain_prox_backward(xr, gr, dim=1, **kw)
+        yc, wc = binding.chain_prox_backward(xc, gc, dim=0, **kw)
+        assert (yr is None) == (yc is None) and (wr is None) == (wc is None)
+        if yr is not None:
+            assert torch.equal(yc.t(), yr)
+        if wr is not None:
+            assert torch.equal(wc.t() if kw["per_edge_w"] else wc, wr)
