@@ -58,7 +58,13 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind) {
         auto it = tuned_map().find(TunedKey{kind, num_chains, n});
         if (it != tuned_map().end()) return it->second;
     }
-    return seg_default_plan(num_chains, n);
+    SegPlan p = seg_default_plan(num_chains, n);
+    const bool has_group = kind == kPlanChain || kind == kPlan2dCol || kind == kPlan2dRow || kind == kPlanBatchCol ||
+                           kind == kPlanBatchRow;
+    const SegTuning &t = seg_tuning(), &d = kDefaultTuning;
+    p.wg = has_group && t.target_lanes == d.target_lanes && t.min_segment == d.min_segment && t.halo == d.halo &&
+           t.ring_slots == d.ring_slots && grp_plan_ok(num_chains, n);
+    return p;
 }
 
 void seg_set_tuned(int kind, int64_t num_chains, int64_t n, const SegPlan &p) {

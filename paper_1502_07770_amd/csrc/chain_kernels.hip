@@ -618,6 +618,11 @@ int seg_candidates(int64_t C, int64_t n, SegPlan *out, int max_out) {
     const size_t base = seg_ws_bytes<T, G>(C, n, d);
     const size_t cap = (2 * base > base + (size_t(64) << 20)) ? 2 * base : base + (size_t(64) << 20);
     int m = 0;
+    if (std::is_same<T, G>::value && grp_plan_ok(C, n) && m < max_out) {
+        out[m] = d;
+        out[m].K = kRingSlots;
+        out[m++].wg = 1;
+    }
     if (m < max_out) out[m++] = d;
     bool whole = false;
     for (int64_t L = 32; !whole; L *= 2) {
@@ -632,7 +637,7 @@ int seg_candidates(int64_t C, int64_t n, SegPlan *out, int max_out) {
                 if (seg_ws_bytes<T, G>(C, n, p) > cap) continue;
                 bool dup = false;
                 for (int j = 0; j < m; ++j)
-                    dup = dup || (out[j].L == p.L && out[j].H == p.H && out[j].K == p.K);
+                    dup = dup || (!out[j].wg && out[j].L == p.L && out[j].H == p.H && out[j].K == p.K);
                 if (!dup && m < max_out) out[m++] = p;
             }
         }

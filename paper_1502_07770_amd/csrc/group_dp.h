@@ -1,0 +1,496 @@
+// group_dp.h -- exact chain TV prox with the deque spread over lanes (gfx950).
+// Included by seg_kernels.h, whose types and helpers it uses.
+//
+// A lane that owns a whole deque (seg_kernels.h) takes a serial walk over the
+// window per node: about 135-200 instructions and two LDS round trips, 0.5 to
+// 1 us a node when a SIMD holds one wave.  That is the time of a launch with
+// few chains (one 512 x 512 image: 128 waves on 1024 SIMDs).  Here a group of
+// GW lanes (16, one DPP row, or a whole wave) owns the deque, one breakpoint
+// per lane in registers, the deque's front at any lane of the group (a ring):
+//  - a lane reads its neighbours by DPP rotation, no LDS;
+//  - the message derivative at the breakpoints is the same chain of FMAs from
+//    the front as dp_step_window's, run as rounds in which every lane takes its
+//    left neighbour's value (round m completes lane m);
+//  - every lane forms the two roots on the segments beside it, and wave masks
+//    pick the lane whose root is lambda^- (the last breakpoint below w^-, or
+//    the lane before the front) and the one whose root is lambda^+;
+//  - those two lanes keep their root as the new breakpoint, the lanes outside
+//    them empty themselves: nothing moves.
+// Every rounded operation and its operands are those of dp_step_ring /
+// dq_scan, so states, lambda pairs and x are the same bits.
+//
+// One workgroup solves one chain: its groups run the chain's segments with a
+// halo, compare their halo state with the neighbour's end state through LDS,
+// rerun from the true state where they differ until nothing changes (round k
+// makes the first k + 1 segments final), and the clips are composed by a scan
+// over the nodes (clips are closed under composition, and composing them
+// rounds nothing).  So a launch is one kernel instead of five.
+// Measured per node step: see k_chain_wg.
+#pragma once
+
+namespace tvc {
+#pragma clang fp contract(off)
+
+template <int CTRL> __device__ __forceinline__ int dpp_mov(int v) {
+    return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) {
+    return __int_as_float(dpp_mov<CTRL>(__float_as_int(v)));
+}
+template <int CTRL> __device__ __forceinline__ double dpp_mov(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)dpp_mov<CTRL>((int)(unsigned)b), hi = (unsigned)dpp_mov<CTRL>((int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+// Lane t of the lane's row of 16.
+template <int t, typename T> __device__ __forceinline__ T row_bcast(T v) { return dpp_mov<0x150 + t>(v); }
+
+// The lanes of a group as a ring: neighbours' values, and masks moved one lane
+// towards the front.
+// (A rotation reads lanes that take part in it only: no lane of the wave may be
+// masked off where one is taken.)
+template <int GW> struct Ring;
+template <> struct Ring<16> {
+    static constexpr uint64_t kFirst = 0x0001000100010001ull, kLast = 0x8000800080008000ull;
+    template <typename T> static __device__ __forceinline__ T prev(T v) { return dpp_mov<0x121>(v); }  // row_ror:1
+    template <typename T> static __device__ __forceinline__ T next(T v) { return dpp_mov<0x12F>(v); }  // row_ror:15
+    static __device__ __forceinline__ uint64_t before(uint64_t m) {
+        return ((m >> 1) & ~kLast) | ((m & kFirst) << 15);
+    }
+    static __device__ __forceinline__ uint64_t bits(uint64_t m, int lane) { return (m >> (lane & 48)) & 0xffff; }
+};
+template <> struct Ring<64> {
+    static constexpr uint64_t kFirst = 1ull, kLast = 1ull << 63;
+    template <typename T> static __device__ __forceinline__ T prev(T v) { return dpp_mov<0x13C>(v); }  // wave_ror:1
+    template <typename T> static __device__ __forceinline__ T next(T v) { return dpp_mov<0x134>(v); }  // wave_rol:1
+    static __device__ __forceinline__ uint64_t before(uint64_t m) { return (m >> 1) | (m << 63); }
+    static __device__ __forceinline__ uint64_t bits(uint64_t m, int) { return m; }
+};
+
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ uint64_t lanes_where(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+
+// A deque per group.  front / back: the lanes of the first and last
+// breakpoint (the last step's lambda^- and lambda^+); pre: the lane before the
+// front; valid: the lanes that hold breakpoints (the others hold +inf).
+template <typename T> struct GDeque {
+    T l, k;
+    uint64_t front, pre, back, valid;
+    uint64_t ovf;  // groups' lanes where a deque did not fit (fewer than GW breakpoints)
+};
+
+// Rounds run between tests that every crossing was reached.
+constexpr int kGrpRounds = 5;
+
+// One step (dp_step_ring with a_i = 1) of every group of the wave.
+template <typename T, int GW>
+__device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf) {
+    using R = Ring<GW>;
+    const T lo = -w, hi = w;
+    const T lamP = R::prev(S.l), lamN = R::next(S.l);
+    const T slP = slope_of<T, T>(sf, R::prev(S.k)), sl = slope_of<T, T>(sf, S.k);
+    const T d = S.l - lamP;
+    const bool at0 = lane_in(S.front), pre = lane_in(S.pre);
+    const T v0 = S.l + (-wprev - yi);
+    // v at this lane's breakpoint; lanes not reached yet hold +inf, above both levels
+    T v = at0 ? v0 : pos_inf<T>();
+    auto rounds = [&]() {
+#pragma unroll
+        for (int r = 0; r < kGrpRounds; ++r) {
+            const T u = fmav(slP, d, R::prev(v));
+            v = at0 ? v0 : u;
+        }
+    };
+    uint64_t mlo, left, right, keep;
+    T vR;  // what lambda^+ is solved from: v at the breakpoint left of it
+    bool deep = false;
+    if constexpr (GW > kTwoEnded) deep = __popcll(S.valid) >= kTwoEnded;
+    if (!deep) {
+        uint64_t mhi;
+        // the w^+ crossing; true if it is at a breakpoint not reached yet
+        auto cross = [&]() {
+            vR = R::prev(v);
+            mhi = lanes_where(v <= hi);
+            right = (lanes_where(vR <= hi) | S.front) & ~mhi;
+            return (right & lanes_where(v == pos_inf<T>()) & S.valid) != 0;
+        };
+        rounds();
+        if (cross()) {
+            rounds();
+            if (cross()) {
+                rounds();
+                cross();
+            }
+        }
+        mlo = lanes_where(v < lo);
+        left = (mlo | S.pre) & ~lanes_where(R::next(v) < lo);
+        keep = mhi & ~mlo & S.valid;
+    } else if constexpr (GW == 64) {
+        // from kTwoEnded breakpoints on: w^- crossing from the front, w^+ crossing
+        // walking from the back (dq_scan), one group per wave
+        const int t = __popcll(S.valid);
+        rounds();
+        for (int done = kGrpRounds;; done += kGrpRounds) {
+            mlo = lanes_where(v < lo);
+            const uint64_t nxt = (lanes_where(R::prev(v) < lo) | S.front) & ~mlo;
+            if (!(nxt & lanes_where(v == pos_inf<T>()) & S.valid) || done >= t) break;
+            rounds();
+        }
+        left = (mlo | S.pre) & ~lanes_where(R::next(v) < lo);
+        const bool atB = lane_in(S.back);
+        const T u0 = S.l + (wprev - yi), dN = S.l - lamN;
+        T u = atB ? u0 : pos_inf<T>();
+        for (int done = 1; !(lanes_where(u <= hi) & S.valid) && done < t; done += 4) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const T e = fmav(sl, dN, R::next(u));
+                u = atB ? u0 : e;
+            }
+        }
+        vR = R::prev(u);
+        const uint64_t ulo = lanes_where(u <= hi) & S.valid;
+        right = ((ulo << 1) | (ulo >> 63)) & ~ulo;
+        const uint64_t after = (left << 1) | (left >> 63);
+        if (!right || (right & mlo)) right = after;  // r is raised to p
+        const int lane = threadIdx.x & 63, h = __ffsll((unsigned long long)S.front) - 1;
+        const int j = (lane - h) & 63, p = (__ffsll((unsigned long long)left) - h) & 63,
+                  r = (__ffsll((unsigned long long)right) - 1 - h) & 63;
+        keep = lanes_where(j >= p && j < r) & S.valid;
+    }
+    const uint64_t on_left = ((GW == 64) ? ((left << 1) | (left >> 63))
+                                         : (((left & ~R::kLast) << 1) | ((left & R::kLast) >> 15)));
+    // lambda^- on the segment right of this lane's breakpoint, or on the left
+    // end piece (slope 1) for the lane before the front
+    const T vN = R::next(v);
+    const T X = pre ? vN : v, base0 = pre ? lamN : S.l;
+    const T rr = pre ? (T)1 : recip(sl);
+    const T lm = clampv(fmav(lo - X, rr, base0), pre ? -pos_inf<T>() : S.l, lamN);
+    // lambda^+ on the segment left of this lane's breakpoint; from lambda^-
+    // where both lie on one segment
+    const bool same = lane_in(on_left);
+    // (every lane takes part in each rotation: none may sit behind a condition)
+    const T lmP = R::prev(lm), rrP = R::prev(rr);
+    const T base = same ? lmP : lamP, span = hi - lo, gap = hi - vR;
+    const T lp = clampv(fmav(same ? span : gap, rrP, base), base, S.l);
+    const bool isL = lane_in(left), isR = lane_in(right);
+    const T kp = sf - (T)1, kk = pre ? kp : S.k;
+    S.k = isR ? sf : kk;
+    const T kept = lane_in(keep) ? S.l : pos_inf<T>(), lr = isR ? lp : kept;
+    S.l = isL ? lm : lr;
+    S.front = left;
+    S.back = right;
+    S.pre = R::before(left);
+    S.valid = left | right | keep;
+    S.ovf |= right & (left | S.pre);
+}
+
+// ---------------------------------------------------------------------------
+// One chain per workgroup.
+// ---------------------------------------------------------------------------
+// Segment length, halo and block size of a launch; lds_lam: the lambda pairs of
+// a chain stay in LDS (else they go to the workspace's stream); cap: entries of
+// the LDS deque of grp_lane_chain, in the same memory (0: an HBM deque per block).
+struct GrpGeom {
+    int L, H, threads, lds_lam, cap;
+};
+struct GrpLds {
+    void *lam;    // [S * L] pairs (lds_lam)
+    void *l, *k;  // end states [threads] (group g's entries from g * GW)
+    int *size;    // [groups]
+    int *need;    // [groups + 1] the state entering a segment changed
+    void *w;      // [2 * waves] the waves' composed clips
+};
+
+template <class Prob>
+struct GroupOk : std::bool_constant<!Prob::kGen && !IsL1<Prob>::value> {};
+
+// Solves chain c with groups of GW lanes; false (for the whole workgroup) if a
+// deque outgrew a group.  kStream: lambda may be kept in the stream (without a
+// store to it in the step loop, the next tile's loads are waited for a tile
+// later; with one, before the loop).
+template <typename T, class Prob, int GW, bool kStream>
+__device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
+                          const GrpGeom &gm, const GrpLds &sh, int L) {
+    using R = Ring<GW>;
+    const int tid = threadIdx.x, lane = tid & 63, gl = tid & (GW - 1), g = tid / GW;
+    const int n = (int)sp.n, H = gm.H, a = g * L;
+    const bool act = a < n;
+    const auto src = Prob::src(pp, sp);
+    T *lamL = (T *)sh.lam;
+    T *esl = (T *)sh.l + g * GW, *esk = (T *)sh.k + g * GW;
+    GDeque<T> S;
+    // the lambda pair of node i: (lo, hi) at lds + 2 i, or in the stream
+    auto put = [&](int i, int which, T v) {
+        if (!kStream || gm.lds_lam)
+            lamL[2 * i + which] = v;
+        else if (i < n)
+            ((T *)(ws.lam + (int64_t)i * ws.C + c))[which] = v;
+    };
+    // Runs the nodes from `halo` before a to the segment's end in tiles of 16
+    // (nodes before the chain's start are skipped); `fresh`: from an empty deque
+    // at the first node, else continuing S.  at_a() is called before node a.
+    auto run = [&](int halo, bool fresh, bool store, auto at_a) {
+        const int from = a - halo, tiles = (halo + L) / 16;
+        int i0 = from;
+        const int h0 = from > 0 ? from : 0;
+        T wprev = (!fresh && from > 0 && act) ? src.weight(src.load(from - 1 < n ? from - 1 : n - 1)) : (T)0;
+        auto tile = [&](int i, T &y, T &w) {
+            const int j = i + (lane & 15);
+            const auto pv = src.load(j < 0 ? 0 : (j < n ? j : n - 1));
+            y = src.data(pv);
+            // the root's zero edge; nodes past the chain's end, run to fill a tile, get
+            // constant data and weight, on which a deque stays short
+            w = j < n - 1 ? src.weight(pv) : (j == n - 1 ? (T)0 : (T)1);
+        };
+        T y, w, yn, wn;
+        tile(i0, y, w);
+        S.ovf = 0;
+        for (int q = 0; q < tiles; ++q, i0 += 16, y = yn, w = wn) {
+            if (16 * q == halo) at_a();
+            tile(i0 + 16, yn, wn);
+            const uint64_t im = lanes_where(fresh && i0 == h0);
+            const uint64_t st = lanes_where(store && act && i0 >= a);
+            const uint64_t live = lanes_where(i0 >= h0);
+            T sf = (T)(i0 + 1);
+            uint64_t init = im;
+            // lane t of the row holds node i0 + t: the tile turns by one lane a node
+#pragma unroll 1
+            for (int t = 0; t < 16; ++t) {
+                const T yi = row_bcast<0>(y), wi = row_bcast<0>(w);
+                y = Ring<16>::next(y);
+                w = Ring<16>::next(w);
+                grp_step<T, GW>(S, yi, wprev, wi, sf);
+                if (init) {  // an empty message: breakpoints y -+ w
+                    if (lane_in(init)) {
+                        S.l = gl == 0 ? yi - wi : (gl == 1 ? yi + wi : pos_inf<T>());
+                        S.k = gl == 0 ? sf - (T)1 : sf;
+                    }
+                    S.front = (S.front & ~init) | (R::kFirst & init);
+                    S.pre = (S.pre & ~init) | (R::kLast & init);
+                    S.back = (S.back & ~init) | ((R::kFirst << 1) & init);
+                    S.valid = (S.valid & ~init) | ((R::kFirst | (R::kFirst << 1)) & init);
+                    S.ovf &= ~init;
+                    init = 0;
+                }
+                S.ovf &= live;
+                if (lane_in((S.front | S.back) & st)) put(i0 + t, lane_in(S.back) ? 1 : 0, S.l);
+                wprev = wi;
+                sf += (T)1;
+            }
+        }
+    };
+    // breakpoints of S in order: this lane's place, and the deque's size
+    auto order = [&](const GDeque<T> &D, int &j, int &size) {
+        const int h = __ffsll((unsigned long long)R::bits(D.front, lane)) - 1;
+        j = (gl - h) & (GW - 1);
+        size = __popcll(R::bits(D.valid, lane));
+    };
+    auto reset = [&]() {
+        S.l = pos_inf<T>();
+        S.k = (T)0;
+        S.front = R::kFirst;
+        S.pre = R::kLast;
+        S.back = R::kFirst;
+        S.valid = 0;
+        S.ovf = 0;
+    };
+    T hl = pos_inf<T>(), hk = (T)0;  // the deque after the halo
+    int hj = 0, hsize = 0;
+    auto group_any = [&](bool p) { return R::bits(lanes_where(p), lane) != 0; };
+    // The first pass runs every segment with its halo; later ones run the
+    // segments whose incoming deque was not the true one again from it.  A pass
+    // makes at least one more segment final, so there are at most as many as
+    // segments.
+    bool mine = act;
+#pragma unroll 1
+    for (int pass = 0; pass <= (int)blockDim.x / GW; ++pass) {
+        reset();
+        if (pass > 0 && lanes_where(mine)) {
+            const int m = mine ? sh.size[g - 1] : 0;
+            if (gl < m) {
+                S.l = esl[gl - GW];
+                S.k = esk[gl - GW];
+            }
+            S.valid = lanes_where(gl < m);
+            S.back = lanes_where(gl == m - 1);
+        }
+        __syncthreads();  // the states have been read
+        bool bad = false, changed = false;
+        if (gl == 0) sh.need[g + 1] = 0;
+        if (lanes_where(mine)) {
+            run(pass == 0 ? H : 0, pass == 0, mine, [&]() {
+                if (pass == 0) {
+                    order(S, hj, hsize);
+                    hl = S.l;
+                    hk = S.k;
+                }
+            });
+            bad = mine && R::bits(S.ovf, lane) != 0;
+            int j, size;
+            order(S, j, size);
+            if (mine) {
+                changed = pass == 0 || size != sh.size[g];
+                if (!changed && j < size) changed = !ent_same<T>(esl[j], esk[j], S.l, S.k);
+            }
+            changed = group_any(changed);
+            if (changed) {
+                if (j < size) {
+                    esl[j] = S.l;
+                    esk[j] = S.k;
+                }
+                if (gl == 0) {
+                    sh.size[g] = size;
+                    sh.need[g + 1] = 1;
+                }
+            }
+        }
+        if (__syncthreads_or(bad)) return false;
+        bool need = act && g > 0 && sh.need[g] != 0;
+        if (pass == 0 && need) {  // every segment wrote its end state: compare it with the halo's
+            need = sh.size[g - 1] != hsize;
+            if (!need && hj < hsize) need = !ent_same<T>(esl[hj - GW], esk[hj - GW], hl, hk);
+        }
+        mine = group_any(need);
+        if (!__syncthreads_or(mine)) break;
+    }
+    // x from the composed clips, a block of blockDim.x nodes at a time from the
+    // end: a suffix scan of (lo, hi) over the wave, then over the waves
+    const auto sink = Prob::sink(pp, sp);
+    T *sw = (T *)sh.w;
+    const int nw = blockDim.x >> 6, wave = tid >> 6;
+    T xin = (T)0;
+    for (int c0 = (n - 1) / (int)blockDim.x * (int)blockDim.x; c0 >= 0; c0 -= (int)blockDim.x) {
+        const int i = c0 + tid;
+        T lo = -pos_inf<T>(), hi = pos_inf<T>();
+        typename Prob::SinkPre sv;
+        if (i < n) {
+            sv = sink.load(i);
+            if (!kStream || gm.lds_lam) {
+                lo = lamL[2 * i];
+                hi = lamL[2 * i + 1];
+            } else {
+                const LamPair<T> p = ws.lam[(int64_t)i * ws.C + c];
+                lo = p.lo;
+                hi = p.hi;
+            }
+            if (i == n - 1) hi = lo;
+        }
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const T olo = __shfl_down(lo, off, 64), ohi = __shfl_down(hi, off, 64);
+            if (lane + off < 64) {
+                const T l2 = clampv(olo, lo, hi), h2 = clampv(ohi, lo, hi);
+                lo = l2;
+                hi = h2;
+            }
+        }
+        if (lane == 0) {
+            sw[2 * wave] = lo;
+            sw[2 * wave + 1] = hi;
+        }
+        __syncthreads();
+        T xr = xin;
+        for (int q = nw - 1; q >= 0; --q) {
+            if (q == wave) xr = xin;
+            xin = clampv(xin, sw[2 * q], sw[2 * q + 1]);
+        }
+        if (i < n) sink.store(i, clampv(xr, lo, hi), sv);
+        __syncthreads();
+    }
+    return true;
+}
+
+// A deque of one lane in LDS: a ring of cap >= 2 n + 4 entries (a step adds at
+// most two; l at [0, cap), k after them), for dq_scan and dq_update.
+template <typename T> struct LdsDeque {
+    T *l, *k;
+    int cap, head, size;
+    __device__ __forceinline__ int at(int j) const {
+        const int i = head + j;
+        return i < 0 ? i + cap : (i >= cap ? i - cap : i);
+    }
+    __device__ __forceinline__ Ent<T, T> ld(int j) const { return mk_ent<T, T>(l[at(j)], k[at(j)]); }
+    __device__ __forceinline__ void put(int j, const Ent<T, T> &e) const {
+        l[at(j)] = e.l;
+        k[at(j)] = e.k;
+    }
+    __device__ __forceinline__ void shift(int d) { head = at(d); }
+};
+
+// The whole chain on one lane with its deque in LDS, lambda in the stream.
+template <typename T, class Prob>
+__device__ void grp_lane_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
+                               T *mem, int cap) {
+    const auto src = Prob::src(pp, sp);
+    auto cy = carry_before<T, Prob>(src, 0);
+    LdsDeque<T> D{mem, mem + cap, cap, 0, 0};
+    D.put(0, mk_ent<T, T>(pos_inf<T>(), (T)0));
+    for (int64_t i = 0; i < sp.n; ++i) {
+        const auto pr = src.load(i);
+        const auto in = step_in<T, Prob>(src, pr, i, i == sp.n - 1, cy);
+        const EndSlope<T, T, false> es(in.sf, in.sprev);
+        const DqScan<T> sc = dq_scan<T, T, false, true>(D, D.size, in, es);
+        const int i0 = sc.p > 0 ? sc.p - 1 : 0, i1 = sc.r > 0 ? sc.r - 1 : 0;
+        T lm, lp, tnew;
+        dq_solve<T, T, false>(sc, in, es, D.size == 0, D.ld(i0), D.ld(i0 + 1), D.ld(i1), D.ld(i1 + 1), lm, lp, tnew);
+        D.size = dq_update<T, T>(D, sc, in.sf, lm, lp, tnew);
+        put_lam<T>(ws.lam, i, ws.C, c, lm, i == sp.n - 1 ? lm : lp);
+    }
+    full_backward<T, Prob>(ws, pp, sp, c);
+}
+
+// A launch over all chains (kList false), or over the chains in ws.ovf_list.
+// Chains whose deque outgrows a group of 16 run with a wave per segment, and
+// beyond 63 breakpoints on one lane, the deque in LDS (gm.cap) or in HBM.
+template <typename T, class Prob, bool kList>
+__global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Prob::Params pp, GrpGeom gm) {
+    extern __shared__ __align__(16) char s_grp[];
+    if (seg_stopped(ws)) return;
+    const int S16 = (int)blockDim.x / 16;
+    GrpLds sh;
+    {
+        char *p = s_grp;
+        sh.l = p;
+        p += sizeof(T) * blockDim.x;
+        sh.k = p;
+        p += sizeof(T) * blockDim.x;
+        sh.w = p;
+        p += 2 * sizeof(T) * (blockDim.x / 64);
+        sh.size = (int *)p;
+        p += sizeof(int) * S16;
+        sh.need = (int *)p;
+        p += sizeof(int) * (S16 + 4);
+        sh.lam = p;
+    }
+    const int64_t count = kList ? (int64_t)*ws.ovf_count : ws.C;
+    for (int64_t q = blockIdx.x; q < count; q += gridDim.x) {
+        // neighbouring chains on one XCD (blocks go round the eight XCDs in turn):
+        // neighbouring columns share cache lines
+        const int64_t x = q & 7, per = count >> 3, rem = count & 7;
+        const int64_t c = kList ? (int64_t)ws.ovf_list[q] : x * per + (x < rem ? x : rem) + (q >> 3);
+        const ChainSpan sp = Prob::span(pp, c, ws.n);
+        if (sp.n <= 0) continue;
+        if (!grp_chain<T, Prob, 16, kList>(ws, pp, sp, c, gm, sh, gm.L)) {
+            __syncthreads();
+            const int waves = (int)blockDim.x / 64;
+            const int Lw = (int)((sp.n + waves - 1) / waves + 15) / 16 * 16;
+            if (!grp_chain<T, Prob, 64, kList>(ws, pp, sp, c, gm, sh, Lw)) {
+                __syncthreads();
+                if (threadIdx.x == 0) {
+                    if (gm.cap)
+                        grp_lane_chain<T, Prob>(ws, pp, sp, c, (T *)sh.lam, gm.cap);
+                    else
+                        seg_full_chain<T, Prob>(ws, pp, sp, c, blockIdx.x);
+                }
+            }
+        }
+        if constexpr (kList) {  // the segments' tails are done
+            for (int64_t s = threadIdx.x; s * ws.L < sp.n; s += blockDim.x)
+                ws.seg_unc[s * ws.C + c] = (int)((s + 1) * ws.L < sp.n ? (s + 1) * ws.L : sp.n);
+        }
+        __syncthreads();
+    }
+}
+
+#pragma clang fp contract(fast)
+}  // namespace tvc

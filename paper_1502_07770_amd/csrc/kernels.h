@@ -32,15 +32,32 @@ struct ChainBatch {
     const int64_t *offsets;  // CSR starts (device) or nullptr
 };
 
+constexpr int64_t kGrpMaxLen = 6144;  // the lambda pairs of an FP64 chain fit LDS (128 KB with the rest)
+constexpr int64_t kGrpMaxNodes = int64_t(9) << 18;
+
 // Segmentation of a launch: segment length L (S = ceil(n / L) segments per
 // chain), halo H run before each segment, checkpoint spacing CK, and the
 // number K of breakpoint slots of the LDS ring (16, 32; 64 or 128 for 8-byte entries).
+// wg: the workgroup-per-chain kernel instead, with a geometry of its own.
 struct SegPlan {
     int64_t L;
     int64_t H;
     int64_t CK;
     int K;
+    int wg = 0;
 };
+
+// Whether a launch of this size takes the workgroup-per-chain kernel (k_chain_wg)
+// unless a plan was tuned or set.  With its deque spread over 16 lanes a node
+// step has a fifth of the latency but a wave advances 4 chains instead of 64:
+// it wins while the lane-per-segment launch leaves SIMDs idle (us, FP32, w = 0.3:
+// 512 x 512 60 against 179, 1024 x 1024 102 against 206, 1500 x 1500 206 against
+// 208, 2048 x 2048 290 against 231), and on chains of a few segments only up to
+// a launch four times smaller (16384 x 128 195 against 89: one lane has no halo
+// there).
+inline bool grp_plan_ok(int64_t num_chains, int64_t n) {
+    return num_chains > 0 && n <= kGrpMaxLen && num_chains * n <= (n < 256 ? kGrpMaxNodes / 4 : kGrpMaxNodes);
+}
 
 // Which launch a plan is for: the best segmentation depends on the problem's
 // data source, so tuned plans are cached per kind and shape.

@@ -1262,6 +1262,12 @@ __device__ void seg_full_chain(const WsOf<T, Prob> &ws, const typename Prob::Par
     full_backward<T, Prob>(ws, pp, sp, c);
 }
 
+#pragma clang fp contract(fast)
+}  // namespace tvc
+#include "group_dp.h"
+namespace tvc {
+#pragma clang fp contract(off)
+
 template <typename T, class Prob, int K, int P>
 __device__ bool fix_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
                           EntOf<T, Prob> *s_ent, int lane);
@@ -1275,7 +1281,8 @@ __device__ bool fix_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
 // ---------------------------------------------------------------------------
 template <typename T, class Prob, int K, int P>
 __global__ __launch_bounds__(64) void k_seg_fix(WsOf<T, Prob> ws, typename Prob::Params pp) {
-    __shared__ EntOf<T, Prob> s_ent[CRing<T, K, typename Prob::Tag>::kRows * 64];
+    constexpr bool kGroup = GroupOk<Prob>::value;  // dirty chains go to k_chain_wg
+    __shared__ EntOf<T, Prob> s_ent[kGroup ? 1 : CRing<T, K, typename Prob::Tag>::kRows * 64];
     if (seg_stopped(ws)) return;
     const int lane = threadIdx.x;
     const int64_t c = (int64_t)blockIdx.x * 64 + lane;
@@ -1292,8 +1299,10 @@ __global__ __launch_bounds__(64) void k_seg_fix(WsOf<T, Prob> ws, typename Prob:
         any_ovf |= ovf[s] != 0;
         if (s > 0 && s + 1 < Sc) any_dirty |= (mis[s] != 0) && (cln[s] == 0);
     }
-    if (any_ovf || (any_dirty && !fix_chain<T, Prob, K, P>(ws, pp, sp, c, s_ent, lane))) {
-        ws.ovf_list[atomicAdd(ws.ovf_count, 1)] = (int)c;  // solved by k_seg_ovf
+    bool redo = any_ovf || any_dirty;
+    if constexpr (!kGroup) redo = any_ovf || (any_dirty && !fix_chain<T, Prob, K, P>(ws, pp, sp, c, s_ent, lane));
+    if (redo) {
+        ws.ovf_list[atomicAdd(ws.ovf_count, 1)] = (int)c;  // solved by k_chain_wg or k_seg_ovf
         return;
     }
     // x entering each segment from the right: compose the segment maps from the
@@ -1507,6 +1516,49 @@ size_t seg_ws_layout(void *base, int64_t C, int64_t n, int64_t L, int64_t H, int
     return off;
 }
 
+// Geometry of a workgroup-per-chain launch: 32-node segments with a 64-node
+// halo, in at most 64 groups; twice as long (the halo costs less, the chain's
+// latency more) while there are more than four waves per SIMD.  us per prox /
+// per 2D iteration, FP32, w = 0.3: 512 x 512 at L = 32 66 / 119, 64 77 / 153,
+// 128 100 / 222; 1024 x 1024 143 / 279, 103 / 261, 116 / 343.  Halos of 48 to
+// 96 are within 5% of it, 32 leaves more segments to run again.
+inline GrpGeom grp_geom(int64_t C, int64_t n) {
+    int L = 32;
+    auto threads = [&](int l) { return (int)((n + l - 1) / l * 16 + 63) / 64 * 64; };
+    while (L < 128 && C * (threads(L) / 64) > 4096) L *= 2;
+    while (threads(L) > 1024) L += 16;
+    return GrpGeom{L, 64, threads(L), 0, 0};
+}
+
+template <typename T, class Prob, bool kList>
+hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, hipStream_t stream) {
+    GrpGeom gm = grp_geom(ws.C, ws.n);
+    const int64_t waves = gm.threads / 64, Lw = (ws.n + waves - 1) / waves + 16;
+    size_t lds = (2 * sizeof(T) + 8) * (size_t)gm.threads + 256;
+    size_t lam = 2 * sizeof(T) * (size_t)(ws.n + (Lw > gm.L ? Lw : gm.L));
+    gm.lds_lam = lds + lam <= 160 * 1024;
+    // a block of a list or of a launch of few chains has an HBM deque of its own;
+    // the blocks of other launches have room for one in LDS
+    const int64_t blocks = kList && ws.C > 256 ? 256 : ws.C;
+    if (blocks > ws.fb_lanes) {
+        gm.cap = (int)(2 * ws.n + 4);
+        const size_t dq = 2 * sizeof(T) * (size_t)gm.cap;
+        lam = lam > dq ? lam : dq;
+        gm.lds_lam = 1;
+        if (lds + lam > 160 * 1024) return hipErrorInvalidValue;  // excluded by grp_plan_ok
+    }
+    if (!kList && !gm.lds_lam) return hipErrorInvalidValue;  // excluded by kGrpMaxLen
+    if (gm.lds_lam) lds += lam;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)k_chain_wg<T, Prob, kList>,
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_chain_wg<T, Prob, kList>), dim3((unsigned)blocks), dim3((unsigned)gm.threads), lds, stream,
+                       ws, pp, gm);
+    return hipGetLastError();
+}
+
 template <typename T, class Prob, int K, int P>
 hipError_t seg_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, hipStream_t stream) {
     if (ws.C <= 0) return hipSuccess;
@@ -1518,7 +1570,12 @@ hipError_t seg_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
     }
     const unsigned fb = (unsigned)((ws.C + 63) / 64);
     hipLaunchKernelGGL((k_seg_fix<T, Prob, K, P>), dim3(fb), dim3(64), 0, stream, ws, pp);
-    hipLaunchKernelGGL((k_seg_ovf<T, Prob>), dim3((unsigned)(ws.fb_lanes / 64)), dim3(64), 0, stream, ws, pp);
+    if constexpr (GroupOk<Prob>::value) {
+        const hipError_t e = grp_launch<T, Prob, true>(ws, pp, stream);
+        if (e != hipSuccess) return e;
+    } else {
+        hipLaunchKernelGGL((k_seg_ovf<T, Prob>), dim3((unsigned)(ws.fb_lanes / 64)), dim3(64), 0, stream, ws, pp);
+    }
     if (ws.S > 1) {
         const unsigned tb = (unsigned)(((ws.S - 1) * ws.C + 63) / 64);
         hipLaunchKernelGGL((k_seg_tail<T, Prob>), dim3(tb), dim3(64), 0, stream, ws, pp);
@@ -1560,6 +1617,13 @@ hipError_t seg_run(void *workspace, int64_t C, int64_t n, const SegPlan &p, cons
                    hipStream_t stream, const int *stop = nullptr) {
     using G = typename Prob::Tag;
     WsOf<T, Prob> ws;
+    if constexpr (GroupOk<Prob>::value) {
+        if (p.wg) {
+            seg_ws_layout<T, 16>(workspace, C, n, p.L, p.H, p.CK, &ws);
+            ws.stop = stop;
+            return grp_launch<T, Prob, false>(ws, pp, stream);
+        }
+    }
     const int K = ring_slots_for<T, G>(p.K);
     if constexpr (ring_max<T, G>() >= 128) {
         if (K == 128) {

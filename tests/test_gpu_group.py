@@ -1,0 +1,88 @@
+"""The chain prox with its deque spread over the lanes of a group (a workgroup per
+chain): small launches take it, and so do the chains that the lane-per-segment
+kernels hand on (a deque deeper than the ring, a segment whose repair did not
+meet the first pass).  Both ways give the bits of the sequential run."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1502_07770_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+TOL = {torch.float32: 1e-4, torch.float64: 1e-12}  # of the data range, as for every chain prox
+
+
+@pytest.fixture
+def tuning():
+    saved = binding.get_tuning()
+    yield binding.set_tuning
+    binding.set_tuning(**saved)
+
+
+def _data(kind, C, n, seed):
+    """(y, w): ordinary chains; square-root ramps whose deques hold from a few to
+    hundreds of breakpoints; constant data with zero weights (two breakpoints more
+    per node, the most there can be)."""
+    if kind == "piecewise":
+        return synth.piecewise_constant(C, n, seed=seed), synth.edge_weights((C, n), lo=0.05, hi=0.8, seed=seed + 1)
+    if kind == "ramp":
+        y = np.sqrt(np.arange(n)[None, :] + 3.0 * np.arange(C)[:, None])
+        return y, np.repeat(np.array([(0.5, 3.0, 10.0, 100.0)[c % 4] for c in range(C)])[:, None], n, axis=1)
+    y, w = np.ones((C, n)), np.zeros((C, n))
+    w[:, n // 2:] = 0.25
+    y[:, n // 2:] += 0.1 * synth.normal((C, n - n // 2), seed=seed)
+    return y, w
+
+
+SHAPES = [(3, 1), (2, 2), (5, 15), (4, 16), (3, 17), (7, 31), (2, 33), (3, 96), (2, 97), (9, 513), (2, 2048),
+          (2, 2049), (1, 6144), (1, 6145), (1100, 130)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("kind", ["piecewise", "ramp", "flat"])
+def test_group_kernel_equals_lane_kernels(tuning, kind, dtype):
+    for C, n in SHAPES:
+        if kind != "piecewise" and n > 2049:
+            continue  # one lane's walk over hundreds of breakpoints a node
+        y, w = _data(kind, C, n, seed=C + n)
+        yt, wt = torch.tensor(y, dtype=dtype, device="cuda"), torch.tensor(w, dtype=dtype, device="cuda")
+        tuning(target_lanes=1 << 17, min_segment=128, halo=128, ring_slots=16)  # the default: a workgroup per chain
+        rows = binding.chain_prox(yt, wt, dim=1)
+        cols = binding.chain_prox(yt.t().contiguous(), wt.t().contiguous(), dim=0).t()
+        tuning(target_lanes=1, min_segment=1, ring_slots=32)  # one lane per chain
+        ref = binding.chain_prox(yt, wt, dim=1)
+        assert torch.equal(rows, ref), (kind, C, n)
+        assert torch.equal(cols, ref), (kind, C, n)
+        if C * n < 20000:
+            yv, wv = yt.double().cpu().numpy(), wt.double().cpu().numpy()
+            err = np.abs(ref.double().cpu().numpy() - oracle.chain_prox(yv, w=wv)).max()
+            assert err <= TOL[dtype] * max(np.ptp(yv), 1.0), (kind, C, n, err)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n", [300, 4100, 20000])
+def test_handed_on_chains_equal_the_sequential_run(tuning, n, dtype):
+    """Without a halo and with 16 ring slots most chains are handed on: their lambda pairs
+    stay in LDS at 300 nodes and go through memory at 20,000."""
+    y = np.concatenate([synth.piecewise_constant(40, n, seed=n), np.sqrt(np.arange(n)[None, :] + np.arange(3)[:, None])])
+    w = np.full((43, n), 0.7)
+    w[40], w[41], w[42] = 1.0, 5.0, 60.0
+    yt, wt = torch.tensor(y, dtype=dtype, device="cuda"), torch.tensor(w, dtype=dtype, device="cuda")
+    tuning(target_lanes=1 << 30, min_segment=32, halo=0, ring_slots=16)
+    got = binding.chain_prox(yt, wt, dim=1)
+    tuning(target_lanes=1, min_segment=1, ring_slots=32)
+    assert torch.equal(got, binding.chain_prox(yt, wt, dim=1))
+
+
+def test_short_weights_and_many_chains(tuning):
+    """A scalar weight of zero, one chain of one node in a batch of batches, and more chains
+    than blocks with a deque of their own in memory."""
+    for dtype in (torch.float32, torch.float64):
+        y = torch.rand(2500, 40, dtype=dtype, device="cuda")
+        z = torch.rand(1, 5, dtype=dtype, device="cuda")
+        a = binding.chain_prox_multi([(y, 1), (z, 0), (y, 0)], [0.0, 0.3, 2.0])
+        tuning(target_lanes=1, min_segment=1, ring_slots=32)
+        b = binding.chain_prox_multi([(y, 1), (z, 0), (y, 0)], [0.0, 0.3, 2.0])
+        assert all(torch.equal(u, v) for u, v in zip(a, b))
+        binding.reset_tuning()
