@@ -21,8 +21,7 @@ static int64_t round_tile(int64_t v) { return (v + kTile - 1) / kTile * kTile; }
 
 // Enough segments per chain that the launch has about target_lanes lanes,
 // with segments no shorter than min_segment; L, H and CK are tile multiples.
-SegPlan seg_default_plan(int64_t num_chains, int64_t n) {
-    const SegTuning &t = seg_tuning();
+static SegPlan plan_for(const SegTuning &t, int64_t num_chains, int64_t n) {
     SegPlan p;
     int64_t S = num_chains > 0 ? (t.target_lanes + num_chains - 1) / num_chains : 1;
     const int64_t smax = (n + t.min_segment - 1) / t.min_segment;
@@ -35,6 +34,15 @@ SegPlan seg_default_plan(int64_t num_chains, int64_t n) {
     p.K = (int)t.ring_slots;
     return p;
 }
+
+SegPlan seg_default_plan(int64_t num_chains, int64_t n) { return plan_for(seg_tuning(), num_chains, n); }
+
+// TV-l1 sets rarely meet bit for bit (their jumps carry running sums), so a
+// segment that starts wrong runs to its end twice: segments only where the chip
+// has no other lanes (one wave per SIMD), and short ones.  ms at 65,536 lanes
+// against 131,072 (FP32, w = 0.55, c = 1): 65536 x 1024 2.2 / 4.3, 4096 x 1024
+// 0.25 / 0.45, 210 x 8044 0.28 / 0.45.
+static const SegTuning kL1Tuning{int64_t(1) << 16, 64, 64, kRingSlots};
 
 // Plans chosen by the autotuner, per (kind, chains, length).
 namespace {
@@ -58,12 +66,14 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind) {
         auto it = tuned_map().find(TunedKey{kind, num_chains, n});
         if (it != tuned_map().end()) return it->second;
     }
-    SegPlan p = seg_default_plan(num_chains, n);
+    const SegTuning &t = seg_tuning(), &d = kDefaultTuning;
+    const bool by_default = t.target_lanes == d.target_lanes && t.min_segment == d.min_segment && t.halo == d.halo &&
+                            t.ring_slots == d.ring_slots;
+    if (by_default && (kind == kPlanL1 || kind == kPlan2dRowL1)) return plan_for(kL1Tuning, num_chains, n);
+    SegPlan p = plan_for(t, num_chains, n);
     const bool has_group = kind == kPlanChain || kind == kPlan2dCol || kind == kPlan2dRow || kind == kPlanBatchCol ||
                            kind == kPlanBatchRow;
-    const SegTuning &t = seg_tuning(), &d = kDefaultTuning;
-    p.wg = has_group && t.target_lanes == d.target_lanes && t.min_segment == d.min_segment && t.halo == d.halo &&
-           t.ring_slots == d.ring_slots && grp_plan_ok(num_chains, n);
+    p.wg = has_group && by_default && grp_plan_ok(num_chains, n);
     return p;
 }
 

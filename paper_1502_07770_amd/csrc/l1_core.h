@@ -254,5 +254,165 @@ __device__ __forceinline__ void l1_step(St &S, T s, T yi, T di, T ci, T lop, T h
     lp = lp < lm ? lm : lp;
 }
 
+// ---------------------------------------------------------------------------
+// The same step on a set held in registers.  Sets of TV-l1 messages are small
+// (salt-and-pepper chains, w = 0.3 to 0.8: two breakpoints in 97% of the
+// steps, the largest set of a 64-lane wave at most 3 in 87%, at most 5 in
+// 99.9%), so the loops over a ring in LDS cost latency and divergence (5 us a
+// node) where a fixed number of positions needs neither: every scan below
+// visits M + 1 or M + 2 positions, selects by comparisons, and moves entries by
+// selects.  Each value is computed by l1_step's operations in l1_step's order,
+// so both give the same bits.
+// ---------------------------------------------------------------------------
+constexpr int kL1Regs = 8;  // largest set held; a step on at most M entries leaves at most M + 3
+template <typename T>
+struct L1Regs {
+    T l[kL1Regs], j[kL1Regs];  // entries past the size: +inf, 0
+    int k[kL1Regs];            // slope tags (integers)
+    int t;
+};
+
+// One step on a set of at most M entries (M + 3 <= kL1Regs).
+template <typename T, int M>
+__device__ __forceinline__ void l1_step_regs(L1Regs<T> &S, int s, T yi, T di, T ci, T lop, T hip, T lo, T hi, bool root,
+                                             T &lm_out, T &lp_out) {
+    static_assert(M + 3 <= kL1Regs, "the step's result fits");
+    constexpr int N = M + 3;  // positions 1 .. M + 2; the set after the insertion is 1 .. t
+    const T inf = (T)__builtin_huge_val();
+    T l[N], J[N];
+    int k[N];
+    if (S.t == 0) {
+        lop = (T)0;
+        hip = (T)0;
+    }
+    // (a) the data breakpoint goes after every entry <= d
+    const bool ins = ci > (T)0;
+    const int t0 = S.t;
+    int q = 0;
+    bool le[M + 2];
+    le[0] = true;
+    le[M + 1] = !ins;
+#pragma unroll
+    for (int i = 1; i <= M; ++i) {
+        const bool b = i <= t0 && S.l[i - 1] <= di;
+        q = b ? i : q;
+        le[i] = b || !ins;
+    }
+    const bool is_end = ins && q == t0;
+    const T cj = (T)2 * ci;
+    l[0] = l[N - 1] = inf;
+    J[0] = J[N - 1] = (T)0;
+    k[0] = k[N - 1] = 0;
+#pragma unroll
+    for (int i = 1; i <= M + 1; ++i) {
+        const T pl = i <= M ? S.l[i <= M ? i - 1 : 0] : inf, pj = i <= M ? S.j[i <= M ? i - 1 : 0] : (T)0;
+        const int pk = i <= M ? S.k[i <= M ? i - 1 : 0] : 0;
+        const T bl = i >= 2 ? S.l[i >= 2 ? i - 2 : 0] : inf, bj = i >= 2 ? S.j[i >= 2 ? i - 2 : 0] : (T)0;
+        const int bk = i >= 2 ? S.k[i >= 2 ? i - 2 : 0] : s - 1;
+        const T ml = le[i - 1] ? di : bl, mj = le[i - 1] ? cj : bj;
+        const int dk = is_end ? 0 : bk;  // the split piece's tag
+        const int mk = le[i - 1] ? dk : bk;
+        l[i] = le[i] ? pl : ml;
+        J[i] = le[i] ? pj : mj;
+        k[i] = le[i] ? pk : mk;
+        k[i] = (is_end && i == t0) ? s - 1 : k[i];  // the old back's right piece is now interior
+    }
+    const int t = t0 + (ins ? 1 : 0);
+    const T basel = lop - yi - ci, baser = hip - yi + ci, v = root ? (T)0 : lo;
+    // left crossing: E the last entry with h(l+) < v, G the one after it
+    T El = (T)0, Ev = (T)0, Gl = inf, Gv = inf;
+    int Ek = 0, Gk = 0, p = 0;
+    bool jump = false, prev = true;
+    const T vl1 = l[1] + basel;
+    T vl = vl1;
+#pragma unroll
+    for (int i = 1; i <= M + 1; ++i) {
+        const T vr = vl + J[i];
+        const bool br = vr < v, g = prev && !br;
+        El = br ? l[i] : El;
+        Ev = br ? vr : Ev;
+        Ek = br ? k[i] : Ek;
+        p = br ? i : p;
+        Gl = g ? l[i] : Gl;
+        Gv = g ? vr : Gv;
+        Gk = g ? k[i] : Gk;
+        jump = g ? vl < v : jump;
+        prev = br;
+        if (i <= M) vl = vr + (T)(s - k[i]) * (l[i + 1] - l[i]);
+    }
+    const bool p0 = p == 0, pe = p == t;
+    const T sl = pe ? (T)1 : (T)(s - Ek);
+    const T lin = clampv(El + (v - Ev) * recip(sl), El, Gl);
+    T lm = p0 ? l[1] - (vl1 - v) : lin;
+    lm = t == 0 ? v - basel : lm;
+    lm = jump ? Gl : lm;
+    // (b) the new front, in the place of the first f entries: flat at lo left of it
+    const int f = p + (jump ? 1 : 0);
+    const T jm = Gv - lo, JF = jump ? (jm < (T)0 ? (T)0 : jm) : (T)0;
+    const int kj = p + 1 == t ? 0 : Gk, kn = pe ? 0 : (p0 ? s - 1 : Ek), kF = jump ? kj : kn;
+    // the front at position 1, the entries after f from position 2 on
+    const bool up = f == 0;
+    const int sh = up ? 0 : f - 1;
+#pragma unroll
+    for (int i = N - 1; i >= 2; --i) {
+        l[i] = up ? l[i - 1] : l[i];
+        J[i] = up ? J[i - 1] : J[i];
+        k[i] = up ? k[i - 1] : k[i];
+    }
+#pragma unroll
+    for (int b = 1; b <= M; b *= 2) {
+        const bool on = (sh & b) != 0;
+#pragma unroll
+        for (int i = 2; i < N; ++i) {
+            l[i] = on ? (i + b < N ? l[i + b < N ? i + b : 0] : inf) : l[i];
+            J[i] = on ? (i + b < N ? J[i + b < N ? i + b : 0] : (T)0) : J[i];
+            k[i] = on ? (i + b < N ? k[i + b < N ? i + b : 0] : 0) : k[i];
+        }
+    }
+    l[1] = lm;
+    J[1] = JF;
+    k[1] = kF;
+    const int t1 = t - f + 1;
+    // (c) right crossing, from the back: U the last entry with h(l+) <= hi, V the one after it
+    T Ul = (T)0, Uu = (T)0, Vl = (T)0, Vu = (T)0;
+    int Uk = 0, R = 0;
+    bool found = false, Vc = false;
+    T ul = (T)0, lnext = (T)0;
+#pragma unroll
+    for (int i = N - 1; i >= 1; --i) {
+        const T top = l[i] + baser, in = ul - (T)(s - k[i]) * (lnext - l[i]);
+        const T ur = i == t1 ? top : in;
+        ul = ur - J[i];
+        lnext = l[i];
+        const bool on = i <= t1 && !found, cR = ur <= hi, u = on && cR, w = on && !cR;
+        Ul = u ? l[i] : Ul;
+        Uu = u ? ur : Uu;
+        Uk = u ? k[i] : Uk;
+        R = u ? i : R;
+        Vl = w ? l[i] : Vl;
+        Vu = w ? ul : Vu;
+        Vc = w ? (i == 1 || ul <= hi) : Vc;
+        found = found || u;
+    }
+    const bool end = found && R == t1, jr = !end && Vc;
+    const T mid = clampv(Vl - (Vu - hi) * recip((T)(s - Uk)), Ul, Vl);
+    T lp = end ? Ul + (hi - Uu) : mid;
+    lp = jr ? Vl : lp;
+    const T jb = hi - Vu, JB = jr ? (jb < (T)0 ? (T)0 : jb) : (T)0;
+    const int r = R + 1;  // the new back: flat at hi right of it
+#pragma unroll
+    for (int i = 1; i <= N; ++i) {
+        const int m = i < N ? i : 0;
+        const int ki = (end && i == t1) ? s - 1 : k[m];
+        const bool in = i < r && i < N, at = i == r;
+        S.l[i - 1] = in ? l[m] : (at ? lp : inf);
+        S.j[i - 1] = in ? J[m] : (at ? JB : (T)0);
+        S.k[i - 1] = in ? ki : 0;
+    }
+    S.t = r;
+    lm_out = lm;
+    lp_out = lp < lm ? lm : lp;
+}
+
 #pragma clang fp contract(fast)
 }  // namespace tvc

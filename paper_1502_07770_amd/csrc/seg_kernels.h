@@ -94,11 +94,12 @@ constexpr int kSaves = 3 + kCheckpoints;  // HS, CK..., ES, ES2
 // The rings of the TV deque (tags in the working precision) copy twice as
 // many, so that a window twice as wide needs no wrap either: the 2D
 // iterations' deques often hold 8 to 15 breakpoints.  The general DP's FP32
-// rings (FP64 prefix-sum tags, 16-byte entries, shallow deques) and the TV-l1
-// sets (TagJ entries, which no window reads) keep kRingCopies.
+// rings (FP64 prefix-sum tags, 16-byte entries, shallow deques) keep
+// kRingCopies; the TV-l1 sets (TagJ entries, which no window reads) copy none,
+// so that four waves' 16-slot rings (32 KiB each) share a CU.
 constexpr int kRingCopies = 8;
 template <typename T, typename G> constexpr int ring_copies() {
-    return std::is_same<T, G>::value ? 2 * kRingCopies : kRingCopies;
+    return std::is_same<G, TagJ<T>>::value ? 0 : (std::is_same<T, G>::value ? 2 * kRingCopies : kRingCopies);
 }
 // Nodes the backward sweep loads ahead of their use.
 constexpr int kSweepTile = 16;
@@ -230,7 +231,7 @@ struct CRing {
         col[m * 64] = e;
         if constexpr (kAll)
             col[(m + K) * 64] = e;
-        else
+        else if constexpr (kCopies > 0)
             col[(m < kCopies ? m + K : m) * 64] = e;  // other slots: the same slot again
     }
     // The slot after the back holds a +inf breakpoint (dp_step_ring's
@@ -753,19 +754,9 @@ __device__ __forceinline__ void node_step(CRing<T, K, typename Prob::Tag> &R, bo
                                           const typename Prob::Src &src, const typename Prob::Pre &pv,
                                           CarryOf<T, Prob> &cy, T &lm, T &lp) {
     const bool root = (i == n - 1);
-    if constexpr (IsL1<Prob>::value) {
-        const T wi = src.weight(pv);
-        const T w = root ? (T)0 : wi;
-        L1Ring<T, K> S(R);
-        l1_step<T>(S, (T)(int)(i + 1), src.data(pv), src.dval(pv), src.cval(pv), -cy.wprev, cy.wprev, -w, w, root,
-                   lm, lp);
-        cy.wprev = wi;
-        ok = ok & (!S.ovf | root);
-    } else {
-        const auto in = step_in<T, Prob>(src, pv, i, root, cy);
-        const bool fits = dp_step_ring<T, typename Prob::Tag, K, Prob::kGen>(R, in, lm, lp);
-        ok = ok & (fits | root);
-    }
+    const auto in = step_in<T, Prob>(src, pv, i, root, cy);
+    const bool fits = dp_step_ring<T, typename Prob::Tag, K, Prob::kGen>(R, in, lm, lp);
+    ok = ok & (fits | root);
     if (root) lp = lm;
 }
 
@@ -884,6 +875,104 @@ __device__ __forceinline__ int64_t fwd_run_t(CRing<T, K, typename Prob::Tag> &R,
     return b;
 }
 
+// The forward run of a TV-l1 problem: the set lives in registers (l1_step_regs)
+// while every lane's holds at most five breakpoints and goes to the ring, whose
+// step takes any size, where one outgrows that; the ring holds it at the run's
+// ends and whenever hook is called.  One copy of the node code, four nodes'
+// data loaded four nodes ahead.  (The unrolled tiles of fwd_run_t would hold
+// the step 96 times.)
+template <typename T, class Prob, int K, int P, bool kStore, class Hook>
+__device__ __forceinline__ int64_t fwd_run_l1(CRing<T, K, typename Prob::Tag> &R, const typename Prob::Src &src,
+                                              bool &ok, CarryOf<T, Prob> &cy, int64_t from, int64_t b, int64_t n,
+                                              LamPair<T> *lam, int64_t C, int64_t c, Hook hook) {
+    L1Regs<T> S;
+    const T inf = pos_inf<T>();
+    auto to_regs = [&]() {
+#pragma unroll
+        for (int j = 0; j < kL1Regs; ++j) {
+            const bool on = j < R.size;
+            const auto e = R.ld(on ? j : 0);
+            S.l[j] = on ? e.l : inf;
+            S.j[j] = on ? e.k.j : (T)0;
+            S.k[j] = on ? (int)e.k.k : 0;
+        }
+        S.t = R.size;
+    };
+    auto to_ring = [&]() {
+        R.head = 0;
+        R.size = S.t;
+#pragma unroll
+        for (int j = 0; j < kL1Regs; ++j)
+            if (j < S.t) R.set(j, mk_ent<T, TagJ<T>>(S.l[j], TagJ<T>{(T)S.k[j], S.j[j]}));
+        R.seal();
+    };
+    bool regs = !__ballot(R.size > kL1Regs - 3);
+    if (regs) to_regs();
+    const bool vec = !__ballot(!src.vec);
+    typename Prob::Pre cur[4], nxt[4];
+    auto fetch = [&](int64_t i, typename Prob::Pre (&o)[4]) {
+        typename Prob::Pre v[4];
+        if (vec && i + 3 < b) {
+            src.load4(i, v);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = src.load(i + j < b ? i + j : b - 1);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = v[j];
+    };
+    fetch(from, cur);
+    LamPair<T> *lq = lam + from * C + c;
+    for (int64_t i0 = from; i0 < b; i0 += 4) {
+        fetch(i0 + 4 < b ? i0 + 4 : b - 1, nxt);
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            const int64_t i = i0 + q;
+            if (i >= b) break;
+            const bool root = i == n - 1;
+            const T wi = src.weight(cur[0]), w = root ? (T)0 : wi;
+            const T yi = src.data(cur[0]), di = src.dval(cur[0]), ci = src.cval(cur[0]);
+            T lm = (T)0, lp = (T)0;
+            if (regs && __ballot(S.t > kL1Regs - 3)) {
+                to_ring();
+                regs = false;
+            }
+            if (regs) {
+                if (!__ballot(S.t > 3))
+                    l1_step_regs<T, 3>(S, (int)i + 1, yi, di, ci, -cy.wprev, cy.wprev, -w, w, root, lm, lp);
+                else
+                    l1_step_regs<T, kL1Regs - 3>(S, (int)i + 1, yi, di, ci, -cy.wprev, cy.wprev, -w, w, root, lm, lp);
+            } else {
+                L1Ring<T, K> Q(R);
+                l1_step<T>(Q, (T)(int)(i + 1), yi, di, ci, -cy.wprev, cy.wprev, -w, w, root, lm, lp);
+                ok = ok & (!Q.ovf | root);
+                if (!__ballot(R.size > kL1Regs - 3)) {
+                    to_regs();
+                    regs = true;
+                }
+            }
+            cy.wprev = wi;
+            if (kStore) {
+                LamPair<T> pr;
+                pr.lo = lm;
+                pr.hi = root ? lm : lp;
+                *lq = pr;
+                lq += C;
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) cur[j] = cur[j + 1];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) cur[j] = nxt[j];
+        if (i0 + 4 <= b && (i0 + 4 - from) % P == 0) {
+            if (regs) to_ring();
+            if (hook(i0 + 4)) return i0 + 4;
+        }
+    }
+    if (regs) to_ring();
+    return b;
+}
+
 // A source whose vec is a compile-time false never takes the 16-byte path.
 template <class S, class = void> struct NeverVec : std::false_type {};
 template <class S> struct NeverVec<S, std::enable_if_t<!S::vec>> : std::true_type {};
@@ -896,11 +985,13 @@ template <typename T, class Prob, int K, int P, bool kStore, class Hook>
 __device__ __forceinline__ int64_t fwd_run(CRing<T, K, typename Prob::Tag> &R, const typename Prob::Src &src,
                                            bool &ok, CarryOf<T, Prob> &cy, int64_t from, int64_t b, int64_t n,
                                            LamPair<T> *lam, int64_t C, int64_t c, Hook hook) {
-    if constexpr (!NeverVec<typename Prob::Src>::value) {
+    if constexpr (IsL1<Prob>::value) return fwd_run_l1<T, Prob, K, P, kStore>(R, src, ok, cy, from, b, n, lam, C, c, hook);
+    if constexpr (!NeverVec<typename Prob::Src>::value && !IsL1<Prob>::value) {
         if (__ballot(!src.vec) == 0)
             return fwd_run_t<T, Prob, K, P, kStore, true>(R, src, ok, cy, from, b, n, lam, C, c, hook);
     }
-    return fwd_run_t<T, Prob, K, P, kStore, false>(R, src, ok, cy, from, b, n, lam, C, c, hook);
+    if constexpr (!IsL1<Prob>::value)
+        return fwd_run_t<T, Prob, K, P, kStore, false>(R, src, ok, cy, from, b, n, lam, C, c, hook);
 }
 
 // Backward clip pass over [a, b) of one chain.  All lanes of a wave share a and

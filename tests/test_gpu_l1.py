@@ -210,3 +210,27 @@ def test_rejects_bad_arguments():
             binding.chain_prox_l1(y, y.clone(), bad, 1.0)
         with pytest.raises(binding.TvChainError):
             binding.chain_prox_l1(y, y.clone(), 0.5, bad)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("w,c", [(0.55, 1.0), (0.3, 0.0), (4.0, 0.7), (30.0, 1.0)])
+def test_register_step_equals_ring_step(dtype, w, c):
+    """A wave's sets stay in registers while its largest holds at most five breakpoints and go
+    to the ring otherwise: the same chains give the same bits alone and next to a chain (one
+    per wave) whose set holds dozens, along rows and columns, at lengths around the four-node
+    groups and with some weights and data terms zero."""
+    for n in (1, 2, 3, 5, 8, 65, 250):
+        y = synth.salt_pepper_chains(63, n, seed=n)
+        deep = np.sqrt(np.arange(n))[None, :] * 3.0
+        wn, cn = np.full((64, n), w), np.full((64, n), c)
+        wn[5], cn[7] = 0.0, 0.0
+        wn[63], cn[63] = 50.0, 0.01
+        both = _dev(np.concatenate([y, deep]), dtype)
+        d = _dev(np.concatenate([np.roll(y, 1, axis=1), deep + 0.01]), dtype)
+        wt, ct = _dev(wn, dtype), _dev(cn, dtype)
+        all_ = binding.chain_prox_l1(both, d, wt, ct, dim=1)
+        few = binding.chain_prox_l1(both[:63].contiguous(), d[:63].contiguous(), wt[:63].contiguous(),
+                                    ct[:63].contiguous(), dim=1)
+        assert torch.equal(all_[:63], few), n
+        cols = binding.chain_prox_l1(*(t.t().contiguous() for t in (both, d, wt, ct)), dim=0)
+        assert torch.equal(cols.t(), all_), n
