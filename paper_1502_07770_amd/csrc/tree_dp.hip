@@ -333,6 +333,321 @@ __device__ __forceinline__ void tree_rank_merge(const TreeWs &W, int64_t cs, int
 // waves per SIMD to hide that latency.
 constexpr int kTreeLanes = 64;
 
+// ---------------------------------------------------------------------------
+// Sixteen lanes (a DPP row) per tree.  Messages are small (random trees of 256
+// nodes with l1 terms: at most 8 breakpoints before the clip in 99% of the
+// nodes, at most 14 in all but a few in a hundred thousand and in the roots that
+// take every pending subtree), so a node's whole message sits one breakpoint
+// per lane:
+//  - the children's runs and the unary's breakpoint are loaded side by side and
+//    sorted once by rank (a lane counts the breakpoints before its own);
+//  - a scan gives every lane the linear piece A z + B right of its breakpoint;
+//  - every lane forms the crossings on its piece, and masks pick the lanes
+//    whose crossing is the new front and the new back.
+// Nothing walks, where a lane per tree ran its own serial walk through memory
+// and a wave every lane's path: 16,384 trees x 256 nodes took 5.7 ms (22 us a
+// node on 256 waves), 65,536 trees 9.0 ms.  Larger messages, up to kTreeWide, are
+// cut where they lie (tree_cut, tree_wide); a tree with one beyond that, or
+// with an invalid numbering, is left to the lane-per-tree kernel.
+// ---------------------------------------------------------------------------
+constexpr int kTreeRow = 16;
+constexpr int kTreeMost = kTreeRow - 2;  // a lane past the last breakpoint and one before the first
+// A message of this many breakpoints takes about as long in tree_cut (twice,
+// a dozen passes of t / 16 loads) as in the lane kernel's merge and scans.
+constexpr int kTreeWide = 128;
+constexpr int64_t kTreeDone = -1, kTreeRedo = -2;  // THdr.start of a tree's first header slot
+
+// Each lane of a row another lane's value (DPP control; lanes without a source read 0).
+template <int CTRL> __device__ __forceinline__ double row_mov(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)b, CTRL, 0xf, 0xf, true);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double row_next(double v) { return row_mov<0x12F>(v); }  // row_ror:15
+__device__ __forceinline__ double row_prev(double v) { return row_mov<0x121>(v); }  // row_ror:1
+__device__ __forceinline__ unsigned row_bits(bool p, int lane) {
+    return (unsigned)(__ballot(p) >> (lane & 48)) & 0xffffu;
+}
+// Inclusive prefix sum, and the sum over the row.
+__device__ __forceinline__ double row_scan(double v) {
+    v += row_mov<0x111>(v);  // row_shr:1, 2, 4, 8
+    v += row_mov<0x112>(v);
+    v += row_mov<0x114>(v);
+    v += row_mov<0x118>(v);
+    return v;
+}
+__device__ __forceinline__ double row_sum(double v) { return row_mov<0x15F>(row_scan(v)); }  // row_newbcast:15
+// Breakpoints before this lane's (ties in lane order): a permutation of the row.
+template <int D> __device__ __forceinline__ int row_before(double l, int j) {
+    const double o = row_mov<0x120 + D>(l);  // row_ror:D
+    return (j >= D ? o <= l : o < l) ? 1 : 0;
+}
+__device__ __forceinline__ int row_rank(double l, int j) {
+    return row_before<1>(l, j) + row_before<2>(l, j) + row_before<3>(l, j) + row_before<4>(l, j) +
+           row_before<5>(l, j) + row_before<6>(l, j) + row_before<7>(l, j) + row_before<8>(l, j) +
+           row_before<9>(l, j) + row_before<10>(l, j) + row_before<11>(l, j) + row_before<12>(l, j) +
+           row_before<13>(l, j) + row_before<14>(l, j) + row_before<15>(l, j);
+}
+// This lane's value to lane `to` of its row.
+__device__ __forceinline__ double row_send(double v, int lane, int to) {
+    const int addr = ((lane & 48) + to) * 4;
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_ds_permute(addr, (int)(unsigned)b);
+    const unsigned hi = (unsigned)__builtin_amdgcn_ds_permute(addr, (int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+// Where A z + B plus the increments of the t breakpoints at s (in any order) and
+// of a jump at d crosses zero: z, the piece left of it (A, B) and right of it
+// (A2, B2, another one at a jump), and the bounds between which the
+// breakpoints right (l > left) and left (l < right) of it lie.  The bracket of
+// the zero shrinks from pivot to pivot; the sums of the breakpoints left of it
+// are kept.
+struct TCut {
+    double z, A, B, A2, B2, left, right;
+};
+__device__ TCut tree_cut(const TreeWs &W, int64_t s, int t, double A, double B, double d, double jump, int lane) {
+    const double inf = __builtin_huge_val();
+    const int j = lane & 15, n = t + (jump > 0.0 ? 1 : 0);
+    auto get = [&](int k) { return k < t ? tb_get(W, s + k) : TBp{d, 0.0, jump, 0.0}; };
+    double lo = -inf, hi = inf;
+    for (int it = 0; it <= n; ++it) {  // every pivot leaves the bracket
+        // a pivot: a breakpoint inside it, of the middle one of the lanes that hold one
+        double q = inf;
+        for (int k = j; k < n; k += kTreeRow) {
+            const double l = get(k).l;
+            q = l > lo && l < hi ? l : q;
+        }
+        unsigned m = row_bits(q < inf, lane);
+        if (!m) break;
+        for (int half = __popc(m) / 2; half > 0; --half) m &= m - 1;
+        q = __shfl(q, (lane & 48) + __ffs(m) - 1, 64);
+        double a1 = 0.0, b1 = 0.0, a2 = 0.0, b2 = 0.0;
+        for (int k = j; k < n; k += kTreeRow) {
+            const TBp e = get(k);
+            const bool in = e.l > lo && e.l < q, at = e.l == q;
+            a1 += in ? e.a : 0.0;
+            b1 += in ? e.b : 0.0;
+            a2 += at ? e.a : 0.0;
+            b2 += at ? e.b : 0.0;
+        }
+        a1 = A + row_sum(a1);
+        b1 = B + row_sum(b1);
+        a2 = a1 + row_sum(a2);
+        b2 = b1 + row_sum(b2);
+        if (a1 * q + b1 >= 0.0) {
+            hi = q;
+        } else if (a2 * q + b2 >= 0.0) {
+            return TCut{q, a1, b1, a2, b2, q, q};
+        } else {
+            lo = q;
+            A = a2;
+            B = b2;
+        }
+    }
+    double z = -B / A;
+    z = z > hi ? hi : z;
+    z = z < lo ? lo : z;
+    return TCut{z, A, B, A, B, lo, hi};
+}
+
+// The clip of a message too large for a row: cut at both levels, the
+// breakpoints between them moved together in place (the next sort orders
+// them).  Returns the new count.
+__device__ int tree_wide(const TreeWs &W, int64_t s, int t, double A, double B, double d, double jump, double lo,
+                         double hi, int lane, TLam *z) {
+    const int j = lane & 15, n = t + (jump > 0.0 ? 1 : 0);
+    const TCut p = tree_cut(W, s, t, A, B - lo, d, jump, lane);
+    TCut r = tree_cut(W, s, t, A, B - hi, d, jump, lane);
+    r.z = r.z < p.z ? p.z : r.z;
+    *z = TLam{p.z, r.z};
+    int m = 0;
+    for (int k0 = 0; k0 < n; k0 += kTreeRow) {
+        const int k = k0 + j;
+        const TBp e = k < t ? tb_get(W, s + k) : TBp{d, 0.0, jump, 0.0};
+        const bool keep = k < n && e.l > p.left && e.l < r.right;
+        const unsigned kept = row_bits(keep, lane);
+        if (keep) tb_put(W, s + m + __popc(kept & ((1u << j) - 1)), e);
+        m += __popc(kept);
+        __threadfence_block();
+    }
+    const bool one = p.left == r.right && p.left == p.z;  // both levels in one jump
+    if (j == 0) {
+        if (one) {
+            tb_put(W, s + m, TBp{p.z, 0.0, hi - lo, 0.0});
+        } else {
+            tb_put(W, s + m, TBp{p.z, p.A2, p.B2, 0.0});
+            tb_put(W, s + m + 1, TBp{r.z, -r.A, -r.B, 0.0});
+        }
+    }
+    return m + (one ? 1 : 2);
+}
+
+template <typename T>
+__global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, const T *__restrict__ a,
+                                                 const T *__restrict__ b, const T *__restrict__ c,
+                                                 const T *__restrict__ d, const T *__restrict__ wm,
+                                                 const T *__restrict__ wp, T *__restrict__ x) {
+    const double inf = __builtin_huge_val();
+    const int lane = threadIdx.x, j = lane & 15;
+    const bool pre = j == 15;  // stands before the first breakpoint
+    const int64_t tr = (int64_t)blockIdx.x * 4 + (lane >> 4);
+    if (tr >= tb.num_trees) return;  // whole rows
+    const int64_t n0 = tb.offsets[tr], n1 = tb.offsets[tr + 1];
+    if (n1 <= n0) return;
+    int64_t top = 6 * n0 + 16 * tr, sp = 0;  // end of the pending runs in this tree's arena; pending messages
+    const int64_t aend = top + 6 * (n1 - n0) + 16;
+    THdr h0{0, 0, 0, -1, 0.0, 0.0}, h1 = h0;  // the last two of them
+    bool ok = true;
+    auto load_in = [&](int64_t i) {
+        TIn q;
+        q.a = a ? (double)a[i] : 1.0;
+        q.b = (double)b[i];
+        q.c = c ? (double)c[i] : 0.0;
+        q.d = d ? (double)d[i] : 0.0;
+        q.lo = (double)wm[i];
+        q.hi = (double)wp[i];
+        q.p = tb.parent[i];
+        return q;
+    };
+    TIn nx = load_in(n0);
+    for (int64_t i = n0; i < n1; ++i) {
+        const TIn in = nx;
+        if (i + 1 < n1) nx = load_in(i + 1);
+        // (a) the children's runs, side by side: the top headers whose node is i
+        // (their regions are contiguous and end at the old top)
+        double bl = -in.b - in.c;
+        int64_t src = -1, t64 = 0;
+        while (sp > 0 && h0.parent == i) {
+            if (j >= t64 && j < t64 + h0.count) src = h0.start + (j - t64);
+            t64 += h0.count;
+            bl += h0.lo;
+            top = h0.start;
+            --sp;
+            h0 = h1;
+            if (sp > 1) h1 = W.hdr[n0 + sp - 2];
+        }
+        const bool data = in.c > 0.0, root = in.p < 0;
+        const double lo = root ? 0.0 : in.lo, hi = in.hi;
+        if ((!root && (in.p <= i || in.p >= n1)) || t64 > (root ? (int64_t)1 << 30 : kTreeWide)) {
+            ok = false;
+            break;
+        }
+        int t = (int)t64, count;
+        if (t + (data ? 1 : 0) > kTreeMost) {
+            const double jump = data ? 2.0 * in.c : 0.0;
+            TLam z;
+            if (root) {  // the zero of h
+                z.lo = z.hi = tree_cut(W, top, t, in.a, bl, in.d, jump, lane).z;
+                count = 0;
+            } else {
+                if (top + t + 3 > aend) {
+                    ok = false;
+                    break;
+                }
+                count = tree_wide(W, top, t, in.a, bl, in.d, jump, lo, hi, lane, &z);
+            }
+            if (j == 0) W.lam[i] = z;
+        } else {
+            TBp e{inf, 0.0, 0.0, 0.0};
+            if (src >= 0) e = tb_get(W, src);
+            // (b) the unary's breakpoint after them
+            if (data && j == t) e = TBp{in.d, 0.0, 2.0 * in.c, 0.0};
+            if (data) ++t;
+            if (t > 1) {
+                const int r = row_rank(e.l, j);
+                const double sl = row_send(e.l, lane, r), sa = row_send(e.a, lane, r), sb = row_send(e.b, lane, r);
+                e.l = sl;
+                e.a = sa;
+                e.b = sb;
+            }
+            // the piece right of each breakpoint; the lane before the first has the left end's
+            double A = row_scan(e.a) + in.a, B = row_scan(e.b) + bl;
+            A = pre ? in.a : A;
+            B = pre ? bl : B;
+            const bool entry = j < t;
+            const double ln = row_next(e.l), vr = A * e.l + B, ve = A * ln + B;
+            // (c) clip to [wm_i, wp_i] (root: the zero of h)
+            const int p = __ffs(~row_bits(entry && vr < lo, lane)) - 1;  // breakpoints left of lambda^-
+            const bool jl = (row_bits(ve < lo, lane) >> ((p + 15) & 15)) & 1;  // at breakpoint p's jump
+            const int F = jl ? p : (p + 15) & 15;
+            double zl = (lo - B) / A;
+            zl = zl > ln ? ln : zl;
+            zl = (!pre && zl < e.l) ? e.l : zl;
+            const double lm = jl ? e.l : zl;  // at lane F
+            const int r0 = __ffs(~row_bits(entry && vr <= hi, lane)) - 1, r = r0 < p ? p : r0;  // left of lambda^+
+            const bool one = jl && r == p;                                                       // both in one jump
+            const bool jr = (row_bits(ve <= hi, lane) >> ((r + 15) & 15)) & 1;
+            const double lf = j == F ? lm : e.l;  // the positions with the new front
+            const double Ap = row_prev(A), Bp = row_prev(B), lp0 = row_prev(lf);
+            double zr = (hi - Bp) / Ap;
+            zr = zr > e.l ? e.l : zr;
+            zr = zr < lp0 ? lp0 : zr;
+            const double lp = jr ? e.l : zr;  // at lane r
+            if (j == F) {
+                e.l = lm;
+                e.a = one ? 0.0 : A;
+                e.b = one ? hi - lo : B - lo;
+            } else if (j == r) {
+                e.l = lp;
+                e.a = -Ap;
+                e.b = hi - Bp;
+            }
+            count = root ? 0 : (one ? 1 : ((r - F) & 15) + 1);
+            if (top + count > aend) {
+                ok = false;
+                break;
+            }
+            const int m = (j - F) & 15;
+            if (m < count) tb_put(W, top + m, e);
+            if (j == F) W.lam[i].lo = lm;
+            if (j == (one || root ? F : r)) W.lam[i].hi = e.l;
+        }
+        // push the clipped message for the parent
+        if (!root) {
+            h1 = h0;
+            h0 = THdr{top, count, 0, in.p, lo, hi};
+            if (j == 0) W.hdr[n0 + sp] = h0;
+            ++sp;
+            top += count;
+        }
+        __threadfence_block();
+    }
+    if (!ok || sp != 0) {
+        if (j == 0) W.hdr[n0].start = kTreeRedo;
+        return;
+    }
+    // backward pass, sixteen nodes at a time from the last: parents have higher
+    // numbers, so a node waits for lanes below its own or for earlier rounds
+    for (int64_t hi = n1 - 1; hi >= n0; hi -= kTreeRow) {
+        const int64_t i = hi - j;
+        const bool in = i >= n0;
+        const int64_t p = in ? tb.parent[i] : -1;
+        const TLam z = in ? W.lam[i] : TLam{0.0, 0.0};
+        bool ready = !in || p < 0 || p > hi;
+        double v = z.lo;
+        if (in && p > hi) {
+            v = (double)x[p];
+            v = v < z.lo ? z.lo : (v > z.hi ? z.hi : v);
+        }
+        v = (double)(T)v;
+        const int from = (lane & 48) + (ready ? j : (int)(hi - p));
+        while (row_bits(!ready, lane)) {
+            const double u = __shfl(v, from, 64);
+            const bool go = __shfl((int)ready, from, 64) != 0;
+            if (!ready && go) {
+                v = (double)(T)(u < z.lo ? z.lo : (u > z.hi ? z.hi : u));
+                ready = true;
+            }
+        }
+        if (in) x[i] = (T)v;
+        __threadfence_block();
+    }
+    if (j == 0) W.hdr[n0].start = kTreeDone;
+}
+
+// A lane per tree, for the trees that k_tree_row left (see its W.hdr marks).
 template <typename T>
 __global__ __launch_bounds__(64) void k_tree_dp(TreeBatch tb, TreeWs W, const T *__restrict__ a,
                                                 const T *__restrict__ b, const T *__restrict__ c,
@@ -342,7 +657,7 @@ __global__ __launch_bounds__(64) void k_tree_dp(TreeBatch tb, TreeWs W, const T 
     const int64_t tr = (int64_t)blockIdx.x * lanes + threadIdx.x;
     if (tr >= tb.num_trees) return;
     const int64_t n0 = tb.offsets[tr], n1 = tb.offsets[tr + 1];
-    if (n1 <= n0) return;
+    if (n1 <= n0 || W.hdr[n0].start != kTreeRedo) return;
     const int64_t abase = 6 * n0 + 16 * tr;     // this tree's arena
     const int64_t aend = abase + 6 * (n1 - n0) + 16;
     int64_t top = abase;                          // end of the pending stack's regions
@@ -581,6 +896,8 @@ hipError_t launch_tree_dp_lanes(int64_t num_trees, int64_t num_nodes, const int6
     hipError_t e = hipMemsetAsync(W.bad, 0, sizeof(int), stream);
     if (e != hipSuccess) return e;
     const TreeBatch tb{num_trees, offsets, parent};
+    hipLaunchKernelGGL((k_tree_row<T>), dim3((unsigned)((num_trees + 3) / 4)), dim3(64), 0, stream, tb, W, a, b, c, d, wm,
+                       wp, x);
     hipLaunchKernelGGL((k_tree_dp<T>), dim3((unsigned)((num_trees + lanes - 1) / lanes)), dim3(64), 0, stream, tb, W,
                        a, b, c, d, wm, wp, x, lanes);
     e = hipGetLastError();

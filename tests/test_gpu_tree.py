@@ -102,3 +102,42 @@ def test_full_size_sample_fp32():
     arrays = [v.double().cpu().numpy() for v in dev]
     rng = np.random.default_rng(3)
     _check(par, off, arrays, x, rng.choice(65536, 300, replace=False), 1e-5)
+
+
+def _stars_and_chains():
+    """Trees around the sizes at which a message outgrows a row of lanes or goes to the lane
+    kernel: k leaves under a root, k leaves under an inner node (k up to 300), chains with
+    large weights (deques of hundreds) and an inner node over two such chains."""
+    trees = []
+    for k in (1, 4, 5, 6, 7, 13, 14, 15, 16, 40, 41, 42, 43, 130, 300):
+        trees.append([k] * k + [-1])
+        trees.append([k] * k + [k + 1, -1])
+    for n in (2, 17, 200):
+        trees.append([j + 1 for j in range(n - 1)] + [-1])
+        trees.append([j + 1 for j in range(n - 1)] + [2 * n] + [n + j + 1 for j in range(n - 1)] + [2 * n, 2 * n + 1, -1])
+    par, off = [], [0]
+    for t in trees:
+        par += [p + off[-1] if p >= 0 else -1 for p in t]
+        off.append(off[-1] + len(t))
+    return np.array(par, dtype=np.int64), np.array(off, dtype=np.int64)
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-11), (torch.float32, 1e-5)])
+@pytest.mark.parametrize("kind", ["random", "ties", "wide weights", "no l1"])
+def test_message_sizes_match_oracle(dtype, tol, kind):
+    """The oracle on trees of every message size, with equal breakpoints (integer data), with
+    weights so large that nothing is clipped, and without l1 terms."""
+    par, off = _stars_and_chains()
+    N = par.size
+    a, b, c, d, wm, wp = _tree_data(N, seed=21, l1=kind != "no l1")
+    if kind == "ties":
+        rng = np.random.default_rng(22)
+        a, b = np.ones(N), rng.integers(-2, 3, N).astype(float)
+        c, d = rng.integers(0, 2, N).astype(float), rng.integers(-1, 2, N).astype(float)
+        wm, wp = -rng.integers(0, 3, N).astype(float), rng.integers(0, 3, N).astype(float)
+    if kind == "wide weights":
+        wm, wp = 40.0 * wm - 20.0, 40.0 * wp + 20.0
+    dev = [torch.tensor(v, dtype=dtype, device="cuda") for v in (a, b, c, d, wm, wp)]
+    x = binding.tree_dp(torch.tensor(par, device="cuda"), torch.tensor(off, device="cuda"), dev[1], dev[4], dev[5],
+                        a=dev[0], c=dev[2] if kind != "no l1" else None, d=dev[3] if kind != "no l1" else None)
+    _check(par, off, [v.double().cpu().numpy() for v in dev], x.double().cpu().numpy(), range(off.size - 1), tol)
