@@ -387,7 +387,7 @@ __global__ __launch_bounds__(64) void k_nc_chain(NcArgs A, const T *__restrict__
 //   f^2: the same on the reversed view; f^3: a wave minimum and per piece the
 //     crossing of min h + C;
 // each pass ends with a prefix count that places the points it emits.  The
-// backward pass is one lane's.  Instantiated for messages of up to 128 and up
+// backward pass looks an edge's intervals up by the whole wave.  Instantiated for messages of up to 128 and up
 // to 256 breakpoints (16 and 32 KiB of LDS per wave), the smaller where
 // msg_cap allows, so that more waves fit on a CU.
 // ---------------------------------------------------------------------------
@@ -395,38 +395,99 @@ constexpr int kWaveMsg = 256;
 
 __device__ __forceinline__ int wv_lane() { return (int)threadIdx.x; }
 
+// Lane shifts and scans by DPP and row swaps: a shuffle through LDS costs about
+// 130 cycles of latency, six of them a scan, and a node's passes hold about
+// fifteen scans; these stay in the vector unit.
+template <int CTRL> __device__ __forceinline__ int wv_dpp(int old, int v) {
+    return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xf, 0xf, false);
+}
+// The row of 16 lanes before this one's (row 0: its own).
+__device__ __forceinline__ int wv_row_before(int v) {
+    const auto s = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    const auto q = __builtin_amdgcn_permlane32_swap(s[1], s[1], false, false);
+    return (int)((wv_lane() >> 4) == 2 ? q[0] : s[0]);
+}
+// The value D lanes below (lanes under D: anything).
+template <int D> __device__ __forceinline__ int wv_shr(int v) {
+    if constexpr (D == 32) {
+        return (int)__builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false)[0];
+    } else if constexpr (D == 16) {
+        return wv_row_before(v);
+    } else if constexpr (D == 8) {
+        const int r = wv_dpp<0x128>(0, v);  // row_ror:8
+        const int p = wv_row_before(r);
+        return (wv_lane() & 15) >= 8 ? r : p;
+    } else {
+#pragma unroll
+        for (int i = 0; i < D; ++i) v = wv_dpp<0x138>(v, v);  // wave_shr:1
+        return v;
+    }
+}
+template <int D> __device__ __forceinline__ double wv_shr(double v) {
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)wv_shr<D>((int)(unsigned)b), hi = (unsigned)wv_shr<D>((int)(b >> 32));
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ double wv_last(double v) {  // lane 63's, to all
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, 63);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), 63);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ int wv_last(int v) { return __builtin_amdgcn_readlane(v, 63); }
+
+// Inclusive prefix sum; every lane adds the same pairs in the same order
+// whatever the means of the shift (spans of 1, 2, 4, ... lanes).
 __device__ __forceinline__ double wv_scan_add(double x) {
     const int lane = wv_lane();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
+    double y = wv_shr<1>(x);
+    if (lane >= 1) x += y;
+    y = wv_shr<2>(x);
+    if (lane >= 2) x += y;
+    y = wv_shr<4>(x);
+    if (lane >= 4) x += y;
+    y = wv_shr<8>(x);
+    if (lane >= 8) x += y;
+    y = wv_shr<16>(x);
+    if (lane >= 16) x += y;
+    y = wv_shr<32>(x);
+    if (lane >= 32) x += y;
     return x;
 }
 
 __device__ __forceinline__ int wv_scan_int(int x) {
-    const int lane = wv_lane();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
+    x += wv_dpp<0x111>(0, x);  // row_shr:1, 2, 4, 8
+    x += wv_dpp<0x112>(0, x);
+    x += wv_dpp<0x114>(0, x);
+    x += wv_dpp<0x118>(0, x);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 to rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 to rows 2 and 3
     return x;
+}
+// Lanes below this one where p holds, and all of them.
+__device__ __forceinline__ int wv_count_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
 }
 
 // Inclusive prefix minimum; ties keep the earlier index.
+template <int CTRL, int ROWS> __device__ __forceinline__ void wv_min_step(double &v, int &i) {
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)(unsigned)b, hi = (int)(b >> 32);
+    const unsigned ol = (unsigned)__builtin_amdgcn_update_dpp(lo, lo, CTRL, ROWS, 0xf, false);
+    const unsigned oh = (unsigned)__builtin_amdgcn_update_dpp(hi, hi, CTRL, ROWS, 0xf, false);
+    const int io = __builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xf, false);  // lanes without a source: themselves
+    const double vo = __longlong_as_double((long long)(((unsigned long long)oh << 32) | ol));
+    const bool take = vo < v || (vo == v && io < i);
+    v = take ? vo : v;
+    i = take ? io : i;
+}
 __device__ __forceinline__ void wv_scan_min(double &v, int &i) {
-    const int lane = wv_lane();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const double vo = __shfl_up(v, d, 64);
-        const int io = __shfl_up(i, d, 64);
-        if (lane >= d && (vo < v || (vo == v && io < i))) {
-            v = vo;
-            i = io;
-        }
-    }
+    wv_min_step<0x111, 0xf>(v, i);
+    wv_min_step<0x112, 0xf>(v, i);
+    wv_min_step<0x114, 0xf>(v, i);
+    wv_min_step<0x118, 0xf>(v, i);
+    wv_min_step<0x142, 0xa>(v, i);
+    wv_min_step<0x143, 0xc>(v, i);
 }
 
 // A message in LDS, read as stored or reversed (phi^rev(z) = phi(-z)).
@@ -437,18 +498,6 @@ struct WView {
     __device__ __forceinline__ double l(int k) const { return rev ? -L[t - 1 - k] : L[k]; }
     __device__ __forceinline__ double s(int k) const { return rev ? -S[t - k] : S[k]; }
 };
-
-// first index in a[0..n) with a[idx] >= v (strict = false: > v)
-__device__ __forceinline__ int wv_lower(const double *a, int n, double v, bool strict) {
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const bool go = strict ? (a[mid] <= v) : (a[mid] < v);
-        if (go) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
 
 // Shared scratch of one wave.
 struct WScratch {
@@ -470,7 +519,7 @@ __device__ void wv_values(const WView &h, double *V) {
         const double d = (k >= 1 && k < h.t) ? h.s(k) * (h.l(k) - h.l(k - 1)) : 0.0;
         const double inc = wv_scan_add(d) + carry;
         if (k < h.t) V[k] = inc;
-        carry = __shfl(inc, 63, 64);
+        carry = wv_last(inc);
     }
     __syncthreads();
 }
@@ -483,17 +532,34 @@ __device__ int wv_sum(const double *ul, const double *us, int tu, const double *
     // record how many of each list lie at or before the element: for the last
     // element of a group of equal positions those are the counts of both lists
     // up to that position, which give the slope right of it
-    for (int i = wv_lane(); i < tu; i += 64) {
-        const int r = wv_lower(ml, tm, ul[i], false);
-        W.T[i + r] = ul[i];
-        W.CU[i + r] = i + 1;
-        W.CM[i + r] = r;
-    }
-    for (int j = wv_lane(); j < tm; j += 64) {
-        const int r = wv_lower(ul, tu, ml[j], true);
-        W.T[j + r] = ml[j];
-        W.CU[j + r] = r;
-        W.CM[j + r] = j + 1;
+    // (the two searches of a lane run side by side: their LDS reads overlap)
+    for (int i = wv_lane(); i < (tu > tm ? tu : tm); i += 64) {
+        const bool iu = i < tu, im = i < tm;
+        const double vu = ul[iu ? i : 0], vm = im ? ml[i] : 0.0;
+        int lo0 = 0, hi0 = iu ? tm : 0, lo1 = 0, hi1 = im ? tu : 0;
+        while (lo0 < hi0 || lo1 < hi1) {
+            const int mid0 = (lo0 + hi0) >> 1, mid1 = (lo1 + hi1) >> 1;
+            const bool b0 = lo0 < hi0, b1 = lo1 < hi1;
+            const double x0 = b0 ? ml[mid0] : 0.0, x1 = b1 ? ul[mid1] : 0.0;
+            if (b0) {
+                if (x0 < vu) lo0 = mid0 + 1;
+                else hi0 = mid0;
+            }
+            if (b1) {
+                if (x1 <= vm) lo1 = mid1 + 1;
+                else hi1 = mid1;
+            }
+        }
+        if (iu) {
+            W.T[i + lo0] = vu;
+            W.CU[i + lo0] = i + 1;
+            W.CM[i + lo0] = lo0;
+        }
+        if (im) {
+            W.T[i + lo1] = vm;
+            W.CU[i + lo1] = lo1;
+            W.CM[i + lo1] = i + 1;
+        }
     }
     __syncthreads();
     const int tot = tu + tm;
@@ -501,8 +567,8 @@ __device__ int wv_sum(const double *ul, const double *us, int tu, const double *
     for (int c = 0; c * 64 < tot; ++c) {
         const int k = c * 64 + wv_lane();
         const bool keep = k < tot && (k == 0 || W.T[k] != W.T[k - 1]);
-        const int inc = wv_scan_int(keep ? 1 : 0);
-        const int pos = base + inc - 1;
+        const unsigned long long kept = __ballot(keep);
+        const int pos = base + wv_count_below(kept);
         if (keep && pos < cap) {
             const double lam = W.T[k];
             int last = k;
@@ -510,10 +576,68 @@ __device__ int wv_sum(const double *ul, const double *us, int tu, const double *
             ol[pos] = lam;
             os[pos + 1] = us[W.CU[last]] + ms[W.CM[last]];
         }
-        base += __shfl(inc, 63, 64);
+        base += __popcll(kept);
     }
     if (wv_lane() == 0) os[0] = us[0] + ms[0];
     __syncthreads();
+    return base <= cap ? base : -1;
+}
+
+// wv_dt of a message of 1 .. 63 breakpoints: lane k holds breakpoint k and piece
+// k, neighbours come by lane shifts, places by counting ballots; nothing goes
+// through LDS but the message itself.
+__device__ int wv_dt_one(const WView &h, double w, double *ol, double *os, int cap, const NcMaps &mp, int64_t &nmap) {
+    const int t = h.t, k = wv_lane();
+    const double lk = k < t ? h.l(k) : 0.0, sk = k <= t ? h.s(k) : 0.0, lp = wv_shr<1>(lk);
+    const double V = wv_scan_add((k >= 1 && k < t) ? sk * (lk - lp) : 0.0) + 0.0;
+    const double g = k < t ? V - w * lk : HUGE_VAL;
+    double pm = g;
+    int pa = k;
+    wv_scan_min(pm, pa);
+    const double gl = wv_shr<1>(g), m = wv_shr<1>(pm), sig = sk - w;
+    const int pp = wv_shr<1>(pa);
+    const bool on = gl <= m, back = sig < 0.0 && (k == t || g <= m);
+    double ps, pe;
+    if (k == 0) {
+        ps = pe = sk;
+    } else if (on) {
+        ps = pe = sig < 0.0 ? sk : w;
+    } else {
+        ps = w;
+        pe = back ? sk : w;
+    }
+    const double pl = wv_shr<1>(pe);
+    const bool in = k >= 1 && k <= t, e1 = in && pl != ps, e2 = in && !on && back, flat = in && k == t && sig >= 0.0;
+    const double la = __shfl(lk, in ? pp : 0, 64);
+    double y = lp + (m - gl) / sig;
+    if (y < lp) y = lp;
+    if (k < t && y > lk) y = lk;
+    const unsigned long long b1 = __ballot(e1), b2 = __ballot(e2), bc = __ballot(e2 || flat);
+    int pos = wv_count_below(b1) + wv_count_below(b2);
+    if (e1) {
+        if (pos < cap) {
+            ol[pos] = lp;
+            os[pos + 1] = ps;
+        }
+        ++pos;
+    }
+    if (e2 && pos < cap) {
+        ol[pos] = y;
+        os[pos + 1] = pe;
+    }
+    bool over = false;
+    if (e2 || flat) {
+        const int64_t ipos = nmap + wv_count_below(bc);
+        const double ihi = e2 ? y : HUGE_VAL;
+        if (ipos < mp.cap) mp.put(ipos, h.rev ? -ihi : la, h.rev ? -la : ihi, h.rev ? -la : la);
+        else over = true;
+    }
+    if (k == 0) os[0] = ps;
+    nmap += __popcll(bc);
+    const int base = __popcll(b1) + __popcll(b2);
+    const bool any_over = __ballot(over) != 0;
+    __syncthreads();
+    if (any_over) return -2;
     return base <= cap ? base : -1;
 }
 
@@ -528,6 +652,7 @@ __device__ int wv_dt(const WView &h, double w, double *ol, double *os, int cap, 
         __syncthreads();
         return 0;
     }
+    if (t < 64) return wv_dt_one(h, w, ol, os, cap, mp, nmap);
     wv_values(h, W.V);
     // prefix minimum of g_k = V_k - w l(k)
     double cv = HUGE_VAL;
@@ -545,8 +670,8 @@ __device__ int wv_dt(const WView &h, double w, double *ol, double *os, int cap, 
             W.PM[k] = v;
             W.PA[k] = i;
         }
-        cv = __shfl(v, 63, 64);
-        ci = __shfl(i, 63, 64);
+        cv = wv_last(v);
+        ci = wv_last(i);
     }
     __syncthreads();
     // pieces k = 0..t: start / end slope of the result
@@ -613,7 +738,7 @@ __device__ int wv_dt(const WView &h, double w, double *ol, double *os, int cap, 
             ol[pos] = y;
             os[pos + 1] = W.PE[k];
         }
-        base += __shfl(inc, 63, 64);
+        base += wv_last(inc);
         const int iinc = wv_scan_int(close ? 1 : 0);
         const int64_t ipos = nmap + ibase + iinc - 1;
         if (close) {
@@ -623,10 +748,90 @@ __device__ int wv_dt(const WView &h, double w, double *ol, double *os, int cap, 
                 over = true;
             }
         }
-        ibase += __shfl(iinc, 63, 64);
+        ibase += wv_last(iinc);
     }
     if (wv_lane() == 0) os[0] = W.PS[0];
     nmap += ibase;
+    const bool any_over = __ballot(over) != 0;
+    __syncthreads();
+    if (any_over) return -2;
+    return base <= cap ? base : -1;
+}
+
+// wv_trunc of a message of 1 .. 63 breakpoints, laid out as wv_dt_one.  Run
+// starts go through T (tsize entries).
+__device__ int wv_trunc_one(const WView &h, double C, double *ol, double *os, int cap, const NcMaps &mp, int64_t &nmap,
+                            const WScratch &W) {
+    const int t = h.t, k = wv_lane();
+    const double lk = k < t ? h.l(k) : 0.0, sk = k <= t ? h.s(k) : 0.0, lp = wv_shr<1>(lk);
+    const double V = wv_scan_add((k >= 1 && k < t) ? sk * (lk - lp) : 0.0) + 0.0, Vp = wv_shr<1>(V);
+    double mv = k < t ? V : HUGE_VAL;
+    int mi = k;
+    wv_scan_min(mv, mi);
+    const double cp = wv_last(mv) + C, xm = h.l(wv_last(mi));
+    // the piece's crossing of cp, and the status of its first and last segment
+    const double va = k == 0 ? V : Vp, xa = k == 0 ? lk : lp;
+    bool cr;
+    if (k == 0) cr = sk < 0.0 && V < cp;
+    else if (k == t) cr = sk > 0.0 && Vp < cp;
+    else cr = (Vp < cp && V > cp) || (Vp > cp && V < cp);
+    cr = cr && k <= t;
+    const double z = cr ? xa + (cp - va) / sk : 0.0;
+    auto segstat = [&](double lo, double hi) -> bool {
+        const double mid = (lo == -HUGE_VAL) ? hi - 1.0 : (hi == HUGE_VAL ? lo + 1.0 : 0.5 * (lo + hi));
+        return va + sk * (mid - xa) >= cp;
+    };
+    const double lo = k == 0 ? -HUGE_VAL : lp, hi = k == t ? HUGE_VAL : lk;
+    const bool s0 = segstat(lo, cr ? z : hi), s1 = cr ? segstat(z, hi) : s0;
+    const double ps = s0 ? 0.0 : sk, pe = s1 ? 0.0 : sk, pl = wv_shr<1>(pe);
+    const unsigned long long m1 = __ballot(s1);
+    const bool in = k <= t, sp1 = k > 0 && ((m1 >> (k - 1)) & 1);
+    const bool e1 = in && k >= 1 && pl != ps, e2 = in && cr && ps != pe;
+    const bool st1 = in && (k >= 1 ? !sp1 && s0 : s0), en1 = in && k >= 1 && sp1 && !s0;
+    const bool st2 = in && cr && !s0 && s1, en2 = in && cr && s0 && !s1;
+    const unsigned long long b1 = __ballot(e1), b2 = __ballot(e2), c1 = __ballot(st1), c2 = __ballot(st2),
+                             d1 = __ballot(en1), d2 = __ballot(en2);
+    int pos = wv_count_below(b1) + wv_count_below(b2);
+    if (e1) {
+        if (pos < cap) {
+            ol[pos] = lp;
+            os[pos + 1] = ps;
+        }
+        ++pos;
+    }
+    if (e2 && pos < cap) {
+        ol[pos] = z;
+        os[pos + 1] = pe;
+    }
+    const double bpos = k >= 1 ? lp : -HUGE_VAL;
+    int sp = wv_count_below(c1) + wv_count_below(c2), ep = wv_count_below(d1) + wv_count_below(d2);
+    if (st1) {
+        if (sp < W.tsize) W.T[sp] = bpos;
+        ++sp;
+    }
+    if (st2 && sp < W.tsize) W.T[sp] = z;
+    __syncthreads();  // every start is in T
+    bool over = false;
+    auto put_end = [&](double e) {
+        const int64_t ipos = nmap + ep;
+        if (ipos < mp.cap && ep < W.tsize) mp.put(ipos, W.T[ep], e, xm);
+        else over = true;
+        ++ep;
+    };
+    if (en1) put_end(bpos);
+    if (en2) put_end(z);
+    const int sb = __popcll(c1) + __popcll(c2);
+    int eb = __popcll(d1) + __popcll(d2);
+    if (sb > eb) {  // a run still open at +inf
+        if (k == 0) {
+            ep = eb;
+            put_end(HUGE_VAL);
+        }
+        ++eb;
+    }
+    if (k == 0) os[0] = ps;
+    nmap += eb;
+    const int base = __popcll(b1) + __popcll(b2);
     const bool any_over = __ballot(over) != 0;
     __syncthreads();
     if (any_over) return -2;
@@ -642,6 +847,7 @@ __device__ int wv_trunc(const WView &h, double C, double *ol, double *os, int ca
         __syncthreads();
         return 0;
     }
+    if (t < 64) return wv_trunc_one(h, C, ol, os, cap, mp, nmap, W);
     wv_values(h, W.V);
     // minimum of V and its first index
     double mv = HUGE_VAL;
@@ -651,8 +857,8 @@ __device__ int wv_trunc(const WView &h, double C, double *ol, double *os, int ca
         double v = (k < t) ? W.V[k] : HUGE_VAL;
         int i = k;
         wv_scan_min(v, i);
-        v = __shfl(v, 63, 64);
-        i = __shfl(i, 63, 64);
+        v = wv_last(v);
+        i = wv_last(i);
         if (v < mv || (v == mv && i < mi)) {
             mv = v;
             mi = i;
@@ -738,7 +944,7 @@ __device__ int wv_trunc(const WView &h, double C, double *ol, double *os, int ca
             ol[pos] = z;
             os[pos + 1] = W.PE[u];
         }
-        base += __shfl(inc, 63, 64);
+        base += wv_last(inc);
         // run starts and ends, in order; a run's interval is written at its
         // end (start positions kept in the T scratch)
         const double bpos = (u >= 1) ? h.l(u - 1) : -HUGE_VAL;
@@ -750,7 +956,7 @@ __device__ int wv_trunc(const WView &h, double C, double *ol, double *os, int ca
             ++sp;
         }
         if (st2 && sp < W.tsize) W.T[sp] = z;
-        sb += __shfl(sinc, 63, 64);
+        sb += wv_last(sinc);
         // ends are written after every start of this chunk is in T
         __syncthreads();
         int ep = eb + einc - ecount;
@@ -765,7 +971,7 @@ __device__ int wv_trunc(const WView &h, double C, double *ol, double *os, int ca
         };
         if (en1) put_end(bpos);
         if (en2) put_end(z);
-        eb += __shfl(einc, 63, 64);
+        eb += wv_last(einc);
         __syncthreads();
     }
     // a run still open at +inf
@@ -786,6 +992,32 @@ __device__ int wv_trunc(const WView &h, double C, double *ol, double *os, int ca
     __syncthreads();
     if (any_over) return -2;
     return base <= cap ? base : -1;
+}
+
+// nc_apply with an interval per lane: one load's latency for 64 intervals.
+__device__ __forceinline__ double wv_apply(const NcMaps &mp, int64_t lo, int64_t hi, double y) {
+    for (int64_t k0 = lo; k0 < hi; k0 += 64) {
+        const int64_t k = k0 + wv_lane();
+        const bool in = k < hi;
+        const double a = in ? mp.p[3 * k] : HUGE_VAL, b = in ? mp.p[3 * k + 1] : -HUGE_VAL;
+        const double c = in ? mp.p[3 * k + 2] : 0.0;
+        const unsigned long long m = __ballot(y >= a && y <= b);
+        if (m) return __shfl(c, __ffsll(m) - 1, 64);
+    }
+    return y;
+}
+
+// The first minimum of the message (l, s) of t breakpoints.
+__device__ __forceinline__ double wv_argmin(const double *l, const double *s, int t) {
+    double v = 0.0, vmin = 0.0, y = t > 0 ? l[0] : 0.0;
+    for (int k = 1; k < t; ++k) {
+        v += s[k] * (l[k] - l[k - 1]);
+        if (v < vmin) {
+            vmin = v;
+            y = l[k];
+        }
+    }
+    return y;
 }
 
 template <typename T, int kCap>
@@ -907,24 +1139,52 @@ __global__ __launch_bounds__(64) void k_nc_wave(NcArgs A, const T *__restrict__ 
         if (lane == 0) atomicOr(A.flag, bad);
         return;
     }
-    if (lane != 0) return;
-    // backward, one lane: the first minimum of the last hat M (in B), then pi
-    double v = 0.0, vmin = 0.0, y = th > 0 ? sB_l[0] : 0.0;
-    for (int k = 1; k < th; ++k) {
-        v += sB_s[k] * (sB_l[k] - sB_l[k - 1]);
-        if (v < vmin) {
-            vmin = v;
-            y = sB_l[k];
-        }
-    }
-    x[n1 - 1] = (T)y;
+    // backward: the first minimum of the last hat M (in B), then pi.  The
+    // intervals of an edge (three consecutive ranges) are loaded one node ahead,
+    // an interval per lane, their offsets two nodes ahead: a lane walking them
+    // waited for memory once per interval, half of the kernel's time.
+    __threadfence_block();
+    double y = wv_argmin(sB_l, sB_s, th);
+    if (lane == 0) x[n1 - 1] = (T)y;
+    struct Edge {
+        int64_t e0, e1, e2, e3;
+    };
+    struct Iv {
+        double a, b, c;
+    };
+    auto offsets = [&](int64_t i, int64_t e3) {
+        const int64_t *eo = A.eoff + 3 * (i > n0 ? i : n0);
+        return Edge{eo[0], eo[1], eo[2], e3};
+    };
+    auto load = [&](const Edge &e) {
+        const int64_t k = e.e0 + lane;
+        const bool in = k < e.e3;
+        return Iv{in ? mp.p[3 * k] : HUGE_VAL, in ? mp.p[3 * k + 1] : -HUGE_VAL, in ? mp.p[3 * k + 2] : 0.0};
+    };
+    if (n1 - 2 < n0) return;
+    Edge cur = offsets(n1 - 2, nmap), nxt = offsets(n1 - 3, cur.e0);
+    Iv v = load(cur);
     for (int64_t i = n1 - 2; i >= n0; --i) {
-        const int64_t *eo = A.eoff + 3 * i;
-        const int64_t e3 = (i + 1 < n1 - 1) ? A.eoff[3 * (i + 1)] : nmap;
-        y = nc_apply(mp, eo[2], e3, y);
-        y = nc_apply(mp, eo[1], eo[2], y);
-        y = nc_apply(mp, eo[0], eo[1], y);
-        x[i] = (T)y;
+        const Edge after = offsets(i - 2, nxt.e0);
+        const Iv vn = load(nxt);
+        if (cur.e3 - cur.e0 <= 64) {
+            const int64_t k = cur.e0 + lane;
+            auto apply = [&](int64_t lo, int64_t hi) {
+                const unsigned long long m = __ballot(k >= lo && k < hi && y >= v.a && y <= v.b);
+                if (m) y = __shfl(v.c, __ffsll(m) - 1, 64);
+            };
+            apply(cur.e2, cur.e3);
+            apply(cur.e1, cur.e2);
+            apply(cur.e0, cur.e1);
+        } else {
+            y = wv_apply(mp, cur.e2, cur.e3, y);
+            y = wv_apply(mp, cur.e1, cur.e2, y);
+            y = wv_apply(mp, cur.e0, cur.e1, y);
+        }
+        if (lane == 0) x[i] = (T)y;
+        cur = nxt;
+        nxt = after;
+        v = vn;
     }
 }
 
@@ -1251,16 +1511,17 @@ __global__ __launch_bounds__(64) void k_nc_tree_wave(NcTreeArgs A, const T *__re
         if (lane == 0) atomicOr(A.flag, bad);
         return;
     }
-    if (lane != 0) return;
+    __threadfence_block();
     for (int64_t i = n1 - 1; i >= n0; --i) {
         const int64_t p = A.parent[i];
         if (p < 0) continue;
         const int64_t *eo = A.eoff + 6 * i;
         double y = (double)x[p];
-        y = nc_apply(mp, eo[4], eo[5], y);
-        y = nc_apply(mp, eo[2], eo[3], y);
-        y = nc_apply(mp, eo[0], eo[1], y);
-        x[i] = (T)y;
+        y = wv_apply(mp, eo[4], eo[5], y);
+        y = wv_apply(mp, eo[2], eo[3], y);
+        y = wv_apply(mp, eo[0], eo[1], y);
+        if (lane == 0) x[i] = (T)y;
+        __threadfence_block();
     }
 }
 
@@ -1556,8 +1817,8 @@ __device__ int wv_side(const WView &h, double alpha, double C, bool mirror, doub
             W.PM[k] = v;
             W.PA[k] = i;
         }
-        cv = __shfl(v, 63, 64);
-        ci = __shfl(i, 63, 64);
+        cv = wv_last(v);
+        ci = wv_last(i);
     }
     __syncthreads();
     // whether g lies above m + C at the start (end) of piece k >= 1
@@ -1628,8 +1889,8 @@ __device__ int wv_side(const WView &h, double alpha, double C, bool mirror, doub
             ol[pos] = y;
             os[pos + 1] = W.PE[k];
         }
-        base += __shfl(inc, 63, 64);
-        start = __shfl(st, 63, 64);
+        base += wv_last(inc);
+        start = wv_last(st);
         const int iinc = wv_scan_int(close ? 1 : 0);
         const int64_t ipos = nmap + ibase + iinc - 1;
         if (close) {
@@ -1642,7 +1903,7 @@ __device__ int wv_side(const WView &h, double alpha, double C, bool mirror, doub
                 over = true;
             }
         }
-        ibase += __shfl(iinc, 63, 64);
+        ibase += wv_last(iinc);
     }
     if (wv_lane() == 0) os[0] = W.PS[0];
     nmap += ibase;
@@ -1779,19 +2040,12 @@ __global__ __launch_bounds__(64) void k_nc_wave_concave(NcgArgs A, const T *__re
         if (lane == 0) atomicOr(A.flag, bad);
         return;
     }
-    if (lane != 0) return;
-    double v = 0.0, vmin = 0.0, y = th > 0 ? sB_l[0] : 0.0;
-    for (int k = 1; k < th; ++k) {
-        v += sB_s[k] * (sB_l[k] - sB_l[k - 1]);
-        if (v < vmin) {
-            vmin = v;
-            y = sB_l[k];
-        }
-    }
-    x[n1 - 1] = (T)y;
+    __threadfence_block();
+    double y = wv_argmin(sB_l, sB_s, th);
+    if (lane == 0) x[n1 - 1] = (T)y;
     for (int64_t i = n1 - 2; i >= n0; --i) {
-        for (int64_t k = A.poff[i + 1] - 1; k >= A.poff[i]; --k) y = nc_apply(mp, A.pmap[2 * k], A.pmap[2 * k + 1], y);
-        x[i] = (T)y;
+        for (int64_t k = A.poff[i + 1] - 1; k >= A.poff[i]; --k) y = wv_apply(mp, A.pmap[2 * k], A.pmap[2 * k + 1], y);
+        if (lane == 0) x[i] = (T)y;
     }
 }
 
@@ -2125,13 +2379,14 @@ __global__ __launch_bounds__(64) void k_nc_tree_wave_concave(NcgTreeArgs G, cons
         if (lane == 0) atomicOr(A.flag, bad);
         return;
     }
-    if (lane != 0) return;
+    __threadfence_block();
     for (int64_t i = n1 - 1; i >= n0; --i) {
         const int64_t p = A.parent[i];
         if (p < 0) continue;
         double y = (double)x[p];
-        for (int64_t k = G.poff[i + 1] - 1; k >= G.poff[i]; --k) y = nc_apply(mp, G.pmap[2 * k], G.pmap[2 * k + 1], y);
-        x[i] = (T)y;
+        for (int64_t k = G.poff[i + 1] - 1; k >= G.poff[i]; --k) y = wv_apply(mp, G.pmap[2 * k], G.pmap[2 * k + 1], y);
+        if (lane == 0) x[i] = (T)y;
+        __threadfence_block();
     }
 }
 
