@@ -1054,16 +1054,18 @@ __global__ __launch_bounds__(64) void k_nc_wave(NcArgs A, const T *__restrict__ 
     constexpr int kPer = kCap / 64;
     double pl[kPer], ps[kPer + 1];
     auto fetch = [&](int64_t i) {
-        const int64_t u0 = A.uoff[i], tu = A.uoff[i + 1] - u0;
+        const int64_t u0 = A.uoff[i], tu64 = A.uoff[i + 1] - u0;
+        // (one value for the wave, so that groups past the unary are branched over)
+        const int tu = __builtin_amdgcn_readfirstlane(tu64 > cap ? cap + 1 : (int)tu64);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int k = lane + 64 * j;
-            pl[j] = (k < tu && tu <= cap) ? (double)ulam[u0 + k] : 0.0;
+            if (64 * j < tu) pl[j] = (k < tu && tu <= cap) ? (double)ulam[u0 + k] : 0.0;
         }
 #pragma unroll
         for (int j = 0; j <= kPer; ++j) {
             const int k = lane + 64 * j;
-            ps[j] = (k <= tu && tu <= cap) ? (double)uslope[u0 + i + k] : 0.0;
+            if (64 * j <= tu) ps[j] = (k <= tu && tu <= cap) ? (double)uslope[u0 + i + k] : 0.0;
         }
     };
     fetch(n0);
@@ -1074,17 +1076,17 @@ __global__ __launch_bounds__(64) void k_nc_wave(NcArgs A, const T *__restrict__ 
             bad = tu64 < 1 ? kNcFlagInvalid : kNcFlagCapacity;
             break;
         }
-        const int tu = (int)tu64;
+        const int tu = __builtin_amdgcn_readfirstlane((int)tu64);
         bool inval = false;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int k = lane + 64 * j;
-            if (k < tu) sU_l[k] = pl[j];
+            if (64 * j < tu && k < tu) sU_l[k] = pl[j];
         }
 #pragma unroll
         for (int j = 0; j <= kPer; ++j) {
             const int k = lane + 64 * j;
-            if (k <= tu) sU_s[k] = ps[j];
+            if (64 * j <= tu && k <= tu) sU_s[k] = ps[j];
         }
         if (i + 1 < n1) fetch(i + 1);
         __syncthreads();
@@ -1401,7 +1403,7 @@ __global__ __launch_bounds__(64) void k_nc_tree_wave(NcTreeArgs A, const T *__re
             bad = tu64 < 1 ? kNcFlagInvalid : kNcFlagCapacity;
             break;
         }
-        const int tu = (int)tu64;
+        const int tu = __builtin_amdgcn_readfirstlane((int)tu64);
         for (int k = lane; k < tu; k += 64) sU_l[k] = (double)ulam[u0 + k];
         for (int k = lane; k <= tu; k += 64) sU_s[k] = (double)uslope[u0 + i + k];
         if (lane == 0) sA_s[0] = 0.0;  // an empty message
@@ -1949,16 +1951,18 @@ __global__ __launch_bounds__(64) void k_nc_wave_concave(NcgArgs A, const T *__re
     constexpr int kPer = kCap / 64;
     double pl[kPer], ps[kPer + 1];
     auto fetch = [&](int64_t i) {
-        const int64_t u0 = A.uoff[i], tu = A.uoff[i + 1] - u0;
+        const int64_t u0 = A.uoff[i], tu64 = A.uoff[i + 1] - u0;
+        // (one value for the wave, so that groups past the unary are branched over)
+        const int tu = __builtin_amdgcn_readfirstlane(tu64 > cap ? cap + 1 : (int)tu64);
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int k = lane + 64 * j;
-            pl[j] = (k < tu && tu <= cap) ? (double)ulam[u0 + k] : 0.0;
+            if (64 * j < tu) pl[j] = (k < tu && tu <= cap) ? (double)ulam[u0 + k] : 0.0;
         }
 #pragma unroll
         for (int j = 0; j <= kPer; ++j) {
             const int k = lane + 64 * j;
-            ps[j] = (k <= tu && tu <= cap) ? (double)uslope[u0 + i + k] : 0.0;
+            if (64 * j <= tu) ps[j] = (k <= tu && tu <= cap) ? (double)uslope[u0 + i + k] : 0.0;
         }
     };
     fetch(n0);
@@ -1969,17 +1973,17 @@ __global__ __launch_bounds__(64) void k_nc_wave_concave(NcgArgs A, const T *__re
             bad = tu64 < 1 ? kNcFlagInvalid : kNcFlagCapacity;
             break;
         }
-        const int tu = (int)tu64;
+        const int tu = __builtin_amdgcn_readfirstlane((int)tu64);
         bool inval = false;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             const int k = lane + 64 * j;
-            if (k < tu) sU_l[k] = pl[j];
+            if (64 * j < tu && k < tu) sU_l[k] = pl[j];
         }
 #pragma unroll
         for (int j = 0; j <= kPer; ++j) {
             const int k = lane + 64 * j;
-            if (k <= tu) sU_s[k] = ps[j];
+            if (64 * j <= tu && k <= tu) sU_s[k] = ps[j];
         }
         if (i + 1 < n1) fetch(i + 1);
         __syncthreads();
@@ -2271,7 +2275,7 @@ __global__ __launch_bounds__(64) void k_nc_tree_wave_concave(NcgTreeArgs G, cons
             bad = tu64 < 1 ? kNcFlagInvalid : kNcFlagCapacity;
             break;
         }
-        const int tu = (int)tu64;
+        const int tu = __builtin_amdgcn_readfirstlane((int)tu64);
         for (int k = lane; k < tu; k += 64) sU_l[k] = (double)ulam[u0 + k];
         for (int k = lane; k <= tu; k += 64) sU_s[k] = (double)uslope[u0 + i + k];
         if (lane == 0) sA_s[0] = 0.0;  // an empty message
