@@ -73,7 +73,7 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind) {
     SegPlan p = plan_for(t, num_chains, n);
     const bool has_group = kind == kPlanChain || kind == kPlan2dCol || kind == kPlan2dRow || kind == kPlanBatchCol ||
                            kind == kPlanBatchRow;
-    p.wg = has_group && by_default && grp_plan_ok(num_chains, n);
+    p.wg = has_group && by_default && grp_plan_ok(num_chains, n, kind != kPlanChain);
     return p;
 }
 

@@ -613,12 +613,12 @@ size_t chain_prox_ws_bytes(const ChainBatch &b, const SegPlan &plan) {
 // 64 MiB).  Segment lengths at or above the chain length are all the same
 // plan, whose halo is never used; only one of them is kept.
 template <typename T, typename G>
-int seg_candidates(int64_t C, int64_t n, SegPlan *out, int max_out) {
+int seg_candidates(int64_t C, int64_t n, SegPlan *out, int max_out, bool iter2d) {
     const SegPlan d = seg_default_plan(C, n);
     const size_t base = seg_ws_bytes<T, G>(C, n, d);
     const size_t cap = (2 * base > base + (size_t(64) << 20)) ? 2 * base : base + (size_t(64) << 20);
     int m = 0;
-    if (std::is_same<T, G>::value && grp_plan_ok(C, n) && m < max_out) {
+    if (std::is_same<T, G>::value && grp_plan_ok(C, n, iter2d) && m < max_out) {
         out[m] = d;
         out[m].K = kRingSlots;
         out[m++].wg = 1;
@@ -669,16 +669,16 @@ size_t seg_ws_bytes_plan(int64_t C, int64_t n, const SegPlan &plan) {
 template size_t seg_ws_bytes_plan<float, float>(int64_t, int64_t, const SegPlan &);
 template size_t seg_ws_bytes_plan<double, double>(int64_t, int64_t, const SegPlan &);
 template size_t seg_ws_bytes_plan<float, double>(int64_t, int64_t, const SegPlan &);
-template int seg_candidates<float, float>(int64_t, int64_t, SegPlan *, int);
-template int seg_candidates<double, double>(int64_t, int64_t, SegPlan *, int);
-template int seg_candidates<float, double>(int64_t, int64_t, SegPlan *, int);
+template int seg_candidates<float, float>(int64_t, int64_t, SegPlan *, int, bool);
+template int seg_candidates<double, double>(int64_t, int64_t, SegPlan *, int, bool);
+template int seg_candidates<float, double>(int64_t, int64_t, SegPlan *, int, bool);
 template size_t seg_bytes_max<float, float>(int64_t, int64_t, int);
 template size_t seg_bytes_max<double, double>(int64_t, int64_t, int);
 template size_t seg_bytes_max<float, double>(int64_t, int64_t, int);
 template size_t seg_ws_bytes_plan<float, TagJ<float>>(int64_t, int64_t, const SegPlan &);
 template size_t seg_ws_bytes_plan<double, TagJ<double>>(int64_t, int64_t, const SegPlan &);
-template int seg_candidates<float, TagJ<float>>(int64_t, int64_t, SegPlan *, int);
-template int seg_candidates<double, TagJ<double>>(int64_t, int64_t, SegPlan *, int);
+template int seg_candidates<float, TagJ<float>>(int64_t, int64_t, SegPlan *, int, bool);
+template int seg_candidates<double, TagJ<double>>(int64_t, int64_t, SegPlan *, int, bool);
 template size_t seg_bytes_max<float, TagJ<float>>(int64_t, int64_t, int);
 template size_t seg_bytes_max<double, TagJ<double>>(int64_t, int64_t, int);
 #endif

@@ -54,9 +54,15 @@ struct SegPlan {
 // 512 x 512 60 against 179, 1024 x 1024 102 against 206, 1500 x 1500 206 against
 // 208, 2048 x 2048 290 against 231), and on chains of a few segments only up to
 // a launch four times smaller (16384 x 128 195 against 89: one lane has no halo
-// there).
-inline bool grp_plan_ok(int64_t num_chains, int64_t n) {
-    return num_chains > 0 && n <= kGrpMaxLen && num_chains * n <= (n < 256 ? kGrpMaxNodes / 4 : kGrpMaxNodes);
+// there).  In the 2D iterations many segments start from a state that is not
+// the true one, which costs the lane kernels more: it wins up to twice the size
+// (ms, 30 iterations: 2048 x 2048 FP32 16.7 against 17.0 at lambda = 0.1 and 75
+// against 133 at 0.25; 7M nodes of a batch 13.7 against 11.8).  More than 1024
+// chains keep their second-attempt deques in LDS, which holds 2n + 4 FP64 entries
+// up to n = 4096.
+inline bool grp_plan_ok(int64_t num_chains, int64_t n, bool iter2d) {
+    const int64_t most = (n < 256 ? kGrpMaxNodes / 4 : kGrpMaxNodes) * (iter2d ? 2 : 1);
+    return num_chains > 0 && n <= (num_chains > 1024 ? 4096 : kGrpMaxLen) && num_chains * n <= most;
 }
 
 // Which launch a plan is for: the best segmentation depends on the problem's
@@ -96,7 +102,7 @@ template <typename T> struct TagJ;
 // query reserves room for the largest of them, so a tuned plan always fits.
 // G is the tag type of the deque entries (T when a_i = 1, FP64 otherwise).
 template <typename T, typename G = T>
-int seg_candidates(int64_t num_chains, int64_t n, SegPlan *out, int max_out);
+int seg_candidates(int64_t num_chains, int64_t n, SegPlan *out, int max_out, bool iter2d = false);
 template <typename T, typename G = T>
 size_t seg_bytes_max(int64_t num_chains, int64_t n, int kind);
 

@@ -215,7 +215,7 @@ template <typename T, typename G = T, class Fn>
 tv_status tune_launch(int64_t C, int64_t n, size_t seg_bytes, Fn launch, hipStream_t st, SegPlan *best_plan,
                              tv_tuning_result *res) {
     SegPlan cand[64];
-    const int m = seg_candidates<T, G>(C, n, cand, 64);
+    const int m = seg_candidates<T, G>(C, n, cand, 64, true);
     int best = -1, tried = 0;
     float best_ms = 0.0f;
     for (int j = 0; j < m; ++j) {

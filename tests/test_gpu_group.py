@@ -86,3 +86,34 @@ def test_short_weights_and_many_chains(tuning):
         b = binding.chain_prox_multi([(y, 1), (z, 0), (y, 0)], [0.0, 0.3, 2.0])
         assert all(torch.equal(u, v) for u, v in zip(a, b))
         binding.reset_tuning()
+
+
+@pytest.mark.parametrize("dtype,shape", [(torch.float32, (2048, 2048)), (torch.float32, (2200, 2150)),
+                                         (torch.float64, (1100, 4096)), (torch.float64, (1027, 4097)),
+                                         (torch.float64, (1024, 4600))])
+def test_2d_solves_of_millions_of_nodes(tuning, dtype, shape):
+    """The 2D iterations take the group kernel up to 4.7M nodes, the deques of more
+    than 1024 chains in LDS (FP64: up to 4096 nodes): the bits of the lane kernels."""
+    f = torch.tensor(synth.shapes_image(*shape, sigma=0.1, seed=5), dtype=dtype, device="cuda")
+    got = []
+    for t in (dict(target_lanes=1 << 17, min_segment=128, halo=128, ring_slots=16),
+              dict(target_lanes=1 << 16, min_segment=128, halo=64, ring_slots=32)):
+        tuning(**t)
+        x, info = binding.Tv2dSolver(*shape, dtype=dtype).solve(f, 0.2, max_iter=3, gap_every=3)
+        got.append((x, info["gap_norm"]))
+    assert torch.equal(got[0][0], got[1][0]) and got[0][1] == got[1][1]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_batched_gap_at_the_edges_of_its_row_blocks(dtype):
+    """The gap's dual pass sums 64 rows a wave, 1024 a step of the block, columns
+    of images of different heights side by side: the single-image gap exactly."""
+    shapes = [(1, 40), (63, 3), (64, 65), (65, 7), (128, 1), (1, 1), (1023, 5), (1024, 70), (1025, 33), (2049, 2)]
+    imgs = [torch.tensor(synth.shapes_image(*s, sigma=0.1, seed=j), dtype=dtype, device="cuda")
+            for j, s in enumerate(shapes)]
+    xs, infos = binding.tv2d_batched(imgs, [0.1] * len(imgs), max_iter=6, gap_every=3)
+    for f, xb, ib in zip(imgs, xs, infos):
+        x1, i1 = binding.tv2d(f, 0.1, max_iter=6, gap_every=3)
+        assert torch.equal(xb, x1)
+        for k in ("gap_norm", "primal", "dual"):
+            assert ib[k] == i1[k], (tuple(f.shape), k)
