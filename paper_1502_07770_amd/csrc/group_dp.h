@@ -195,30 +195,38 @@ struct GrpGeom {
 };
 struct GrpLds {
     void *lam;    // [S * L] pairs (lds_lam)
-    void *l, *k;  // end states [threads] (group g's entries from g * GW)
-    int *size;    // [groups]
+    void *l, *k;  // end states [2 * threads] (group g's entries from 2 g * GW, at most 64)
+    int *size;    // [groups] (-1: no end state yet)
     int *need;    // [groups + 1] the state entering a segment changed
+    int *wide;    // [groups + 1] the segments of a pass that outgrew 16 lanes; their number first
     void *w;      // [2 * waves] the waves' composed clips
 };
+constexpr size_t grp_lds_bytes(size_t threads, size_t elem) { return (4 * elem + 2) * threads + 256; }
 
 template <class Prob>
 struct GroupOk : std::bool_constant<!Prob::kGen && !IsL1<Prob>::value> {};
 
 // Solves chain c with groups of GW lanes; false (for the whole workgroup) if a
-// deque outgrew a group.  kStream: lambda may be kept in the stream (without a
+// deque outgrew a wave, or an end state its 2 GW entries.  A segment whose deque
+// outgrows 16 lanes is run again in the same pass by a whole wave, from its
+// neighbour's end state (the wide segments of a pass, a wave each): deques of 16
+// to 23 breakpoints come up in a few segments of many chains of a 2D iteration
+// from lambda = 1.5 sigma on (us an iteration, FP32, sigma = 0.1; in brackets with
+// the whole chain run again by waves: 512 x 512 at lambda = 0.2 237 (342), 1024 x
+// 1024 at 0.15 457 (742), at 0.25 726 (924)).  kStream: lambda may be kept in the stream (without a
 // store to it in the step loop, the next tile's loads are waited for a tile
 // later; with one, before the loop).
 template <typename T, class Prob, int GW, bool kStream>
 __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
                           const GrpGeom &gm, const GrpLds &sh, int L) {
     using R = Ring<GW>;
+    constexpr int E = GW == 16 ? 32 : 64;  // entries of a saved end state
     const int tid = threadIdx.x, lane = tid & 63, gl = tid & (GW - 1), g = tid / GW;
-    const int n = (int)sp.n, H = gm.H, a = g * L;
-    const bool act = a < n;
+    const int n = (int)sp.n, H = gm.H, nw = blockDim.x >> 6, wave = tid >> 6;
+    const bool act = g * L < n;
     const auto src = Prob::src(pp, sp);
     T *lamL = (T *)sh.lam;
-    T *esl = (T *)sh.l + g * GW, *esk = (T *)sh.k + g * GW;
-    GDeque<T> S;
+    T *const esl = (T *)sh.l, *const esk = (T *)sh.k;
     // the lambda pair of node i: (lo, hi) at lds + 2 i, or in the stream
     auto put = [&](int i, int which, T v) {
         if (!kStream || gm.lds_lam)
@@ -227,13 +235,17 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
             ((T *)(ws.lam + (int64_t)i * ws.C + c))[which] = v;
     };
     // Runs the nodes from `halo` before a to the segment's end in tiles of 16
-    // (nodes before the chain's start are skipped); `fresh`: from an empty deque
-    // at the first node, else continuing S.  at_a() is called before node a.
-    auto run = [&](int halo, bool fresh, bool store, auto at_a) {
+    // (nodes before the chain's start are skipped) with groups of W lanes;
+    // `fresh`: from an empty deque at the first node, else continuing S.  at_a()
+    // is called before node a.
+    auto run = [&](auto width, GDeque<T> &S, int a, int halo, bool fresh, bool store, auto at_a) {
+        constexpr int W = decltype(width)::value;
+        using RW = Ring<W>;
+        const int gw = tid & (W - 1);
         const int from = a - halo, tiles = (halo + L) / 16;
         int i0 = from;
         const int h0 = from > 0 ? from : 0;
-        T wprev = (!fresh && from > 0 && act) ? src.weight(src.load(from - 1 < n ? from - 1 : n - 1)) : (T)0;
+        T wprev = (!fresh && from > 0 && a < n) ? src.weight(src.load(from - 1 < n ? from - 1 : n - 1)) : (T)0;
         auto tile = [&](int i, T &y, T &w) {
             const int j = i + (lane & 15);
             const auto pv = src.load(j < 0 ? 0 : (j < n ? j : n - 1));
@@ -249,7 +261,7 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
             if (16 * q == halo) at_a();
             tile(i0 + 16, yn, wn);
             const uint64_t im = lanes_where(fresh && i0 == h0);
-            const uint64_t st = lanes_where(store && act && i0 >= a);
+            const uint64_t st = lanes_where(store && a < n && i0 >= a);
             const uint64_t live = lanes_where(i0 >= h0);
             T sf = (T)(i0 + 1);
             uint64_t init = im;
@@ -259,16 +271,16 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
                 const T yi = row_bcast<0>(y), wi = row_bcast<0>(w);
                 y = Ring<16>::next(y);
                 w = Ring<16>::next(w);
-                grp_step<T, GW>(S, yi, wprev, wi, sf);
+                grp_step<T, W>(S, yi, wprev, wi, sf);
                 if (init) {  // an empty message: breakpoints y -+ w
                     if (lane_in(init)) {
-                        S.l = gl == 0 ? yi - wi : (gl == 1 ? yi + wi : pos_inf<T>());
-                        S.k = gl == 0 ? sf - (T)1 : sf;
+                        S.l = gw == 0 ? yi - wi : (gw == 1 ? yi + wi : pos_inf<T>());
+                        S.k = gw == 0 ? sf - (T)1 : sf;
                     }
-                    S.front = (S.front & ~init) | (R::kFirst & init);
-                    S.pre = (S.pre & ~init) | (R::kLast & init);
-                    S.back = (S.back & ~init) | ((R::kFirst << 1) & init);
-                    S.valid = (S.valid & ~init) | ((R::kFirst | (R::kFirst << 1)) & init);
+                    S.front = (S.front & ~init) | (RW::kFirst & init);
+                    S.pre = (S.pre & ~init) | (RW::kLast & init);
+                    S.back = (S.back & ~init) | ((RW::kFirst << 1) & init);
+                    S.valid = (S.valid & ~init) | ((RW::kFirst | (RW::kFirst << 1)) & init);
                     S.ovf &= ~init;
                     init = 0;
                 }
@@ -279,76 +291,114 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
             }
         }
     };
-    // breakpoints of S in order: this lane's place, and the deque's size
-    auto order = [&](const GDeque<T> &D, int &j, int &size) {
-        const int h = __ffsll((unsigned long long)R::bits(D.front, lane)) - 1;
-        j = (gl - h) & (GW - 1);
-        size = __popcll(R::bits(D.valid, lane));
-    };
-    auto reset = [&]() {
-        S.l = pos_inf<T>();
-        S.k = (T)0;
-        S.front = R::kFirst;
-        S.pre = R::kLast;
-        S.back = R::kFirst;
-        S.valid = 0;
+    // The deque of m breakpoints at esl / esk[at ..], or an empty one.
+    auto load = [&](auto width, GDeque<T> &S, int m, int at) {
+        constexpr int W = decltype(width)::value;
+        const int gw = tid & (W - 1);
+        S.l = gw < m ? esl[at + gw] : pos_inf<T>();
+        S.k = gw < m ? esk[at + gw] : (T)0;
+        S.front = Ring<W>::kFirst;
+        S.pre = Ring<W>::kLast;
+        S.valid = lanes_where(gw < m);
+        S.back = lanes_where(gw == (m > 0 ? m - 1 : 0));
         S.ovf = 0;
     };
-    T hl = pos_inf<T>(), hk = (T)0;  // the deque after the halo
+    // breakpoints of S in order: this lane's place, and the deque's size
+    auto order = [&](auto width, const GDeque<T> &D, int &j, int &size) {
+        constexpr int W = decltype(width)::value;
+        const int h = __ffsll((unsigned long long)Ring<W>::bits(D.front, lane)) - 1;
+        j = (tid - h) & (W - 1);
+        size = __popcll(Ring<W>::bits(D.valid, lane));
+    };
+    // S as the end state of segment q, whose breakpoint j this lane holds; a
+    // state that differs from the last one is written and told to q's neighbour
+    auto end_state = [&](auto width, const GDeque<T> &S, int q, int j, int size, bool on) {
+        constexpr int W = decltype(width)::value;
+        bool differs = on && size != sh.size[on ? q : 0];
+        if (on && !differs && j < size) differs = !ent_same<T>(esl[q * E + j], esk[q * E + j], S.l, S.k);
+        if (Ring<W>::bits(lanes_where(differs), lane)) {
+            if (j < size) {
+                esl[q * E + j] = S.l;
+                esk[q * E + j] = S.k;
+            }
+            if ((tid & (W - 1)) == 0) {
+                sh.size[q] = size;
+                sh.need[q + 1] = 1;
+            }
+        }
+    };
+    constexpr auto kGroup = std::integral_constant<int, GW>{};
+    constexpr auto kWave = std::integral_constant<int, 64>{};
+    // the state a segment was last run from (first the deque after its halo)
+    T hl = pos_inf<T>(), hk = (T)0;
     int hj = 0, hsize = 0;
     auto group_any = [&](bool p) { return R::bits(lanes_where(p), lane) != 0; };
     // The first pass runs every segment with its halo; later ones run the
     // segments whose incoming deque was not the true one again from it.  A pass
     // makes at least one more segment final, so there are at most as many as
     // segments.
-    bool mine = act;
+    bool mine = act, wide = false;
+    if (gl == 0) sh.size[g] = -1;
 #pragma unroll 1
     for (int pass = 0; pass <= (int)blockDim.x / GW; ++pass) {
-        reset();
-        if (pass > 0 && lanes_where(mine)) {
-            const int m = mine ? sh.size[g - 1] : 0;
-            if (gl < m) {
-                S.l = esl[gl - GW];
-                S.k = esk[gl - GW];
-            }
-            S.valid = lanes_where(gl < m);
-            S.back = lanes_where(gl == m - 1);
-        }
+        GDeque<T> S;
+        const int m = (pass > 0 && mine) ? sh.size[g - 1] : 0;
+        if (GW == 16 && m >= GW) wide = true;
+        const bool here = mine && !wide;
+        load(kGroup, S, here ? m : 0, (g - 1) * E);
+        if (GW == 16 && tid == 0) sh.wide[0] = 0;
         __syncthreads();  // the states have been read
-        bool bad = false, changed = false;
         if (gl == 0) sh.need[g + 1] = 0;
-        if (lanes_where(mine)) {
-            run(pass == 0 ? H : 0, pass == 0, mine, [&]() {
+        bool bad = false;
+        if (lanes_where(here)) {
+            if (pass > 0 && here) {
+                hl = S.l;
+                hk = S.k;
+                hj = gl;
+                hsize = m;
+            }
+            run(kGroup, S, g * L, pass == 0 ? H : 0, pass == 0, here, [&]() {
                 if (pass == 0) {
-                    order(S, hj, hsize);
+                    order(kGroup, S, hj, hsize);
                     hl = S.l;
                     hk = S.k;
                 }
             });
-            bad = mine && R::bits(S.ovf, lane) != 0;
+            bad = here && R::bits(S.ovf, lane) != 0;
             int j, size;
-            order(S, j, size);
-            if (mine) {
-                changed = pass == 0 || size != sh.size[g];
-                if (!changed && j < size) changed = !ent_same<T>(esl[j], esk[j], S.l, S.k);
-            }
-            changed = group_any(changed);
-            if (changed) {
-                if (j < size) {
-                    esl[j] = S.l;
-                    esk[j] = S.k;
-                }
-                if (gl == 0) {
-                    sh.size[g] = size;
-                    sh.need[g + 1] = 1;
-                }
-            }
+            order(kGroup, S, j, size);
+            end_state(kGroup, S, g, j, size, here && !bad);
         }
-        if (__syncthreads_or(bad)) return false;
+        if constexpr (GW == 16) {
+            if (bad) wide = true;
+            if (mine && wide && gl == 0) sh.wide[1 + atomicAdd(sh.wide, 1)] = g;
+            __syncthreads();
+            const int count = sh.wide[0];
+            bad = false;
+            for (int q0 = 0; q0 < count; q0 += nw) {
+                // (a segment whose neighbour has no end state yet waits for it)
+                const int q = __builtin_amdgcn_readfirstlane(q0 + wave < count ? sh.wide[1 + q0 + wave] : -1);
+                const int mq = __builtin_amdgcn_readfirstlane(q > 0 ? sh.size[q - 1] : 0);
+                const bool go = q >= 0 && mq >= 0;
+                load(kWave, S, go ? mq : 0, (q - 1) * E);
+                if (go && lane == 0) sh.need[q] = 0;
+                __syncthreads();
+                if (go) {
+                    run(kWave, S, q * L, 0, q == 0, true, []() {});
+                    int j, size;
+                    order(kWave, S, j, size);
+                    bad = S.ovf != 0 || size > E;
+                    if (!bad) end_state(kWave, S, q, j, size, true);
+                }
+                if (__syncthreads_or(bad)) return false;
+            }
+        } else if (__syncthreads_or(bad)) {
+            return false;
+        }
         bool need = act && g > 0 && sh.need[g] != 0;
-        if (pass == 0 && need) {  // every segment wrote its end state: compare it with the halo's
+        if (need && !wide) {
             need = sh.size[g - 1] != hsize;
-            if (!need && hj < hsize) need = !ent_same<T>(esl[hj - GW], esk[hj - GW], hl, hk);
+            if (!need && hj < hsize) need = !ent_same<T>(esl[(g - 1) * E + hj], esk[(g - 1) * E + hj], hl, hk);
         }
         mine = group_any(need);
         if (!__syncthreads_or(mine)) break;
@@ -357,7 +407,6 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
     // end: a suffix scan of (lo, hi) over the wave, then over the waves
     const auto sink = Prob::sink(pp, sp);
     T *sw = (T *)sh.w;
-    const int nw = blockDim.x >> 6, wave = tid >> 6;
     T xin = (T)0;
     for (int c0 = (n - 1) / (int)blockDim.x * (int)blockDim.x; c0 >= 0; c0 -= (int)blockDim.x) {
         const int i = c0 + tid;
@@ -440,8 +489,9 @@ __device__ void grp_lane_chain(const WsOf<T, Prob> &ws, const typename Prob::Par
 }
 
 // A launch over all chains (kList false), or over the chains in ws.ovf_list.
-// Chains whose deque outgrows a group of 16 run with a wave per segment, and
-// beyond 63 breakpoints on one lane, the deque in LDS (gm.cap) or in HBM.
+// Segments whose deque outgrows a group of 16 are run by a whole wave (grp_chain),
+// chains with more than 31 breakpoints at a segment's end with a wave per segment,
+// and beyond 63 breakpoints on one lane, the deque in LDS (gm.cap) or in HBM.
 template <typename T, class Prob, bool kList>
 __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Prob::Params pp, GrpGeom gm) {
     extern __shared__ __align__(16) char s_grp[];
@@ -451,14 +501,16 @@ __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Pr
     {
         char *p = s_grp;
         sh.l = p;
-        p += sizeof(T) * blockDim.x;
+        p += 2 * sizeof(T) * blockDim.x;
         sh.k = p;
-        p += sizeof(T) * blockDim.x;
+        p += 2 * sizeof(T) * blockDim.x;
         sh.w = p;
         p += 2 * sizeof(T) * (blockDim.x / 64);
         sh.size = (int *)p;
         p += sizeof(int) * S16;
         sh.need = (int *)p;
+        p += sizeof(int) * (S16 + 4);
+        sh.wide = (int *)p;
         p += sizeof(int) * (S16 + 4);
         sh.lam = p;
     }
@@ -478,7 +530,7 @@ __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Pr
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     if (gm.cap)
-                        grp_lane_chain<T, Prob>(ws, pp, sp, c, (T *)sh.lam, gm.cap);
+                        grp_lane_chain<T, Prob>(ws, pp, sp, c, (T *)s_grp, gm.cap);
                     else
                         seg_full_chain<T, Prob>(ws, pp, sp, c, blockIdx.x);
                 }

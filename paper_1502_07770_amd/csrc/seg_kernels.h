@@ -1625,9 +1625,11 @@ template <typename T, class Prob, bool kList>
 hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, hipStream_t stream) {
     GrpGeom gm = grp_geom(ws.C, ws.n);
     const int64_t waves = gm.threads / 64, Lw = (ws.n + waves - 1) / waves + 16;
-    size_t lds = (2 * sizeof(T) + 8) * (size_t)gm.threads + 256;
-    size_t lam = 2 * sizeof(T) * (size_t)(ws.n + (Lw > gm.L ? Lw : gm.L));
-    gm.lds_lam = lds + lam <= 160 * 1024;
+    const size_t most = 160 * 1024, state = grp_lds_bytes(gm.threads, sizeof(T)),
+                 lam = 2 * sizeof(T) * (size_t)(ws.n + (Lw > gm.L ? Lw : gm.L));
+    gm.lds_lam = state + lam <= most;
+    if (!kList && !gm.lds_lam) return hipErrorInvalidValue;  // excluded by kGrpMaxLen
+    size_t lds = gm.lds_lam ? state + lam : state;
     // a block of a list or of a launch of few chains has an HBM deque of its own;
     // the blocks of other launches have room for one in LDS.  512 blocks of a list
     // fill the chip (24 images of 64 to 1024 rows: 13.5 ms, 256 blocks 14.5, 1024
@@ -1636,12 +1638,9 @@ hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
     if (blocks > ws.fb_lanes) {
         gm.cap = (int)(2 * ws.n + 4);
         const size_t dq = 2 * sizeof(T) * (size_t)gm.cap;
-        lam = lam > dq ? lam : dq;
-        gm.lds_lam = 1;
-        if (lds + lam > 160 * 1024) return hipErrorInvalidValue;  // excluded by grp_plan_ok
+        lds = lds > dq ? lds : dq;
+        if (lds > most) return hipErrorInvalidValue;  // excluded by grp_plan_ok
     }
-    if (!kList && !gm.lds_lam) return hipErrorInvalidValue;  // excluded by kGrpMaxLen
-    if (gm.lds_lam) lds += lam;
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute((const void *)k_chain_wg<T, Prob, kList>,
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
