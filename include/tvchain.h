@@ -591,7 +591,8 @@ typedef struct {
 tv_status tv_set_tuning(const tv_tuning *tuning);
 tv_status tv_get_tuning(tv_tuning *tuning);
 
-/* Segment length L the current tuning gives this layout (0 on bad layouts). */
+/* Segment length L the current tuning gives this layout in FP32 (0 on bad
+ * layouts); large FP64 launches take segments twice as long by default. */
 int64_t tv_chain_prox_segment_length(const tv_chain_layout *layout);
 
 /* Static description of a status code. */

@@ -44,6 +44,19 @@ SegPlan seg_default_plan(int64_t num_chains, int64_t n) { return plan_for(seg_tu
 // 0.25 / 0.45, 210 x 8044 0.28 / 0.45.
 static const SegTuning kL1Tuning{int64_t(1) << 16, 64, 64, kRingSlots};
 
+// Half the lanes, and segments twice as long (the halo is half of the work at 128
+// nodes), where the entries of a ring have 16 bytes (FP64, and FP64 tags): five
+// rings of 16 slots and their copies fill a CU's LDS, so 131,072 lanes are eight
+// waves a CU in two uneven turns.  us at 65,536 lanes against 131,072, w = 0.1 /
+// 0.5: FP64 4096 x 4096 384 / 682 against 544 / 1106, 65536 x 256 278 / 311
+// against 442 / 538; FP32 with weighted data, 4096 x 4096 444 against 599.
+// The 2D iterations gain too: more of their segments do not meet, and each costs
+// a repair (20 iterations of 4096 x 4096, lambda 0.1: FP32 17.6 against 18.5 ms,
+// FP64 26 against 31).  FP32 chains stay at 131,072 lanes (4096 x 4096 at w = 0.05
+// 226 against 244) except where one lane per chain is a wave on every SIMD and the
+// halo would be as long as half the chain (65536 x 256 158 against 193).
+static const SegTuning kHalfTuning{int64_t(1) << 16, 128, 128, kRingSlots};
+
 // Plans chosen by the autotuner, per (kind, chains, length).
 namespace {
 struct TunedKey {
@@ -60,7 +73,7 @@ std::map<TunedKey, SegPlan> &tuned_map() {
 }
 }  // namespace
 
-SegPlan seg_plan(int64_t num_chains, int64_t n, int kind) {
+SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem) {
     {
         std::lock_guard<std::mutex> lk(g_tuned_mu);
         auto it = tuned_map().find(TunedKey{kind, num_chains, n});
@@ -70,10 +83,11 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind) {
     const bool by_default = t.target_lanes == d.target_lanes && t.min_segment == d.min_segment && t.halo == d.halo &&
                             t.ring_slots == d.ring_slots;
     if (by_default && (kind == kPlanL1 || kind == kPlan2dRowL1)) return plan_for(kL1Tuning, num_chains, n);
-    SegPlan p = plan_for(t, num_chains, n);
-    const bool has_group = kind == kPlanChain || kind == kPlan2dCol || kind == kPlan2dRow || kind == kPlanBatchCol ||
-                           kind == kPlanBatchRow;
-    p.wg = has_group && by_default && grp_plan_ok(num_chains, n, kind != kPlanChain);
+    const bool iter2d = kind == kPlan2dCol || kind == kPlan2dRow || kind == kPlanBatchCol || kind == kPlanBatchRow;
+    const bool half = iter2d || kind == kPlanDp ||
+                      (kind == kPlanChain && (elem == 8 || (num_chains >= (int64_t(1) << 16) && n <= 256)));
+    SegPlan p = plan_for(by_default && half ? kHalfTuning : t, num_chains, n);
+    p.wg = by_default && (iter2d || kind == kPlanChain) && grp_plan_ok(num_chains, n, iter2d);
     return p;
 }
 
@@ -245,7 +259,7 @@ tv_status tv_chain_prox(const tv_chain_layout *layout, tv_dtype dtype, const voi
     if (!w && !(isfinite(w_scalar) && w_scalar >= 0.0)) return TV_ERR_INVALID_ARG;
     if (overlaps(layout, x, layout, y, dtype) || overlaps(layout, x, layout, w, dtype)) return TV_ERR_INVALID_ARG;
     const ChainBatch b = to_batch(layout);
-    const SegPlan plan = seg_plan(b.num_chains, b.n);
+    const SegPlan plan = seg_plan(b.num_chains, b.n, kPlanChain, dtype == TV_F32 ? 4 : 8);
     const size_t need = dtype == TV_F32 ? chain_prox_ws_bytes<float>(b, plan) : chain_prox_ws_bytes<double>(b, plan);
     if (!workspace || workspace_bytes < need) return TV_ERR_WORKSPACE;
     tv_status st = device_check();
@@ -268,7 +282,7 @@ tv_status tv_chain_prox_noalloc(const tv_chain_layout *layout, tv_dtype dtype, c
     if (!w && !(isfinite(w_scalar) && w_scalar >= 0.0)) return TV_ERR_INVALID_ARG;
     if (overlaps(layout, x, layout, y, dtype) || overlaps(layout, x, layout, w, dtype)) return TV_ERR_INVALID_ARG;
     const ChainBatch b = to_batch(layout);
-    const SegPlan plan = seg_plan(b.num_chains, b.n);
+    const SegPlan plan = seg_plan(b.num_chains, b.n, kPlanChain, dtype == TV_F32 ? 4 : 8);
     const size_t need = dtype == TV_F32 ? chain_prox_ws_bytes<float>(b, plan) : chain_prox_ws_bytes<double>(b, plan);
     if (need > TV_NOALLOC_SCRATCH_BYTES) return TV_ERR_WORKSPACE;
     tv_status st = device_check();
@@ -530,7 +544,7 @@ tv_status tv_chain_prox_multi(int num_batches, const tv_chain_layout *layouts, t
         }
         bs[b] = to_batch(&layouts[b]);
     }
-    const SegPlan plan = seg_plan(C, n);
+    const SegPlan plan = seg_plan(C, n, kPlanChain, dtype == TV_F32 ? 4 : 8);
     ChainBatch all{C, n, 1, n, nullptr};
     const size_t need = dtype == TV_F32 ? chain_prox_ws_bytes<float>(all, plan) : chain_prox_ws_bytes<double>(all, plan);
     if (!workspace || workspace_bytes < need) return TV_ERR_WORKSPACE;

@@ -655,7 +655,7 @@ size_t seg_bytes_max(int64_t C, int64_t n, int kind) {
         mx = b > mx ? b : mx;
     }
     // a plan tuned for this shape earlier (or set by hand) must fit too
-    const size_t t = seg_ws_bytes<T, G>(C, n, seg_plan(C, n, kind));
+    const size_t t = seg_ws_bytes<T, G>(C, n, seg_plan(C, n, kind, sizeof(T)));
     return t > mx ? t : mx;
 }
 

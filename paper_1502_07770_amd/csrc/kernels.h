@@ -91,7 +91,7 @@ SegTuning &seg_tuning();
 // The plan used for a launch of num_chains chains of length <= n: the tuned
 // plan of this kind and shape if one was chosen (tv_*_autotune), else the
 // process-wide tuning.
-SegPlan seg_plan(int64_t num_chains, int64_t n, int kind = kPlanChain);
+SegPlan seg_plan(int64_t num_chains, int64_t n, int kind = kPlanChain, size_t elem = 4);
 SegPlan seg_default_plan(int64_t num_chains, int64_t n);
 void seg_set_tuned(int kind, int64_t num_chains, int64_t n, const SegPlan &p);
 void seg_clear_tuned();
