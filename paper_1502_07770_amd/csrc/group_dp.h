@@ -45,6 +45,42 @@ template <int CTRL> __device__ __forceinline__ double dpp_mov(double v) {
 // Lane t of the lane's row of 16.
 template <int t, typename T> __device__ __forceinline__ T row_bcast(T v) { return dpp_mov<0x150 + t>(v); }
 
+// kGrpRounds rounds of v = fma(a, d, m ? b : v of the lane before), the rotation
+// taken as the select's DPP operand; the compiler makes a move, a select and the
+// FMA of each (1024 x 1024, us a 2D iteration: FP32 143 -> 138, FP64 252 -> 242).
+// A DPP operand has to be two wait states old.
+constexpr int kGrpRounds = 5;  // run between tests that every crossing was reached
+#define TVC_GRP_ROUND32(rot) \
+    "s_nop 1\n\tv_cndmask_b32_dpp %0, %0, %1, vcc " rot " row_mask:0xf bank_mask:0xf\n\tv_fmac_f32 %0, %2, %3\n\t"
+#define TVC_GRP_ROUND64(rot)                                                             \
+    "s_nop 1\n\tv_cndmask_b32_dpp %0, %2, %4, vcc " rot " row_mask:0xf bank_mask:0xf\n\t" \
+    "v_cndmask_b32_dpp %1, %3, %5, vcc " rot " row_mask:0xf bank_mask:0xf"
+#define TVC_GRP_ROUNDS(name, rot)                                                                         \
+    __device__ __forceinline__ void name(float &v, float b, float a, float d, uint64_t m) {               \
+        register uint64_t vcc asm("vcc") = m;                                                             \
+        static_assert(kGrpRounds == 5, "");                                                               \
+        asm(TVC_GRP_ROUND32(rot) TVC_GRP_ROUND32(rot) TVC_GRP_ROUND32(rot) TVC_GRP_ROUND32(rot)           \
+                TVC_GRP_ROUND32(rot) "s_nop 1"                                                            \
+            : "+v"(v)                                                                                     \
+            : "v"(b), "v"(a), "v"(d), "s"(vcc));                                                          \
+    }                                                                                                     \
+    __device__ __forceinline__ void name(double &v, double b, double a, double d, uint64_t m) {           \
+        register uint64_t vcc asm("vcc") = m;                                                             \
+        _Pragma("unroll") for (int r = 0; r < kGrpRounds; ++r) {                                          \
+            int lo, hi;                                                                                   \
+            asm(TVC_GRP_ROUND64(rot)                                                                      \
+                : "=&v"(lo), "=&v"(hi)                                                                    \
+                : "v"(__double2loint(v)), "v"(__double2hiint(v)), "v"(__double2loint(b)),                 \
+                  "v"(__double2hiint(b)), "s"(vcc));                                                      \
+            v = fmav(a, d, __hiloint2double(hi, lo));                                                     \
+        }                                                                                                 \
+    }
+TVC_GRP_ROUNDS(row_rounds, "row_ror:1")
+TVC_GRP_ROUNDS(wave_rounds, "wave_ror:1")
+#undef TVC_GRP_ROUND32
+#undef TVC_GRP_ROUND64
+#undef TVC_GRP_ROUNDS
+
 // The lanes of a group as a ring: neighbours' values, and masks moved one lane
 // towards the front.
 // (A rotation reads lanes that take part in it only: no lane of the wave may be
@@ -54,6 +90,9 @@ template <> struct Ring<16> {
     static constexpr uint64_t kFirst = 0x0001000100010001ull, kLast = 0x8000800080008000ull;
     template <typename T> static __device__ __forceinline__ T prev(T v) { return dpp_mov<0x121>(v); }  // row_ror:1
     template <typename T> static __device__ __forceinline__ T next(T v) { return dpp_mov<0x12F>(v); }  // row_ror:15
+    template <typename T> static __device__ __forceinline__ void rounds(T &v, T b, T a, T d, uint64_t m) {
+        row_rounds(v, b, a, d, m);
+    }
     static __device__ __forceinline__ uint64_t before(uint64_t m) {
         return ((m >> 1) & ~kLast) | ((m & kFirst) << 15);
     }
@@ -63,6 +102,9 @@ template <> struct Ring<64> {
     static constexpr uint64_t kFirst = 1ull, kLast = 1ull << 63;
     template <typename T> static __device__ __forceinline__ T prev(T v) { return dpp_mov<0x13C>(v); }  // wave_ror:1
     template <typename T> static __device__ __forceinline__ T next(T v) { return dpp_mov<0x134>(v); }  // wave_rol:1
+    template <typename T> static __device__ __forceinline__ void rounds(T &v, T b, T a, T d, uint64_t m) {
+        wave_rounds(v, b, a, d, m);
+    }
     static __device__ __forceinline__ uint64_t before(uint64_t m) { return (m >> 1) | (m << 63); }
     static __device__ __forceinline__ uint64_t bits(uint64_t m, int) { return m; }
 };
@@ -79,9 +121,6 @@ template <typename T> struct GDeque {
     uint64_t ovf;  // groups' lanes where a deque did not fit (fewer than GW breakpoints)
 };
 
-// Rounds run between tests that every crossing was reached.
-constexpr int kGrpRounds = 5;
-
 // One step (dp_step_ring with a_i = 1) of every group of the wave.
 template <typename T, int GW>
 __device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf) {
@@ -89,18 +128,12 @@ __device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf)
     const T lo = -w, hi = w;
     const T lamP = R::prev(S.l), lamN = R::next(S.l);
     const T slP = slope_of<T, T>(sf, R::prev(S.k)), sl = slope_of<T, T>(sf, S.k);
-    const T d = S.l - lamP;
     const bool at0 = lane_in(S.front), pre = lane_in(S.pre);
+    const T d = at0 ? (T)0 : S.l - lamP;
     const T v0 = S.l + (-wprev - yi);
     // v at this lane's breakpoint; lanes not reached yet hold +inf, above both levels
     T v = at0 ? v0 : pos_inf<T>();
-    auto rounds = [&]() {
-#pragma unroll
-        for (int r = 0; r < kGrpRounds; ++r) {
-            const T u = fmav(slP, d, R::prev(v));
-            v = at0 ? v0 : u;
-        }
-    };
+    auto rounds = [&]() { R::rounds(v, v0, slP, d, S.front); };
     uint64_t mlo, left, right, keep;
     T vR;  // what lambda^+ is solved from: v at the breakpoint left of it
     bool deep = false;
@@ -213,9 +246,9 @@ struct GroupOk : std::bool_constant<!Prob::kGen && !IsL1<Prob>::value> {};
 // to 23 breakpoints come up in a few segments of many chains of a 2D iteration
 // from lambda = 1.5 sigma on (us an iteration, FP32, sigma = 0.1; in brackets with
 // the whole chain run again by waves: 512 x 512 at lambda = 0.2 237 (342), 1024 x
-// 1024 at 0.15 457 (742), at 0.25 726 (924)).  kStream: lambda may be kept in the stream (without a
-// store to it in the step loop, the next tile's loads are waited for a tile
-// later; with one, before the loop).
+// 1024 at 0.15 457 (742), at 0.25 726 (924)).  kStream: lambda may be kept in the
+// stream (without a store to it in the step loop, the next tile's loads are waited
+// for a tile later; with one, before the loop).
 template <typename T, class Prob, int GW, bool kStream>
 __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
                           const GrpGeom &gm, const GrpLds &sh, int L) {
