@@ -1612,10 +1612,16 @@ size_t seg_ws_layout(void *base, int64_t C, int64_t n, int64_t L, int64_t H, int
 // latency more) while there are more than four waves per SIMD.  us per prox /
 // per 2D iteration, FP32, w = 0.3: 512 x 512 at L = 32 66 / 119, 64 77 / 153,
 // 128 100 / 222; 1024 x 1024 143 / 279, 103 / 261, 116 / 343.  Halos of 48 to
-// 96 are within 5% of it, 32 leaves more segments to run again.
+// 96 are within 5% of it, 32 leaves more segments to run again.  16-node segments
+// where half of the SIMDs would stay idle, on chains short enough that their
+// later passes do not add up (us, L = 32 / 16: 64 x 256 47 / 40, 256 x 256 57 / 51,
+// 2D 203 x 317 FP64 112 / 103; but 128 x 512 59 / 62, 64 x 1000 56 / 75), and up to
+// 128 nodes, where 32-node segments fit one wave, only on a quarter of the chip
+// (2D 128 x 128 60 / 52; 512 x 128 42 / 44).
 inline GrpGeom grp_geom(int64_t C, int64_t n) {
     int L = 32;
     auto threads = [&](int l) { return (int)((n + l - 1) / l * 16 + 63) / 64 * 64; };
+    if (n <= 384 && C * (threads(16) / 64) <= (n <= 128 ? 512 : 1280)) L = 16;
     while (L < 128 && C * (threads(L) / 64) > 4096) L *= 2;
     while (threads(L) > 1024) L += 16;
     return GrpGeom{L, 64, threads(L), 0, 0};

@@ -117,3 +117,20 @@ def test_batched_gap_at_the_edges_of_its_row_blocks(dtype):
         assert torch.equal(xb, x1)
         for k in ("gap_norm", "primal", "dual"):
             assert ib[k] == i1[k], (tuple(f.shape), k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_segment_lengths_and_wide_segments(tuning, dtype):
+    """At the edges of the rule for 16-node segments, and on ramps whose deques
+    outgrow 16 lanes in some segments (run by a wave) or 31 breakpoints at a
+    segment's end (the whole chain by waves): the bits of one lane per chain."""
+    for C, n in [(3, 64), (2, 80), (40, 384), (40, 385), (213, 384), (214, 384), (256, 128), (257, 128), (255, 129)]:
+        y, w = _data("piecewise", C, n, seed=n)
+        ramp = np.sqrt(np.arange(n)[None, :] + 2.0 * np.arange(C)[:, None])
+        ramp[:, ::7] += 0.3 * synth.normal((C, (n + 6) // 7), seed=C)
+        for yy, ww in ((y, w), (ramp, np.full((C, n), 1.5)), (ramp, np.full((C, n), 4.0))):
+            yt, wt = torch.tensor(yy, dtype=dtype, device="cuda"), torch.tensor(ww, dtype=dtype, device="cuda")
+            tuning(target_lanes=1 << 17, min_segment=128, halo=128, ring_slots=16)
+            got = binding.chain_prox(yt, wt, dim=1)
+            tuning(target_lanes=1, min_segment=1, ring_slots=32)
+            assert torch.equal(got, binding.chain_prox(yt, wt, dim=1)), (C, n, ww[0, 0])
