@@ -83,11 +83,19 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem) {
     const bool by_default = t.target_lanes == d.target_lanes && t.min_segment == d.min_segment && t.halo == d.halo &&
                             t.ring_slots == d.ring_slots;
     if (by_default && (kind == kPlanL1 || kind == kPlan2dRowL1)) return plan_for(kL1Tuning, num_chains, n);
-    const bool iter2d = kind == kPlan2dCol || kind == kPlan2dRow || kind == kPlanBatchCol || kind == kPlanBatchRow;
+    const bool batch = kind == kPlanBatchCol || kind == kPlanBatchRow;
+    const bool iter2d = kind == kPlan2dCol || kind == kPlan2dRow || batch, chain = kind == kPlanChain || kind == kPlanDp;
     const bool half = iter2d || kind == kPlanDp ||
                       (kind == kPlanChain && (elem == 8 || (num_chains >= (int64_t(1) << 16) && n <= 256)));
     SegPlan p = plan_for(by_default && half ? kHalfTuning : t, num_chains, n);
-    p.wg = by_default && (iter2d || kind == kPlanChain) && grp_plan_ok(num_chains, n, iter2d);
+    // A group step in FP64 costs twice an FP32 one, a lane step a quarter more: the
+    // group kernel up to 1.6M nodes there (us, prox at w = 0.3, group / lanes: 1000 x
+    // 1500 242 / 350, 1500 x 1500 392 / 312; a 2D iteration at lambda = 0.1: 1250 x
+    // 1250 553 / 630, 1700 x 1700 930 / 713), a batch of images up to twice that (its
+    // num_chains * n counts the longest image's side for all).
+    const int64_t most64 = (int64_t(batch ? 12 : 6) << 18) / (n < 256 ? 4 : 1);
+    p.wg = by_default && (iter2d || chain) && grp_plan_ok(num_chains, n, iter2d) &&
+           (elem == 4 || num_chains * n <= most64);
     return p;
 }
 
@@ -344,7 +352,7 @@ tv_status tv_chain_dp(const tv_chain_layout *layout, tv_dtype dtype, const void 
                       const void *wp, void *x, void *workspace, size_t workspace_bytes, hipStream_t stream) {
     tv_status st = dp_args(layout, dtype, a, b, wm, wp, x);
     if (st != TV_OK || layout->num_chains == 0) return st;
-    const SegPlan plan = seg_plan(layout->num_chains, layout->length, kPlanDp);
+    const SegPlan plan = seg_plan(layout->num_chains, layout->length, kPlanDp, dtype == TV_F32 ? 4 : 8);
     if (!workspace || workspace_bytes < dp_ws_bytes_plan(layout, dtype, plan)) return TV_ERR_WORKSPACE;
     st = device_check();
     if (st != TV_OK) return st;

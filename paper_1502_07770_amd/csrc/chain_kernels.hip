@@ -618,7 +618,7 @@ int seg_candidates(int64_t C, int64_t n, SegPlan *out, int max_out, bool iter2d)
     const size_t base = seg_ws_bytes<T, G>(C, n, d);
     const size_t cap = (2 * base > base + (size_t(64) << 20)) ? 2 * base : base + (size_t(64) << 20);
     int m = 0;
-    if (std::is_same<T, G>::value && grp_plan_ok(C, n, iter2d) && m < max_out) {
+    if (!std::is_same<G, TagJ<T>>::value && grp_plan_ok(C, n, iter2d) && m < max_out) {
         out[m] = d;
         out[m].K = kRingSlots;
         out[m++].wg = 1;

@@ -115,22 +115,24 @@ __device__ __forceinline__ uint64_t lanes_where(bool p) { return __builtin_amdgc
 // A deque per group.  front / back: the lanes of the first and last
 // breakpoint (the last step's lambda^- and lambda^+); pre: the lane before the
 // front; valid: the lanes that hold breakpoints (the others hold +inf).
-template <typename T> struct GDeque {
-    T l, k;
+template <typename T, typename G> struct GDeque {
+    T l;
+    G k;
     uint64_t front, pre, back, valid;
     uint64_t ovf;  // groups' lanes where a deque did not fit (fewer than GW breakpoints)
 };
 
-// One step (dp_step_ring with a_i = 1) of every group of the wave.
-template <typename T, int GW>
-__device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf) {
+// One step (dp_step_ring) of every group of the wave.
+template <typename T, typename G, bool kGen, int GW>
+__device__ __forceinline__ void grp_step(GDeque<T, G> &S, const StepIn<T, G> &in) {
     using R = Ring<GW>;
-    const T lo = -w, hi = w;
+    const EndSlope<T, G, kGen> es(in.sf, in.sprev);
+    const T lo = in.lo, hi = in.hi;
     const T lamP = R::prev(S.l), lamN = R::next(S.l);
-    const T slP = slope_of<T, T>(sf, R::prev(S.k)), sl = slope_of<T, T>(sf, S.k);
+    const T slP = slope_of<T, G>(in.sf, R::prev(S.k)), sl = slope_of<T, G>(in.sf, S.k);
     const bool at0 = lane_in(S.front), pre = lane_in(S.pre);
     const T d = at0 ? (T)0 : S.l - lamP;
-    const T v0 = S.l + (-wprev - yi);
+    const T v0 = es.mul(S.l) + (in.lop - in.yi);
     // v at this lane's breakpoint; lanes not reached yet hold +inf, above both levels
     T v = at0 ? v0 : pos_inf<T>();
     auto rounds = [&]() { R::rounds(v, v0, slP, d, S.front); };
@@ -171,7 +173,7 @@ __device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf)
         }
         left = (mlo | S.pre) & ~lanes_where(R::next(v) < lo);
         const bool atB = lane_in(S.back);
-        const T u0 = S.l + (wprev - yi), dN = S.l - lamN;
+        const T u0 = es.mul(S.l) + (in.hip - in.yi), dN = S.l - lamN;
         T u = atB ? u0 : pos_inf<T>();
         for (int done = 1; !(lanes_where(u <= hi) & S.valid) && done < t; done += 4) {
 #pragma unroll
@@ -193,10 +195,10 @@ __device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf)
     const uint64_t on_left = ((GW == 64) ? ((left << 1) | (left >> 63))
                                          : (((left & ~R::kLast) << 1) | ((left & R::kLast) >> 15)));
     // lambda^- on the segment right of this lane's breakpoint, or on the left
-    // end piece (slope 1) for the lane before the front
+    // end piece (slope a_s) for the lane before the front
     const T vN = R::next(v);
     const T X = pre ? vN : v, base0 = pre ? lamN : S.l;
-    const T rr = pre ? (T)1 : recip(sl);
+    const T rr = pre ? es.ra : recip(sl);
     const T lm = clampv(fmav(lo - X, rr, base0), pre ? -pos_inf<T>() : S.l, lamN);
     // lambda^+ on the segment left of this lane's breakpoint; from lambda^-
     // where both lie on one segment
@@ -206,8 +208,8 @@ __device__ __forceinline__ void grp_step(GDeque<T> &S, T yi, T wprev, T w, T sf)
     const T base = same ? lmP : lamP, span = hi - lo, gap = hi - vR;
     const T lp = clampv(fmav(same ? span : gap, rrP, base), base, S.l);
     const bool isL = lane_in(left), isR = lane_in(right);
-    const T kp = sf - (T)1, kk = pre ? kp : S.k;
-    S.k = isR ? sf : kk;
+    const G kk = pre ? in.sprev : S.k;
+    S.k = isR ? in.sf : kk;
     const T kept = lane_in(keep) ? S.l : pos_inf<T>(), lr = isR ? lp : kept;
     S.l = isL ? lm : lr;
     S.front = left;
@@ -234,10 +236,12 @@ struct GrpLds {
     int *wide;    // [groups + 1] the segments of a pass that outgrew 16 lanes; their number first
     void *w;      // [2 * waves] the waves' composed clips
 };
-constexpr size_t grp_lds_bytes(size_t threads, size_t elem) { return (4 * elem + 2) * threads + 256; }
+constexpr size_t grp_lds_bytes(size_t threads, size_t elem, size_t tag) {
+    return (2 * elem + 2 * tag + 2) * threads + 256;
+}
 
 template <class Prob>
-struct GroupOk : std::bool_constant<!Prob::kGen && !IsL1<Prob>::value> {};
+struct GroupOk : std::bool_constant<!IsL1<Prob>::value> {};
 
 // Solves chain c with groups of GW lanes; false (for the whole workgroup) if a
 // deque outgrew a wave, or an end state its 2 GW entries.  A segment whose deque
@@ -253,13 +257,16 @@ template <typename T, class Prob, int GW, bool kStream>
 __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
                           const GrpGeom &gm, const GrpLds &sh, int L) {
     using R = Ring<GW>;
+    using G = typename Prob::Tag;
+    constexpr bool kGen = Prob::kGen;
     constexpr int E = GW == 16 ? 32 : 64;  // entries of a saved end state
     const int tid = threadIdx.x, lane = tid & 63, gl = tid & (GW - 1), g = tid / GW;
     const int n = (int)sp.n, H = gm.H, nw = blockDim.x >> 6, wave = tid >> 6;
     const bool act = g * L < n;
     const auto src = Prob::src(pp, sp);
     T *lamL = (T *)sh.lam;
-    T *const esl = (T *)sh.l, *const esk = (T *)sh.k;
+    T *const esl = (T *)sh.l;
+    G *const esk = (G *)sh.k;
     // the lambda pair of node i: (lo, hi) at lds + 2 i, or in the stream
     auto put = [&](int i, int which, T v) {
         if (!kStream || gm.lds_lam)
@@ -271,7 +278,7 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
     // (nodes before the chain's start are skipped) with groups of W lanes;
     // `fresh`: from an empty deque at the first node, else continuing S.  at_a()
     // is called before node a.
-    auto run = [&](auto width, GDeque<T> &S, int a, int halo, bool fresh, bool store, auto at_a) {
+    auto run = [&](auto width, GDeque<T, G> &S, int a, int halo, bool fresh, bool store, auto at_a) {
         constexpr int W = decltype(width)::value;
         using RW = Ring<W>;
         const int gw = tid & (W - 1);
@@ -282,37 +289,97 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
         while (16 * q < halo && !lanes_where(a < n && from + 16 * q >= 0)) ++q;
         int i0 = from + 16 * q;
         const int h0 = from > 0 ? from : 0;
-        T wprev = (!fresh && from > 0 && a < n) ? src.weight(src.load(from - 1 < n ? from - 1 : n - 1)) : (T)0;
-        auto tile = [&](int i, T &y, T &w) {
-            const int j = i + (lane & 15);
-            const auto pv = src.load(j < 0 ? 0 : (j < n ? j : n - 1));
-            y = src.data(pv);
-            // the root's zero edge; nodes past the chain's end, run to fill a tile, get
-            // constant data and weight, on which a deque stays short
-            w = j < n - 1 ? src.weight(pv) : (j == n - 1 ? (T)0 : (T)1);
+        StepIn<T, G> in;
+        in.lop = (T)0;
+        in.hip = (T)0;
+        G first = (G)0, last = (G)0;  // general a_i: the sums before the first node and of the chain
+        if (from > 0 && a < n) {
+            if constexpr (kGen) first = src.prefix_before(from);
+            if (!fresh) {
+                const auto pv = src.load(from - 1);
+                if constexpr (kGen) {
+                    in.lop = src.wlo(pv);
+                    in.hip = src.whi(pv);
+                } else {
+                    in.hip = src.weight(pv);
+                }
+            }
+        }
+        if constexpr (kGen) {
+            if (a < n && a + L > n) last = src.prefix_before(n);
+        }
+        in.sprev = first;
+        // A lane's node of a tile: what is loaded, and the step's inputs from it.  The
+        // root has a zero edge; nodes past the chain's end, run to fill a tile, get
+        // constant data and weight, on which a deque stays short.
+        struct Tile {
+            T y, lo, hi;
+            G s;
         };
-        T y, w, yn, wn;
-        tile(i0, y, w);
+        auto load = [&](int i) {
+            const int j = i + (lane & 15);
+            return src.load(j < 0 ? 0 : (j < n ? j : n - 1));
+        };
+        auto inputs = [&](const typename Prob::Pre &pv, int i, Tile &t) {
+            const int j = i + (lane & 15);
+            t.y = src.data(pv);
+            const T end = j == n - 1 ? (T)0 : (T)1;
+            if constexpr (kGen) {
+                t.lo = j < n - 1 ? src.wlo(pv) : -end;
+                t.hi = j < n - 1 ? src.whi(pv) : end;
+                // the anchor's group of 8 summed left to right
+                t.s = src.prefix(pv, j, (G)0);
+#pragma unroll
+                for (int r = 0; r < 7; ++r) t.s = src.prefix(pv, j, Ring<16>::prev(t.s));
+                if (j >= n) t.s = last + (G)(j - n + 1);
+            } else {
+                t.hi = j < n - 1 ? src.weight(pv) : end;
+            }
+        };
+        Tile t, tn;
+        typename Prob::Pre pn = load(i0);
+        if constexpr (!kGen) inputs(pn, i0, t);
         S.ovf = 0;
-        for (; q < tiles; ++q, i0 += 16, y = yn, w = wn) {
+        for (; q < tiles; ++q, i0 += 16) {
             if (16 * q == halo) at_a();
-            tile(i0 + 16, yn, wn);
+            if constexpr (kGen) {  // (its sums wait for the loads: formed a tile later)
+                inputs(pn, i0, t);
+                pn = load(i0 + 16);
+            } else {
+                pn = load(i0 + 16);
+                inputs(pn, i0 + 16, tn);
+            }
             const uint64_t im = lanes_where(fresh && i0 == h0);
             const uint64_t st = lanes_where(store && a < n && i0 >= a);
             const uint64_t live = lanes_where(i0 >= h0);
-            T sf = (T)(i0 + 1);
+            if constexpr (kGen)
+                in.sprev = lane_in(im) ? first : in.sprev;
+            else
+                in.sf = (G)(i0 + 1);
             uint64_t init = im;
-            // lane t of the row holds node i0 + t: the tile turns by one lane a node
+            // lane k of the row holds node i0 + k: the tile turns by one lane a node
 #pragma unroll 1
-            for (int t = 0; t < 16; ++t) {
-                const T yi = row_bcast<0>(y), wi = row_bcast<0>(w);
-                y = Ring<16>::next(y);
-                w = Ring<16>::next(w);
-                grp_step<T, W>(S, yi, wprev, wi, sf);
-                if (init) {  // an empty message: breakpoints y -+ w
+            for (int k = 0; k < 16; ++k) {
+                in.yi = row_bcast<0>(t.y);
+                in.hi = row_bcast<0>(t.hi);
+                t.y = Ring<16>::next(t.y);
+                t.hi = Ring<16>::next(t.hi);
+                if constexpr (kGen) {
+                    in.lo = row_bcast<0>(t.lo);
+                    in.sf = row_bcast<0>(t.s);
+                    t.lo = Ring<16>::next(t.lo);
+                    t.s = Ring<16>::next(t.s);
+                } else {
+                    in.lo = -in.hi;
+                    in.lop = -in.hip;
+                    in.sprev = in.sf - (G)1;
+                }
+                grp_step<T, G, kGen, W>(S, in);
+                if (init) {  // an empty message: breakpoints (b_s + w^-) / a_s and (b_s + w^+) / a_s
                     if (lane_in(init)) {
-                        S.l = gw == 0 ? yi - wi : (gw == 1 ? yi + wi : pos_inf<T>());
-                        S.k = gw == 0 ? sf - (T)1 : sf;
+                        const EndSlope<T, G, kGen> es(in.sf, in.sprev);
+                        S.l = gw == 0 ? es.div(in.yi + in.lo) : (gw == 1 ? es.div(in.yi + in.hi) : pos_inf<T>());
+                        S.k = gw == 0 ? in.sprev : in.sf;
                     }
                     S.front = (S.front & ~init) | (RW::kFirst & init);
                     S.pre = (S.pre & ~init) | (RW::kLast & init);
@@ -322,18 +389,24 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
                     init = 0;
                 }
                 S.ovf &= live;
-                if (lane_in((S.front | S.back) & st)) put(i0 + t, lane_in(S.back) ? 1 : 0, S.l);
-                wprev = wi;
-                sf += (T)1;
+                if (lane_in((S.front | S.back) & st)) put(i0 + k, lane_in(S.back) ? 1 : 0, S.l);
+                in.hip = in.hi;
+                if constexpr (kGen) {
+                    in.lop = in.lo;
+                    in.sprev = in.sf;
+                } else {
+                    in.sf += (G)1;
+                }
             }
+            if constexpr (!kGen) t = tn;
         }
     };
     // The deque of m breakpoints at esl / esk[at ..], or an empty one.
-    auto load = [&](auto width, GDeque<T> &S, int m, int at) {
+    auto load = [&](auto width, GDeque<T, G> &S, int m, int at) {
         constexpr int W = decltype(width)::value;
         const int gw = tid & (W - 1);
         S.l = gw < m ? esl[at + gw] : pos_inf<T>();
-        S.k = gw < m ? esk[at + gw] : (T)0;
+        S.k = gw < m ? esk[at + gw] : (G)0;
         S.front = Ring<W>::kFirst;
         S.pre = Ring<W>::kLast;
         S.valid = lanes_where(gw < m);
@@ -341,7 +414,7 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
         S.ovf = 0;
     };
     // breakpoints of S in order: this lane's place, and the deque's size
-    auto order = [&](auto width, const GDeque<T> &D, int &j, int &size) {
+    auto order = [&](auto width, const GDeque<T, G> &D, int &j, int &size) {
         constexpr int W = decltype(width)::value;
         const int h = __ffsll((unsigned long long)Ring<W>::bits(D.front, lane)) - 1;
         j = (tid - h) & (W - 1);
@@ -349,7 +422,7 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
     };
     // S as the end state of segment q, whose breakpoint j this lane holds; a
     // state that differs from the last one is written and told to q's neighbour
-    auto end_state = [&](auto width, const GDeque<T> &S, int q, int j, int size, bool on) {
+    auto end_state = [&](auto width, const GDeque<T, G> &S, int q, int j, int size, bool on) {
         constexpr int W = decltype(width)::value;
         bool differs = on && size != sh.size[on ? q : 0];
         if (on && !differs && j < size) differs = !ent_same<T>(esl[q * E + j], esk[q * E + j], S.l, S.k);
@@ -367,7 +440,8 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
     constexpr auto kGroup = std::integral_constant<int, GW>{};
     constexpr auto kWave = std::integral_constant<int, 64>{};
     // the state a segment was last run from (first the deque after its halo)
-    T hl = pos_inf<T>(), hk = (T)0;
+    T hl = pos_inf<T>();
+    G hk = (G)0;
     int hj = 0, hsize = 0;
     auto group_any = [&](bool p) { return R::bits(lanes_where(p), lane) != 0; };
     // The first pass runs every segment with its halo; later ones run the
@@ -378,7 +452,7 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
     if (gl == 0) sh.size[g] = -1;
 #pragma unroll 1
     for (int pass = 0; pass <= (int)blockDim.x / GW; ++pass) {
-        GDeque<T> S;
+        GDeque<T, G> S;
         const int m = (pass > 0 && mine) ? sh.size[g - 1] : 0;
         if (GW == 16 && m >= GW) wide = true;
         const bool here = mine && !wide;
@@ -487,16 +561,17 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
 }
 
 // A deque of one lane in LDS: a ring of cap >= 2 n + 4 entries (a step adds at
-// most two; l at [0, cap), k after them), for dq_scan and dq_update.
-template <typename T> struct LdsDeque {
-    T *l, *k;
+// most two; tags first), for dq_scan and dq_update.
+template <typename T, typename G> struct LdsDeque {
+    G *k;
+    T *l;
     int cap, head, size;
     __device__ __forceinline__ int at(int j) const {
         const int i = head + j;
         return i < 0 ? i + cap : (i >= cap ? i - cap : i);
     }
-    __device__ __forceinline__ Ent<T, T> ld(int j) const { return mk_ent<T, T>(l[at(j)], k[at(j)]); }
-    __device__ __forceinline__ void put(int j, const Ent<T, T> &e) const {
+    __device__ __forceinline__ Ent<T, G> ld(int j) const { return mk_ent<T, G>(l[at(j)], k[at(j)]); }
+    __device__ __forceinline__ void put(int j, const Ent<T, G> &e) const {
         l[at(j)] = e.l;
         k[at(j)] = e.k;
     }
@@ -506,20 +581,23 @@ template <typename T> struct LdsDeque {
 // The whole chain on one lane with its deque in LDS, lambda in the stream.
 template <typename T, class Prob>
 __device__ void grp_lane_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
-                               T *mem, int cap) {
+                               void *mem, int cap) {
+    using G = typename Prob::Tag;
+    constexpr bool kGen = Prob::kGen;
     const auto src = Prob::src(pp, sp);
     auto cy = carry_before<T, Prob>(src, 0);
-    LdsDeque<T> D{mem, mem + cap, cap, 0, 0};
-    D.put(0, mk_ent<T, T>(pos_inf<T>(), (T)0));
+    LdsDeque<T, G> D{(G *)mem, (T *)((G *)mem + cap), cap, 0, 0};
+    D.put(0, mk_ent<T, G>(pos_inf<T>(), (G)0));
     for (int64_t i = 0; i < sp.n; ++i) {
         const auto pr = src.load(i);
         const auto in = step_in<T, Prob>(src, pr, i, i == sp.n - 1, cy);
-        const EndSlope<T, T, false> es(in.sf, in.sprev);
-        const DqScan<T> sc = dq_scan<T, T, false, true>(D, D.size, in, es);
+        const EndSlope<T, G, kGen> es(in.sf, in.sprev);
+        const DqScan<T> sc = dq_scan<T, G, kGen, true>(D, D.size, in, es);
         const int i0 = sc.p > 0 ? sc.p - 1 : 0, i1 = sc.r > 0 ? sc.r - 1 : 0;
-        T lm, lp, tnew;
-        dq_solve<T, T, false>(sc, in, es, D.size == 0, D.ld(i0), D.ld(i0 + 1), D.ld(i1), D.ld(i1 + 1), lm, lp, tnew);
-        D.size = dq_update<T, T>(D, sc, in.sf, lm, lp, tnew);
+        T lm, lp;
+        G tnew;
+        dq_solve<T, G, kGen>(sc, in, es, D.size == 0, D.ld(i0), D.ld(i0 + 1), D.ld(i1), D.ld(i1 + 1), lm, lp, tnew);
+        D.size = dq_update<T, G>(D, sc, in.sf, lm, lp, tnew);
         put_lam<T>(ws.lam, i, ws.C, c, lm, i == sp.n - 1 ? lm : lp);
     }
     full_backward<T, Prob>(ws, pp, sp, c);
@@ -537,9 +615,9 @@ __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Pr
     GrpLds sh;
     {
         char *p = s_grp;
-        sh.l = p;
-        p += 2 * sizeof(T) * blockDim.x;
         sh.k = p;
+        p += 2 * sizeof(typename Prob::Tag) * blockDim.x;
+        sh.l = p;
         p += 2 * sizeof(T) * blockDim.x;
         sh.w = p;
         p += 2 * sizeof(T) * (blockDim.x / 64);
@@ -567,7 +645,7 @@ __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Pr
                 __syncthreads();
                 if (threadIdx.x == 0) {
                     if (gm.cap)
-                        grp_lane_chain<T, Prob>(ws, pp, sp, c, (T *)s_grp, gm.cap);
+                        grp_lane_chain<T, Prob>(ws, pp, sp, c, s_grp, gm.cap);
                     else
                         seg_full_chain<T, Prob>(ws, pp, sp, c, blockIdx.x);
                 }

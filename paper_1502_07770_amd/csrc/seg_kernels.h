@@ -1631,7 +1631,7 @@ template <typename T, class Prob, bool kList>
 hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, hipStream_t stream) {
     GrpGeom gm = grp_geom(ws.C, ws.n);
     const int64_t waves = gm.threads / 64, Lw = (ws.n + waves - 1) / waves + 16;
-    const size_t most = 160 * 1024, state = grp_lds_bytes(gm.threads, sizeof(T)),
+    const size_t most = 160 * 1024, state = grp_lds_bytes(gm.threads, sizeof(T), sizeof(typename Prob::Tag)),
                  lam = 2 * sizeof(T) * (size_t)(ws.n + (Lw > gm.L ? Lw : gm.L));
     gm.lds_lam = state + lam <= most;
     if (!kList && !gm.lds_lam) return hipErrorInvalidValue;  // excluded by kGrpMaxLen
@@ -1643,7 +1643,7 @@ hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
     const int64_t blocks = kList && ws.C > 512 ? 512 : ws.C;
     if (blocks > ws.fb_lanes) {
         gm.cap = (int)(2 * ws.n + 4);
-        const size_t dq = 2 * sizeof(T) * (size_t)gm.cap;
+        const size_t dq = (sizeof(T) + sizeof(typename Prob::Tag)) * (size_t)gm.cap;
         lds = lds > dq ? lds : dq;
         if (lds > most) return hipErrorInvalidValue;  // excluded by grp_plan_ok
     }

@@ -542,7 +542,7 @@ static tv_status tv2d_solve_t(const T *f, int64_t H, int64_t W, int64_t ld, doub
                            la.seq);
     }
     const int every = opt->gap_every > 0 ? opt->gap_every : 1;
-    const SegPlan pc = seg_plan(W, H, kPlan2dCol), pr = seg_plan(H, W, kPlan2dRow);
+    const SegPlan pc = seg_plan(W, H, kPlan2dCol, sizeof(T)), pr = seg_plan(H, W, kPlan2dRow, sizeof(T));
     if (seg_ws_bytes_plan<T>(W, H, pc) > ws.seg_bytes || seg_ws_bytes_plan<T>(H, W, pr) > ws.seg_bytes)
         return TV_ERR_WORKSPACE;
     ChunkGraphs graphs;
@@ -595,8 +595,8 @@ static tv_status tv2d_autotune_t(const T *f, int64_t H, int64_t W, int64_t ld, d
     // Run a few iterations first: the deques of the column and row chains
     // deepen as the dual variable builds up, and a plan timed on the first
     // iteration's data alone would pick a ring that overflows later on.
-    if (tv2d_iters<T>(ws, f, ld, H, W, lam, 0, kTuneWarm, false, 0.0, nullptr, seg_plan(W, H, kPlan2dCol),
-                      seg_plan(H, W, kPlan2dRow), st) != hipSuccess)
+    if (tv2d_iters<T>(ws, f, ld, H, W, lam, 0, kTuneWarm, false, 0.0, nullptr, seg_plan(W, H, kPlan2dCol, sizeof(T)),
+                      seg_plan(H, W, kPlan2dRow, sizeof(T)), st) != hipSuccess)
         return TV_ERR_HIP;
     // the timed steps read iteration kTuneWarm's scalars from the first slot
     hipLaunchKernelGGL(k_ctl_sched, dim3(1), dim3(64), 0, st, &ws.hdr->ctl, ws.sched, 1);

@@ -134,3 +134,25 @@ def test_segment_lengths_and_wide_segments(tuning, dtype):
             got = binding.chain_prox(yt, wt, dim=1)
             tuning(target_lanes=1, min_segment=1, ring_slots=32)
             assert torch.equal(got, binding.chain_prox(yt, wt, dim=1)), (C, n, ww[0, 0])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_weighted_data_and_asymmetric_edges_equal_lane_kernels(tuning, dtype):
+    """General quadratic unaries and asymmetric edges by groups of lanes: tile,
+    anchor-group and segment remainders, deques past 16 lanes, both layouts."""
+    shapes = [(3, 1), (2, 2), (5, 7), (5, 8), (4, 9), (4, 17), (3, 33), (40, 385), (2, 511), (9, 520), (1, 2049),
+              (1, 6144), (1, 6145), (1100, 270)]
+    for C, n in shapes:
+        y, w = _data("piecewise", C, n, seed=C + n)
+        a = np.exp(synth.normal((C, n), seed=n))
+        ramp = np.sqrt(np.arange(n)[None, :] + 2.0 * np.arange(C)[:, None])
+        for b, wm, wp, aa in ((a * y, -w, 0.5 * w, a), (ramp, np.full((C, n), -3.0), np.full((C, n), 2.0), None),
+                              (a * y, 0.25 * w, w, a)):
+            t = [None if v is None else torch.tensor(v, dtype=dtype, device="cuda") for v in (aa, b, wm, wp)]
+            tuning(target_lanes=1 << 17, min_segment=128, halo=128, ring_slots=16)
+            got = binding.chain_dp(t[1], t[2], t[3], a=t[0], dim=1)
+            c = [None if v is None else v.t().contiguous() for v in t]
+            cols = binding.chain_dp(c[1], c[2], c[3], a=c[0], dim=0).t()
+            tuning(target_lanes=1, min_segment=1, ring_slots=32)
+            ref = binding.chain_dp(t[1], t[2], t[3], a=t[0], dim=1)
+            assert torch.equal(got, ref) and torch.equal(cols, ref), (C, n)
