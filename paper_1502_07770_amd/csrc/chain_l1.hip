@@ -5,7 +5,8 @@
 //
 // the row subproblem of the TV-l1 primal-dual iteration (eq. (prox-pq), with
 // the quadratic weight normalised to 1).  The message step is l1_step
-// (l1_core.h) on the LDS ring, whose entries hold (lambda, slope tag, jump);
+// (l1_core.h): up to five breakpoints of a set in registers (l1_step_regs), more
+// on the LDS ring, whose entries hold (lambda, slope tag, jump);
 // segments, halos, repair, fix-up, overflow fallbacks and the backward pass are
 // the ones of the chain prox, and segment boundaries compare sets bit for bit,
 // so the output is the sequential run's for every plan.  The set is FP64 for

@@ -26,14 +26,17 @@
 //               tags); where they differ it reruns the segment from that end
 //               state until the deque meets a first-pass checkpoint (or the
 //               segment end) and redoes the backward pass left of it.
-//  k_seg_fix    one lane per chain: redoes, sequentially, the rare segments
-//               whose repair started from a state that was not yet the true one;
-//               then composes the value entering each segment from the root.
-//               Chains whose deque outgrew the ring go to k_seg_ovf.
-//  k_seg_ovf    a pool of lanes solves the overflowed chains with the deque in
-//               HBM.
+//  k_seg_fix    one lane per chain: composes the value entering each segment
+//               from the root.  Chains whose deque outgrew the ring, or with a
+//               segment whose repair started from a state that was not yet the
+//               true one, are handed on (TV-l1: such a segment is redone here,
+//               sequentially).
+//  k_chain_wg   (group_dp.h) solves the handed-on chains, a workgroup each, the
+//               deque spread over lanes; k_seg_ovf for TV-l1, a pool of lanes
+//               with the set in a large ring or in HBM.
 //  k_seg_tail   finishes each segment's un-collapsed right tail from the value at
 //               the segment's right end.
+// Small launches skip all this: k_chain_wg takes every chain (seg_plan's rule).
 // The output is bit-identical to running the DP sequentially per chain.
 //
 // The deque is a ring of packed (lambda, tag) entries in LDS whose first
@@ -1364,9 +1367,10 @@ __device__ bool fix_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
                           EntOf<T, Prob> *s_ent, int lane);
 
 // ---------------------------------------------------------------------------
-// Fix-up, one lane per chain (a no-op for almost every chain).  Walks the
-// segments keeping track of whether the saved end state of the previous
-// segment is the true one; where it is not, the segment is redone
+// Fix-up, one lane per chain (a no-op for almost every chain): chains with an
+// overflow, or a segment repaired from a state that was not the true one, go to
+// the list for k_chain_wg.  TV-l1 walks the segments here (fix_chain): where the
+// previous segment's saved end state is not the true one, the segment is redone
 // sequentially from the true state until a checkpoint matches and past the
 // region the repair kernel rewrote.
 // ---------------------------------------------------------------------------

@@ -3,7 +3,8 @@
 //     x = argmin_x  sum_i ( a_i x_i^2 / 2 - b_i x_i + c_i |x_i - d_i| ) + sum_{i != root} f_i(x_parent(i) - x_i),
 //     f_i(z) = wm_i z (z < 0), wp_i z (z >= 0),
 //
-// (the chain is the tree with parent(i) = i + 1).  One lane per tree.  The
+// (the chain is the tree with parent(i) = i + 1).  Sixteen lanes per tree, a
+// breakpoint each (k_tree_row); trees it leaves, one lane each (k_tree_dp).  The
 // derivative of each message is kept as in Sec. 4.2: its left end (al, bl),
 // right end (ar, br) and the multiset of breakpoints (lambda, da, db) sorted
 // by lambda (right of lambda the linear piece changes by (da, db)).  A node's

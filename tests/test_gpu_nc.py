@@ -207,3 +207,29 @@ def test_chain_ranges_outside_the_nodes_are_rejected():
             binding.chain_nc(_dev(bad, torch.int64), _dev(uoff, torch.int64), _dev(ulam, torch.float64),
                              _dev(usl, torch.float64), _dev(w, torch.float64), _dev(C, torch.float64), msg_cap=cap)
         assert e.value.status == binding.TV_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_wave_messages_around_one_and_two_breakpoints_a_lane(dtype):
+    """A wave handles messages of up to 64 breakpoints one a lane and longer ones in
+    groups of 64: unaries of 60 to 66 and 126 to 130 levels, plain and truncated."""
+    g = np.random.default_rng(64)
+    for trunc in (0.0, 1.0):
+        ts = np.array([t for k in list(range(60, 67)) + list(range(126, 131)) for t in (k, 1, k, 3)])
+        coff = np.arange(0, ts.size + 1, 4).astype(np.int64)
+        uoff = np.concatenate([[0], np.cumsum(ts)]).astype(np.int64)
+        ulam = np.concatenate([np.cumsum(np.concatenate([[g.normal() * 2], g.uniform(0, 0.2, t - 1)])) for t in ts])
+        sl = [g.normal(size=t + 1) * 2 for t in ts]
+        for s in sl:
+            s[0], s[-1] = -abs(s[0]) - 0.05, abs(s[-1]) + 0.05
+        usl, w = np.concatenate(sl), g.uniform(0, 2, ts.size)
+        C = np.where(g.random(ts.size) < trunc, g.uniform(0.1, 3, ts.size), np.inf)
+        if dtype == torch.float32:
+            ulam, usl, w = (a.astype(np.float32).astype(np.float64) for a in (ulam, usl, w))
+            C = C.astype(np.float32).astype(np.float64)
+        x = binding.chain_nc(_dev(coff, torch.int64), _dev(uoff, torch.int64), _dev(ulam, dtype), _dev(usl, dtype),
+                             _dev(w, dtype), _dev(C, dtype), msg_cap=256).double().cpu().numpy()
+        if dtype == torch.float64:
+            _check(coff, uoff, ulam, usl, w, C, x, 1e-9)
+        else:
+            _check(coff, uoff, ulam, usl, w, C, x, 1e-6, 8 * 2.0 ** -23 * (np.abs(ulam).max() + 1) * 4)
