@@ -215,7 +215,7 @@ def test_wave_messages_around_one_and_two_breakpoints_a_lane(dtype):
     groups of 64: unaries of 60 to 66 and 126 to 130 levels, plain and truncated."""
     g = np.random.default_rng(64)
     for trunc in (0.0, 1.0):
-        ts = np.array([t for k in list(range(60, 67)) + list(range(126, 131)) for t in (k, 1, k, 3)])
+        ts = np.array([t for k in list(range(60, 67)) + list(range(126, 131)) for t in (k, 1, 64, 3)])  # <= 198 in all
         coff = np.arange(0, ts.size + 1, 4).astype(np.int64)
         uoff = np.concatenate([[0], np.cumsum(ts)]).astype(np.int64)
         ulam = np.concatenate([np.cumsum(np.concatenate([[g.normal() * 2], g.uniform(0, 0.2, t - 1)])) for t in ts])
