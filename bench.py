@@ -9,7 +9,7 @@ timing starts.  value = Gelem/s = nodes / time.
 
 Also on the same JSON line:
   roofline     -- one tv_chain_prox_multi launch (its kernels: k_seg_main,
-                  k_seg_repair, k_seg_fix, k_seg_ovf, k_seg_tail) timed with HIP events;
+                  k_seg_repair, k_seg_fix, k_chain_wg, k_seg_tail) timed with HIP events;
                   algorithmic bytes 8 B/node (y read, x written) / duration vs the
                   8 TB/s HBM peak; traffic from the committed rocprofv3
                   FETCH_SIZE/WRITE_SIZE summary when it was taken on the current
@@ -1075,7 +1075,7 @@ def main():
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": traffic,
             "kernel": "one tv_chain_prox_multi launch over rows + columns (k_seg_main, k_seg_repair, k_seg_fix, "
-                      "k_seg_ovf, k_seg_tail)",
+                      "k_chain_wg, k_seg_tail)",
             "alg_bytes_per_launch": alg_bytes,
             "measured_copy_gbs": r["copy_gbs"],
             "frac_of_measured_copy": round(achieved / r["copy_gbs"], 4),
