@@ -180,9 +180,8 @@ struct MultiProb {
 // elements per node, so the same wave-per-chain scan runs on columns.  Rows of
 // the tile are padded by 64 / kCpb elements: the staging accesses of a wave
 // (kCpb chains x 64 / kCpb nodes) fall into distinct banks.  (A lane per chain
-// walking its column twice, the kernel this replaces, is a serial chain of
-// memory accesses on few waves: 2655 us for 1,111 columns of 3,001 FP32
-// nodes.)
+// walking its column twice is a serial chain of memory accesses: 2655 us for
+// 1,111 columns of 3,001 FP32 nodes; it is kept for many short chains.)
 // ---------------------------------------------------------------------------
 constexpr int kAdjV = 8;
 
@@ -545,6 +544,73 @@ __global__ __launch_bounds__(64 * (kCpb ? kCpb : kAdjWaves)) void k_chain_adjoin
 }
 
 // ---------------------------------------------------------------------------
+// Many short strided chains (a few samples along the leading axis of a large
+// array): one lane per chain, neighbouring lanes reading neighbouring chains.
+// Two passes: left to right, run sums of g in FP64; at the end of each run its
+// mean goes to grad_y at the run's last node, and the boundary edge that closed
+// the previous run gets s_e (mean_prev - mean) in grad_w; right to left, each
+// run's mean is spread over the run.  A wave per chain has 512 nodes' worth of
+// scans whatever the length, 2.3 ns a chain with the chip full: 1,048,576 x 4
+// FP32 25 us by lanes, 2400 by waves; 65,536 x 64 72 and 178.
+// ---------------------------------------------------------------------------
+template <typename T>
+__global__ __launch_bounds__(64) void k_chain_adjoint_lanes(ChainBatch b, const T *__restrict__ x,
+                                                            const T *__restrict__ g, T *__restrict__ gy,
+                                                            T *__restrict__ gw, int w_per_edge) {
+    const int64_t c = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    if (c >= b.num_chains) return;
+    const ChainSpan a = PlainProb<T, false>::span(
+        typename PlainProb<T, false>::Params{nullptr, nullptr, (T)0, nullptr, b.es, b.cs, nullptr}, c, b.n);
+    const int64_t n = a.n;
+    if (n <= 0) {
+        if (gw && !w_per_edge) gw[c] = (T)0;
+        return;
+    }
+    double run_sum = 0.0, prev_mean = 0.0, wsum = 0.0;
+    int64_t run_len = 0, prev_end = -1;
+    T xprev_end_val = (T)0, xi = x[a.base];
+    for (int64_t i = 0; i < n; ++i) {
+        const T xn = (i + 1 < n) ? x[a.base + (i + 1) * a.es] : xi;
+        run_sum += (double)g[a.base + i * a.es];
+        ++run_len;
+        const bool end = (i + 1 == n) || (xn != xi);
+        if (end) {
+            const double mean = run_sum / (double)run_len;
+            if (gy) gy[a.base + i * a.es] = (T)mean;
+            if (prev_end >= 0) {
+                // boundary edge prev_end: sign of the jump from the previous run
+                const double sgn = (xi > xprev_end_val) ? 1.0 : -1.0;
+                const double d = sgn * (prev_mean - mean);
+                if (gw && w_per_edge) gw[a.base + prev_end * a.es] = (T)d;
+                wsum += d;
+            }
+            prev_mean = mean;
+            prev_end = i;
+            xprev_end_val = xi;
+            run_sum = 0.0;
+            run_len = 0;
+        } else if (gw && w_per_edge) {
+            gw[a.base + i * a.es] = (T)0;
+        }
+        xi = xn;
+    }
+    if (gw) {
+        if (w_per_edge) gw[a.base + (n - 1) * a.es] = (T)0;
+        else gw[c] = (T)wsum;
+    }
+    if (!gy) return;
+    T cur = gy[a.base + (n - 1) * a.es];
+    T xr = x[a.base + (n - 1) * a.es];
+    for (int64_t i = n - 2; i >= 0; --i) {
+        const int64_t o = a.base + i * a.es;
+        const T xv = x[o];
+        if (xv != xr) cur = gy[o];  // node i closes a run: its mean was stored here
+        else gy[o] = cur;
+        xr = xv;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers
 // ---------------------------------------------------------------------------
 template <typename T>
@@ -693,7 +759,18 @@ hipError_t launch_chain_adjoint(const ChainBatch &b, const T *x, const T *g, T *
                            w_per_edge);
         return hipGetLastError();
     }
-    // Strided chains: eight per block read a 32-byte sector per node (FP32; 4096 x 4096:
+    // A lane's walk takes n memory latencies whatever the number of chains, a wave per
+    // chain C / 430 us whatever the length up to a chunk; the line follows both sides
+    // measured (us, lanes / waves, FP32: 3000 x 16 13.8 / 15.1, 6000 x 32 23 / 18, 9000 x 32
+    // 24 / 28, 18000 x 64 55 / 52, 24000 x 64 57 / 68, 36000 x 96 103 / 104, 32768 x 128
+    // 125 / 95, 65536 x 128 145 / 187, 80000 x 200 285 / 255, 131072 x 200 357 / 457,
+    // 131072 x 256 462 / 456; FP64 within a tenth of the same line).
+    if (b.n <= 256 && (double)b.num_chains >= (double)b.n * (170.0 + 1.7 * (double)b.n)) {
+        hipLaunchKernelGGL((k_chain_adjoint_lanes<T>), dim3((unsigned)((b.num_chains + 63) / 64)), dim3(64), 0, stream,
+                           b, x, g, gy, gw, w_per_edge);
+        return hipGetLastError();
+    }
+    // Other strided chains: eight per block read a 32-byte sector per node (FP32; 4096 x 4096:
     // 0.13 ms, 2.1 TB/s); with fewer than 2048 chains that leaves compute units without
     // a block, and four do better (1,111 chains of 3,001: 72 us against 80-100).
     const int cpb = b.num_chains >= 2048 ? 8 : 4;

@@ -247,3 +247,25 @@ def test_strided_chains_equal_unit_stride(n, C, dtype):
             assert torch.equal(yc.t(), yr)
         if wr is not None:
             assert torch.equal(wc.t() if kw["per_edge_w"] else wc, wr)
+
+
+@pytest.mark.parametrize("dtype,eps", [(torch.float32, 2.0 ** -24), (torch.float64, 2.0 ** -53)])
+@pytest.mark.parametrize("n,C", [(1, 172), (1, 171), (4, 707), (4, 708), (16, 70001), (63, 19000), (256, 160000), (257, 4000)])
+def test_short_strided_chains(n, C, dtype, eps):
+    """Many short strided chains take a lane each, fewer or longer ones a wave: both sides of
+    the line give the rows' gradients.  The FP64 run sums are added in another order: n
+    roundings of 2^-53 each on sums of at most n max|g|, then one rounding to the type."""
+    rng = np.random.default_rng(n + C)
+    x = _dev((rng.random((C, n)) < 0.3).cumsum(1) % 3, dtype)
+    g = _dev(rng.normal(size=(C, n)), dtype)
+    top = float(g.abs().max())
+    xc, gc = x.t().contiguous(), g.t().contiguous()
+    for kw in (dict(per_edge_w=True), dict(per_edge_w=False), dict(per_edge_w=True, need_y=False),
+               dict(per_edge_w=True, need_w=False)):
+        yr, wr = binding.chain_prox_backward(x, g, dim=1, **kw)
+        yc, wc = binding.chain_prox_backward(xc, gc, dim=0, **kw)
+        assert (yr is None) == (yc is None) and (wr is None) == (wc is None)
+        for a, b, m in ((yr, yc, top), (wr, wc, 2 * top * (1 if kw["per_edge_w"] else n))):
+            if a is not None:
+                b = b.t() if b.dim() == 2 else b
+                assert float((a - b).abs().max()) <= m * (2 * eps + 4 * n * 2.0 ** -53)
