@@ -152,7 +152,7 @@ typedef struct {
  * times every candidate plan that fits the workspace on this data (one untimed
  * and three timed launches each, HIP events on `stream`) and makes the fastest
  * the plan of every later tv_chain_prox / tv_chain_prox_multi launch with the
- * same total number of chains and (maximum) length, in this process.
+ * same dtype, total number of chains and (maximum) length, in this process.
  * Arguments as tv_chain_prox_multi; x receives the prox.  Synchronous.  Results
  * never depend on the plan (the segmented solve is exact), only speed does.
  * The workspace queries above already reserve room for every candidate. */
@@ -591,8 +591,10 @@ typedef struct {
 tv_status tv_set_tuning(const tv_tuning *tuning);
 tv_status tv_get_tuning(tv_tuning *tuning);
 
-/* Segment length L the current tuning gives this layout in FP32 (0 on bad
- * layouts); large FP64 launches take segments twice as long by default. */
+/* Segment length L of the lane-per-segment kernels that the current tuning gives
+ * this layout in FP32, or in FP64 where only FP64 was autotuned (0 on bad
+ * layouts).  Large FP64 launches take segments twice as long by default, and
+ * small launches solve a chain per workgroup with segments of their own. */
 int64_t tv_chain_prox_segment_length(const tv_chain_layout *layout);
 
 /* Static description of a status code. */

@@ -3,6 +3,7 @@
 
 #include <map>
 #include <mutex>
+#include <tuple>
 
 #include "../../include/tvchain.h"
 #include "kernels.h"
@@ -57,13 +58,16 @@ static const SegTuning kL1Tuning{int64_t(1) << 16, 64, 64, kRingSlots};
 // halo would be as long as half the chain (65536 x 256 158 against 193).
 static const SegTuning kHalfTuning{int64_t(1) << 16, 128, 128, kRingSlots};
 
-// Plans chosen by the autotuner, per (kind, chains, length).
+// Plans chosen by the autotuner, per (kind, chains, length, working precision):
+// the best one differs between the precisions (us, prox of 1500 x 1500 by groups /
+// by lanes: FP32 175 / 227, FP64 392 / 312).
 namespace {
 struct TunedKey {
     int kind;
     int64_t C, n;
+    size_t elem;
     bool operator<(const TunedKey &o) const {
-        return kind != o.kind ? kind < o.kind : (C != o.C ? C < o.C : n < o.n);
+        return std::tie(kind, C, n, elem) < std::tie(o.kind, o.C, o.n, o.elem);
     }
 };
 std::mutex g_tuned_mu;
@@ -76,7 +80,7 @@ std::map<TunedKey, SegPlan> &tuned_map() {
 SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem) {
     {
         std::lock_guard<std::mutex> lk(g_tuned_mu);
-        auto it = tuned_map().find(TunedKey{kind, num_chains, n});
+        auto it = tuned_map().find(TunedKey{kind, num_chains, n, elem});
         if (it != tuned_map().end()) return it->second;
     }
     const SegTuning &t = seg_tuning(), &d = kDefaultTuning;
@@ -99,9 +103,14 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem) {
     return p;
 }
 
-void seg_set_tuned(int kind, int64_t num_chains, int64_t n, const SegPlan &p) {
+void seg_set_tuned(int kind, int64_t num_chains, int64_t n, const SegPlan &p, size_t elem) {
     std::lock_guard<std::mutex> lk(g_tuned_mu);
-    tuned_map()[TunedKey{kind, num_chains, n}] = p;
+    tuned_map()[TunedKey{kind, num_chains, n, elem}] = p;
+}
+
+static bool seg_is_tuned(int kind, int64_t num_chains, int64_t n, size_t elem) {
+    std::lock_guard<std::mutex> lk(g_tuned_mu);
+    return tuned_map().count(TunedKey{kind, num_chains, n, elem}) != 0;
 }
 
 void seg_clear_tuned() {
@@ -386,7 +395,7 @@ tv_status tv_chain_dp_autotune(const tv_chain_layout *layout, tv_dtype dtype, co
         }
     }
     if (best < 0) return TV_ERR_WORKSPACE;
-    seg_set_tuned(kPlanDp, C, n, cand[best]);
+    seg_set_tuned(kPlanDp, C, n, cand[best], dtype == TV_F32 ? 4 : 8);
     if (chosen) {
         chosen->segment_length = cand[best].L;
         chosen->halo = cand[best].H;
@@ -448,7 +457,7 @@ tv_status tv_chain_prox_l1_autotune(const tv_chain_layout *layout, tv_dtype dtyp
     for (int j = 0; j < m; ++j) {
         const size_t need = seg_ws_bytes_plan<double, TagJ<double>>(C, n, cand[j]);
         if (need > workspace_bytes) continue;
-        seg_set_tuned(kPlanL1, C, n, cand[j]);
+        seg_set_tuned(kPlanL1, C, n, cand[j], 8);
         auto run = [&]() {
             return dtype == TV_F32
                        ? launch_chain_l1<float>(b, (const float *)y, (const float *)d, (const float *)w,
@@ -466,7 +475,7 @@ tv_status tv_chain_prox_l1_autotune(const tv_chain_layout *layout, tv_dtype dtyp
         }
     }
     if (best < 0) return TV_ERR_WORKSPACE;
-    seg_set_tuned(kPlanL1, C, n, cand[best]);
+    seg_set_tuned(kPlanL1, C, n, cand[best], 8);
     // x from the chosen plan (every plan gives the same bits)
     st = tv_chain_prox_l1(layout, dtype, y, d, w, w_scalar, c, c_scalar, x, workspace, workspace_bytes, stream);
     if (st != TV_OK) return st;
@@ -611,7 +620,7 @@ tv_status tv_chain_prox_autotune(int num_batches, const tv_chain_layout *layouts
         }
     }
     if (best < 0) return TV_ERR_WORKSPACE;
-    seg_set_tuned(kPlanChain, C, n, cand[best]);
+    seg_set_tuned(kPlanChain, C, n, cand[best], dtype == TV_F32 ? 4 : 8);
     if (chosen) {
         chosen->segment_length = cand[best].L;
         chosen->halo = cand[best].H;
@@ -647,7 +656,9 @@ tv_status tv_get_tuning(tv_tuning *t) {
 
 int64_t tv_chain_prox_segment_length(const tv_chain_layout *layout) {
     if (!layout || layout->num_chains < 1 || layout->length < 1) return 0;
-    return seg_plan(layout->num_chains, layout->length).L;
+    const int64_t C = layout->num_chains, n = layout->length;
+    const bool only64 = !seg_is_tuned(kPlanChain, C, n, 4) && seg_is_tuned(kPlanChain, C, n, 8);
+    return seg_plan(C, n, kPlanChain, only64 ? 8 : 4).L;
 }
 
 size_t tv_chain_prox_backward_workspace(const tv_chain_layout *layout, tv_dtype dtype) {

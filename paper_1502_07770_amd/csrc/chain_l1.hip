@@ -121,7 +121,7 @@ template <typename T>
 hipError_t launch_chain_l1(const ChainBatch &bt, const T *y, const T *d, const T *w, T w_scalar, const T *c,
                            T c_scalar, T *x, void *workspace, hipStream_t stream) {
     if (bt.num_chains <= 0) return hipSuccess;
-    const SegPlan plan = seg_plan(bt.num_chains, bt.n, kPlanL1);
+    const SegPlan plan = seg_plan(bt.num_chains, bt.n, kPlanL1, 8);
     using R = typename L1Run<L1Prob, T>::Prob;
     typename R::Params pp{y, d, w, c, w_scalar, c_scalar, x, bt.es, bt.cs, bt.offsets};
     return seg_run<double, R, kTile>(workspace, bt.num_chains, bt.n, plan, pp, stream);

@@ -89,11 +89,12 @@ struct SegTuning {
 };
 SegTuning &seg_tuning();
 // The plan used for a launch of num_chains chains of length <= n: the tuned
-// plan of this kind and shape if one was chosen (tv_*_autotune), else the
+// plan of this kind, shape and working precision (elem bytes; 8 for TV-l1 sets,
+// which are FP64 on either data) if one was chosen (tv_*_autotune), else the
 // process-wide tuning.
-SegPlan seg_plan(int64_t num_chains, int64_t n, int kind = kPlanChain, size_t elem = 4);
+SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem);
 SegPlan seg_default_plan(int64_t num_chains, int64_t n);
-void seg_set_tuned(int kind, int64_t num_chains, int64_t n, const SegPlan &p);
+void seg_set_tuned(int kind, int64_t num_chains, int64_t n, const SegPlan &p, size_t elem);
 void seg_clear_tuned();
 // Tag of a TV-l1 breakpoint (slope tag and jump; defined in l1_core.h).
 template <typename T> struct TagJ;

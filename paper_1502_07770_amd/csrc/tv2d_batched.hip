@@ -716,8 +716,8 @@ static tv_status batched_autotune_t(const BGeom &g, const int64_t *H, const int6
         g.nrows, g.maxW, ws.seg_bytes,
         [&](const SegPlan &p) { return batched_row_step<T>(g, ws, f, 0, ws.sched, p, st); }, st, &pr, row);
     if (s != TV_OK) return s;
-    seg_set_tuned(kPlanBatchCol, g.ncols, g.maxH, pc);
-    seg_set_tuned(kPlanBatchRow, g.nrows, g.maxW, pr);
+    seg_set_tuned(kPlanBatchCol, g.ncols, g.maxH, pc, sizeof(T));
+    seg_set_tuned(kPlanBatchRow, g.nrows, g.maxW, pr, sizeof(T));
     return hipStreamSynchronize(st) == hipSuccess ? TV_OK : TV_ERR_HIP;
 }
 

@@ -610,8 +610,8 @@ static tv_status tv2d_autotune_t(const T *f, int64_t H, int64_t W, int64_t ld, d
         H, W, ws.seg_bytes,
         [&](const SegPlan &p) { return tv2d_row_step<T>(ws, f, ld, H, W, lam, 0, ws.sched, p, st); }, st, &pr, row);
     if (s != TV_OK) return s;
-    seg_set_tuned(kPlan2dCol, W, H, pc);
-    seg_set_tuned(kPlan2dRow, H, W, pr);
+    seg_set_tuned(kPlan2dCol, W, H, pc, sizeof(T));
+    seg_set_tuned(kPlan2dRow, H, W, pr, sizeof(T));
     return hipStreamSynchronize(st) == hipSuccess ? TV_OK : TV_ERR_HIP;
 }
 
@@ -768,7 +768,7 @@ static tv_status tv2d_l1_solve_t(const T *f, int64_t H, int64_t W, int64_t ld, d
     tv2d_layout<T>(workspace, H, W, &ws, true);
     tv_status s = tv2d_l1_init<T>(f, H, W, ld, opt->tau0, ws, st);
     if (s != TV_OK) return s;
-    const SegPlan pc = seg_plan(W, H, kPlan2dColL1), pr = seg_plan(H, W, kPlan2dRowL1);
+    const SegPlan pc = seg_plan(W, H, kPlan2dColL1, sizeof(T)), pr = seg_plan(H, W, kPlan2dRowL1, 8);
     if (seg_ws_bytes_plan<T>(W, H, pc) > ws.seg_bytes || seg_ws_bytes_plan<double, TagJ<double>>(H, W, pr) > ws.seg_bytes)
         return TV_ERR_WORKSPACE;
     const int every = opt->gap_every > 0 ? opt->gap_every : 1;
@@ -798,7 +798,7 @@ static tv_status tv2d_l1_autotune_t(const T *f, int64_t H, int64_t W, int64_t ld
     tv_status s = tv2d_l1_init<T>(f, H, W, ld, tau0, ws, st);
     if (s != TV_OK) return s;
     // a few iterations first, so the plans are timed on later-iteration data
-    const SegPlan pc0 = seg_plan(W, H, kPlan2dColL1), pr0 = seg_plan(H, W, kPlan2dRowL1);
+    const SegPlan pc0 = seg_plan(W, H, kPlan2dColL1, sizeof(T)), pr0 = seg_plan(H, W, kPlan2dRowL1, 8);
     for (int k = 0; k < kTuneWarm; ++k) {
         if (tv2d_col_step<T>(ws, H, W, lam, k & 1, ws.sched, pc0, st) != hipSuccess) return TV_ERR_HIP;
         if (tv2d_l1_row_step<T>(ws, f, ld, H, W, lam, k & 1, ws.sched, pr0, st) != hipSuccess) return TV_ERR_HIP;
@@ -814,8 +814,8 @@ static tv_status tv2d_l1_autotune_t(const T *f, int64_t H, int64_t W, int64_t ld
         [&](const SegPlan &p) { return tv2d_l1_row_step<T>(ws, f, ld, H, W, lam, 0, ws.sched, p, st); }, st, &pr,
         row);
     if (s != TV_OK) return s;
-    seg_set_tuned(kPlan2dColL1, W, H, pc);
-    seg_set_tuned(kPlan2dRowL1, H, W, pr);
+    seg_set_tuned(kPlan2dColL1, W, H, pc, sizeof(T));
+    seg_set_tuned(kPlan2dRowL1, H, W, pr, 8);
     return hipStreamSynchronize(st) == hipSuccess ? TV_OK : TV_ERR_HIP;
 }
 

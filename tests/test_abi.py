@@ -291,3 +291,34 @@ def test_nc_tree_concave_argument_errors(lib):
                                   None, 8, 8, 8, None, 0, None) == binding.TV_OK
     assert lib.tv_tree_nc_concave(binding.TV_F64, 1, 4, 3, None, None, None, None, None, None, None, None, None,
                                   None, 8, 8, 8, None, 0, None) == binding.TV_ERR_INVALID_ARG
+
+
+class _SegPlan(ctypes.Structure):
+    _fields_ = [("L", ctypes.c_int64), ("H", ctypes.c_int64), ("CK", ctypes.c_int64), ("K", ctypes.c_int),
+                ("wg", ctypes.c_int)]
+
+
+@pytest.fixture
+def plans(lib):
+    """The library's plan rule and its table of tuned plans (C++ functions of the .so):
+    plan(chains, length, kind, element size) and tuned(kind, chains, length, plan, element size)."""
+    plan, tuned = lib._ZN3tvc8seg_planEllim, lib._ZN3tvc13seg_set_tunedEillRKNS_7SegPlanEm
+    plan.restype, plan.argtypes = _SegPlan, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t]
+    tuned.restype = None
+    tuned.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(_SegPlan), ctypes.c_size_t]
+    yield plan, tuned
+    binding.autotune_clear()
+
+
+@pytest.mark.parametrize("kind", range(9))
+def test_tuned_plans_are_per_precision(plans, kind):
+    """A plan tuned in one precision leaves the other one's plan as it was."""
+    plan, tuned = plans
+    get = lambda elem: [getattr(plan(1500, 1500, kind, elem), f) for f, _ in _SegPlan._fields_]
+    for elem, other in ((4, 8), (8, 4)):
+        before = get(other)
+        p = _SegPlan(32, 16, 32, 32, 0)
+        tuned(kind, 1500, 1500, ctypes.byref(p), elem)
+        assert get(elem) == [32, 16, 32, 32, 0]
+        assert get(other) == before
+        binding.autotune_clear()
