@@ -248,8 +248,9 @@ tv_status tv_chain_prox_l1_autotune(const tv_chain_layout *layout, tv_dtype dtyp
  *
  * on a batch of trees (a chain is the tree with parent(i) = i + 1).  The
  * message derivative of each node is the sum of its children's clipped
- * messages plus its unary; breakpoint sets are merged in order.  One tree per
- * lane, computed in FP64 whatever the dtype.
+ * messages plus its unary; breakpoint sets are merged in order.  Sixteen lanes per
+ * tree, one for what is left of a tree whose messages are deep, computed in FP64
+ * whatever the dtype.
  *  offsets : DEVICE int64[num_trees + 1]: tree t is nodes offsets[t] ..
  *            offsets[t+1]-1 of every per-node array.
  *  parent  : DEVICE int64[num_nodes]: global index of each node's parent, -1 at

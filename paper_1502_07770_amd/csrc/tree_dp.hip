@@ -348,15 +348,36 @@ constexpr int kTreeLanes = 64;
 // Nothing walks, where a lane per tree ran its own serial walk through memory
 // and a wave every lane's path: 16,384 trees x 256 nodes took 5.7 ms (22 us a
 // node on 256 waves), 65,536 trees 9.0 ms.  Larger messages, up to kTreeWide, are
-// cut where they lie (tree_cut, tree_wide); a tree with one beyond that, or
-// with an invalid numbering, is left to the lane-per-tree kernel.
+// cut where they lie (tree_cut, tree_wide) a few times per tree.  A tree with more
+// of them, or with one beyond that, goes on in the lane-per-tree kernel from the node
+// that it has reached: there a step on a deep sorted message reads the few
+// breakpoints that it drops (16,384 paths of 256 nodes with smooth data, w = 30:
+// 1.1 ms by lanes, 19 ms with every message cut here).  One with an invalid
+// numbering is done again there from the start.
 // ---------------------------------------------------------------------------
 constexpr int kTreeRow = 16;
 constexpr int kTreeMost = kTreeRow - 2;  // a lane past the last breakpoint and one before the first
 // A message of this many breakpoints takes about as long in tree_cut (twice,
 // a dozen passes of t / 16 loads) as in the lane kernel's merge and scans.
 constexpr int kTreeWide = 128;
-constexpr int64_t kTreeDone = -1, kTreeRedo = -2;  // THdr.start of a tree's first header slot
+// How many of them a tree may have: each counts by what it costs a lane less than here.
+// With one child's message and no l1 term a lane reads only what it drops: the first one
+// ends the row's work.  With one child and an l1 term a lane shifts half of a sorted run:
+// ten of them do.  Several children's messages a lane merges, which takes as long as here
+// without l1 terms (six) and longer with them (they count the other way).  us, lanes alone /
+// every wide message cut here / this rule: 16,384 x 256 smooth paths, w = 3 1170 / 8300 /
+// 1210, with l1 terms, w = 30 4110 / 6810 / 4450; caterpillars, w = 30 3050 / 3710 / 3130,
+// with l1 terms 5090 / 4190 / 4360; random trees with l1 terms, w = 30 14800 / 4630 / 8670.
+// What a row spends before it hands over stays: paths of 60 smooth nodes, w = 30, 247 us by
+// lanes, 360 by this rule.
+constexpr int kTreeWideMost = 60, kTreeWidePath = 61, kTreeWidePathL1 = 6, kTreeWideMerge = 10,
+              kTreeWideMergeL1 = 20;
+// The lane kernel's orders, in the lambda pair of a tree's last node: the node to go on
+// from and the pending messages there, or kTreeDone.
+constexpr int64_t kTreeDone = -1;
+__device__ __forceinline__ void tree_order(const TreeWs &W, int64_t last, int64_t node, int64_t pending) {
+    W.lam[last] = TLam{__longlong_as_double(node), __longlong_as_double(pending)};
+}
 
 // Each lane of a row another lane's value (DPP control; lanes without a source read 0).
 template <int CTRL> __device__ __forceinline__ double row_mov(double v) {
@@ -485,6 +506,30 @@ __device__ int tree_wide(const TreeWs &W, int64_t s, int t, double A, double B, 
     return m + (one ? 1 : 2);
 }
 
+// The pending stack as it was before messages of t breakpoints in all were taken from it.
+__device__ __forceinline__ void tree_untake(const TreeWs &W, int64_t n0, int64_t t, int64_t *top, int64_t *sp) {
+    for (const int64_t end = *top + t; *top < end; ++*sp) *top += W.hdr[n0 + *sp].count;
+}
+
+// Sorts the t breakpoints at s by rank (ties in memory order), by way of the free
+// entries at tmp.
+__device__ void tree_sort(const TreeWs &W, int64_t s, int t, int64_t tmp, int lane) {
+    const int j = lane & 15;
+    for (int k = j; k < t; k += kTreeRow) {
+        const TBp e = tb_get(W, s + k);
+        int r = 0;
+#pragma unroll 8
+        for (int m = 0; m < t; ++m) {
+            const double l = W.ent[s + m].l;
+            r += (l < e.l || (l == e.l && m < k)) ? 1 : 0;
+        }
+        tb_put(W, tmp + r, e);
+    }
+    __threadfence_block();
+    for (int k = j; k < t; k += kTreeRow) tb_put(W, s + k, tb_get(W, tmp + k));
+    __threadfence_block();
+}
+
 template <typename T>
 __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, const T *__restrict__ a,
                                                  const T *__restrict__ b, const T *__restrict__ c,
@@ -500,7 +545,8 @@ __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, cons
     int64_t top = 6 * n0 + 16 * tr, sp = 0;  // end of the pending runs in this tree's arena; pending messages
     const int64_t aend = top + 6 * (n1 - n0) + 16;
     THdr h0{0, 0, 0, -1, 0.0, 0.0}, h1 = h0;  // the last two of them
-    bool ok = true;
+    int64_t t64 = 0;  // breakpoints of a node's children
+    int wide = 0;  // what the messages cut where they lie have cost so far
     auto load_in = [&](int64_t i) {
         TIn q;
         q.a = a ? (double)a[i] : 1.0;
@@ -513,16 +559,19 @@ __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, cons
         return q;
     };
     TIn nx = load_in(n0);
-    for (int64_t i = n0; i < n1; ++i) {
+    int64_t i = n0;  // stops at the node to go on from in the lane kernel
+    for (; i < n1; ++i) {
         const TIn in = nx;
         if (i + 1 < n1) nx = load_in(i + 1);
         // (a) the children's runs, side by side: the top headers whose node is i
         // (their regions are contiguous and end at the old top)
         double bl = -in.b - in.c;
-        int64_t src = -1, t64 = 0;
+        int64_t src = -1;
+        t64 = 0;
         while (sp > 0 && h0.parent == i) {
-            if (j >= t64 && j < t64 + h0.count) src = h0.start + (j - t64);
-            t64 += h0.count;
+            const int64_t hc = top - h0.start;  // its count
+            if (j >= t64 && j < t64 + hc) src = h0.start + (j - t64);
+            t64 += hc;
             bl += h0.lo;
             top = h0.start;
             --sp;
@@ -531,22 +580,20 @@ __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, cons
         }
         const bool data = in.c > 0.0, root = in.p < 0;
         const double lo = root ? 0.0 : in.lo, hi = in.hi;
-        if ((!root && (in.p <= i || in.p >= n1)) || t64 > (root ? (int64_t)1 << 30 : kTreeWide)) {
-            ok = false;
-            break;
-        }
+        if ((!root && (in.p <= i || in.p >= n1)) || t64 > (root ? (int64_t)1 << 30 : kTreeWide)) break;
         int t = (int)t64, count;
-        if (t + (data ? 1 : 0) > kTreeMost) {
+        const bool big = t + (data ? 1 : 0) > kTreeMost;
+        if (big) {
             const double jump = data ? 2.0 * in.c : 0.0;
             TLam z;
             if (root) {  // the zero of h
                 z.lo = z.hi = tree_cut(W, top, t, in.a, bl, in.d, jump, lane).z;
                 count = 0;
             } else {
-                if (top + t + 3 > aend) {
-                    ok = false;
-                    break;
-                }
+                const bool one_run = W.hdr[n0 + sp].count == t64;
+                wide += one_run ? (data ? kTreeWidePathL1 : kTreeWidePath) : (data ? -kTreeWideMergeL1 : kTreeWideMerge);
+                wide = wide > 0 ? wide : 0;
+                if (wide > kTreeWideMost || top + t + 3 > aend) break;
                 count = tree_wide(W, top, t, in.a, bl, in.d, jump, lo, hi, lane, &z);
             }
             if (j == 0) W.lam[i] = z;
@@ -596,10 +643,7 @@ __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, cons
                 e.b = hi - Bp;
             }
             count = root ? 0 : (one ? 1 : ((r - F) & 15) + 1);
-            if (top + count > aend) {
-                ok = false;
-                break;
-            }
+            if (top + count > aend) break;
             const int m = (j - F) & 15;
             if (m < count) tb_put(W, top + m, e);
             if (j == F) W.lam[i].lo = lm;
@@ -608,15 +652,27 @@ __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, cons
         // push the clipped message for the parent
         if (!root) {
             h1 = h0;
-            h0 = THdr{top, count, 0, in.p, lo, hi};
+            h0 = THdr{top, count, big ? -1 : top, in.p, lo, hi};  // (region -1: not sorted)
             if (j == 0) W.hdr[n0 + sp] = h0;
             ++sp;
             top += count;
         }
         __threadfence_block();
     }
-    if (!ok || sp != 0) {
-        if (j == 0) W.hdr[n0].start = kTreeRedo;
+    if (i < n1 || sp != 0) {
+        if (i < n1) tree_untake(W, n0, t64, &top, &sp);
+        // the pending messages as the lane kernel keeps them: sorted, each its own region;
+        // where that cannot be (no room to sort, an invalid numbering) it starts again
+        bool again = i == n1;
+        for (int64_t q = 0; q < sp && !again; ++q) {
+            const THdr hd = W.hdr[n0 + q];
+            if (hd.reg >= 0) continue;
+            again = top + hd.count > aend;
+            if (again) break;
+            tree_sort(W, hd.start, (int)hd.count, top, lane);
+            if (j == 0) W.hdr[n0 + q].reg = hd.start;
+        }
+        if (j == 0) tree_order(W, n1 - 1, again ? n0 : i, again ? 0 : sp);
         return;
     }
     // backward pass, sixteen nodes at a time from the last: parents have higher
@@ -645,10 +701,10 @@ __global__ __launch_bounds__(64, 4) void k_tree_row(TreeBatch tb, TreeWs W, cons
         if (in) x[i] = (T)v;
         __threadfence_block();
     }
-    if (j == 0) W.hdr[n0].start = kTreeDone;
+    if (j == 0) tree_order(W, n1 - 1, kTreeDone, 0);
 }
 
-// A lane per tree, for the trees that k_tree_row left (see its W.hdr marks).
+// A lane per tree, for the trees that k_tree_row left, from the node it left them at.
 template <typename T>
 __global__ __launch_bounds__(64) void k_tree_dp(TreeBatch tb, TreeWs W, const T *__restrict__ a,
                                                 const T *__restrict__ b, const T *__restrict__ c,
@@ -658,11 +714,15 @@ __global__ __launch_bounds__(64) void k_tree_dp(TreeBatch tb, TreeWs W, const T 
     const int64_t tr = (int64_t)blockIdx.x * lanes + threadIdx.x;
     if (tr >= tb.num_trees) return;
     const int64_t n0 = tb.offsets[tr], n1 = tb.offsets[tr + 1];
-    if (n1 <= n0 || W.hdr[n0].start != kTreeRedo) return;
+    if (n1 <= n0) return;
+    const TLam order = W.lam[n1 - 1];
+    const int64_t from = __double_as_longlong(order.lo);
+    if (from == kTreeDone) return;
     const int64_t abase = 6 * n0 + 16 * tr;     // this tree's arena
     const int64_t aend = abase + 6 * (n1 - n0) + 16;
     int64_t top = abase;                          // end of the pending stack's regions
-    int64_t sp = n0;                              // header stack pointer
+    int64_t sp = n0 + __double_as_longlong(order.hi);  // header stack pointer
+    if (sp > n0) top = W.hdr[sp - 1].start + W.hdr[sp - 1].count;
     bool ok = true;
     // a node's inputs are loaded while the node before it is processed
     auto load_in = [&](int64_t i) {
@@ -676,8 +736,9 @@ __global__ __launch_bounds__(64) void k_tree_dp(TreeBatch tb, TreeWs W, const T 
         q.p = tb.parent[i];
         return q;
     };
-    TIn nx = load_in(n0);
+    TIn nx = load_in(from);
     for (int64_t i = n0; i < n1 && ok; ++i) {
+        if (i < from) continue;  // (the lanes' nodes stay abreast)
         const TIn in = nx;
         if (i + 1 < n1) nx = load_in(i + 1);
         // (a) the children's messages: the top headers whose node is i, their

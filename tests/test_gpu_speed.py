@@ -32,3 +32,18 @@ def test_adjoint_of_many_short_strided_chains():
     four = torch.randn(16, 1 << 20, device="cuda")
     copy = _us(lambda: four.clone())
     assert _us(lambda: binding.chain_prox_backward(x, g, dim=0, per_edge_w=True)) < 20 * copy + 200
+
+
+def test_trees_with_deep_messages():
+    """4096 paths of 256 nodes with smooth data and a large weight, whose messages hold dozens of
+    breakpoints: 0.95 ms by a lane per tree, 7.1 ms with every message cut by a row of lanes;
+    the same trees with shallow messages take 0.6."""
+    T, n = 4096, 256
+    par = torch.arange(1, T * n + 1, device="cuda").reshape(T, n)
+    par[:, -1] = -1
+    par = par.reshape(-1)
+    off = torch.arange(T + 1, device="cuda") * n
+    b = torch.sqrt(torch.arange(n, device="cuda")[None, :] + torch.arange(T, device="cuda")[:, None].float()).reshape(-1)
+    noise = torch.randn(T * n, device="cuda")
+    shallow = _us(lambda: binding.tree_dp(par, off, noise, torch.full_like(b, -0.5), torch.full_like(b, 0.5)))
+    assert _us(lambda: binding.tree_dp(par, off, b, torch.full_like(b, -30.0), torch.full_like(b, 30.0))) < 5 * shallow

@@ -141,3 +141,59 @@ def test_message_sizes_match_oracle(dtype, tol, kind):
     x = binding.tree_dp(torch.tensor(par, device="cuda"), torch.tensor(off, device="cuda"), dev[1], dev[4], dev[5],
                         a=dev[0], c=dev[2] if kind != "no l1" else None, d=dev[3] if kind != "no l1" else None)
     _check(par, off, [v.double().cpu().numpy() for v in dev], x.double().cpu().numpy(), range(off.size - 1), tol)
+
+
+def _deep_trees():
+    """Trees that change to the lane kernel on the way, at different nodes: paths of smooth
+    data, the same below inner nodes with leaves, and several of them under one node, with
+    subtrees pending on both sides of the change."""
+    trees = []
+    for n in (20, 61, 150, 400):
+        path = [j + 1 for j in range(n - 1)] + [-1]
+        cater = [min(j + 1 + (j % 2), n - 1) for j in range(n - 1)] + [-1]
+        q = n // 4
+        joined = [n - 1 if j % q == q - 1 else min(j + 1, n - 1) for j in range(n - 1)] + [-1]
+        late = [n - 1] * 3 + [j + 1 for j in range(3, n - 1)] + [-1]  # leaves pending below a path
+        trees += [path, cater, joined, late, cater, path]
+    par, off = [], [0]
+    for t in trees:
+        par += [p + off[-1] if p >= 0 else -1 for p in t]
+        off.append(off[-1] + len(t))
+    return np.array(par, dtype=np.int64), np.array(off, dtype=np.int64)
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float64, 1e-11), (torch.float32, 1e-5)])
+@pytest.mark.parametrize("l1", [0.0, 0.1, 1.0])
+@pytest.mark.parametrize("w", [2.0, 30.0])
+def test_trees_handed_over_match_oracle(dtype, tol, l1, w):
+    """l1: the share of the nodes with an l1 term, whose messages are cut where they lie and
+    are sorted before the lane kernel takes them."""
+    par, off = _deep_trees()
+    N = par.size
+    rng = np.random.default_rng(int(w) + 3)
+    a = np.ones(N)
+    b = np.concatenate([np.sqrt(np.arange(m) + k) for k, m in enumerate(np.diff(off))])
+    c = rng.uniform(0.2, 1.0, N) * (rng.random(N) < l1)
+    d = b + rng.normal(size=N)
+    dev = [torch.tensor(v, dtype=dtype, device="cuda") for v in (a, b, c, d, np.full(N, -w), np.full(N, 0.7 * w))]
+    x = binding.tree_dp(torch.tensor(par, device="cuda"), torch.tensor(off, device="cuda"), dev[1], dev[4], dev[5],
+                        c=dev[2] if l1 else None, d=dev[3] if l1 else None)
+    _check(par, off, [v.double().cpu().numpy() for v in dev], x.double().cpu().numpy(), range(off.size - 1), tol)
+
+
+def test_numbering_is_checked_after_the_change_of_kernels():
+    """A path that is handed over, then a subtree that is not a contiguous range."""
+    n = 60
+    par = np.array([j + 1 for j in range(n)] + [n + 3, n + 4, n + 4, n + 4, -1], dtype=np.int64)
+    b = torch.tensor(np.sqrt(np.arange(par.size)), device="cuda")
+    w = torch.full_like(b, 30.0)
+    off = torch.tensor([0, par.size], device="cuda")
+    with pytest.raises(binding.TvChainError) as e:
+        binding.tree_dp(torch.tensor(par, device="cuda"), off, b, -w, w)
+    assert e.value.status == binding.TV_ERR_INVALID_ARG
+    par[n + 1:n + 4] = (n + 2, n + 3, n + 4)  # the same as a path: accepted
+    par[n] = n + 1
+    x = binding.tree_dp(torch.tensor(par, device="cuda"), off, b, -w, w).cpu().numpy()
+    o = oracle.tree_pq(par, np.ones(par.size), b.cpu().numpy(), np.zeros(par.size), np.zeros(par.size),
+                       -w.cpu().numpy(), w.cpu().numpy())[0]
+    assert np.abs(x - o).max() <= 1e-11 * max(np.ptp(o), np.ptp(b.cpu().numpy()))
