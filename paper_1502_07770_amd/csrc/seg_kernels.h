@@ -26,11 +26,11 @@
 //               tags); where they differ it reruns the segment from that end
 //               state until the deque meets a first-pass checkpoint (or the
 //               segment end) and redoes the backward pass left of it.
-//  k_seg_fix    one lane per chain: composes the value entering each segment
-//               from the root.  Chains whose deque outgrew the ring, or with a
-//               segment whose repair started from a state that was not yet the
-//               true one, are handed on (TV-l1: such a segment is redone here,
-//               sequentially).
+//  k_seg_fix    one lane per chain: redoes, sequentially, the rare segments
+//               whose repair started from a state that was not yet the true one;
+//               then composes the value entering each segment from the root.
+//               Chains whose deque outgrew the ring are handed on, and so are
+//               those with such segments where many have them (fix_rule).
 //  k_chain_wg   (group_dp.h) solves the handed-on chains, a workgroup each, the
 //               deque spread over lanes; k_seg_ovf for TV-l1, a pool of lanes
 //               with the set in a large ring or in HBM.
@@ -132,14 +132,16 @@ struct SegWs {
     T *seg_hi;
     int *seg_unc;       // [S][C] first node of the un-collapsed tail
     T *seg_xb;          // [S][C] x at the first node after the segment
-    int *ovf_count;     // chains appended to ovf_list (zeroed by k_seg_main)
-    int *ovf_list;      // [C] chains whose deque outgrew the LDS ring
+    int *ovf_count;     // [2] chains appended to ovf_list; segments repaired from a state that was not the
+                        // true one (both zeroed by k_seg_main)
+    int *ovf_list;      // [C] chains handed on by k_seg_fix
     LamPair<T> *sw_cp;  // [kCheckpoints][S][C] first-pass backward-sweep state at the checkpoints
     T *fb_lam;          // [fb_lanes][2n+4] HBM deques of the overflow kernel
     G *fb_tag;
     int64_t fb_cap;
     int64_t fb_lanes;
     const int *stop;    // device flag (or null): when set, every kernel of the launch returns at once
+    int list_L, list_waves;  // segment length and waves per chain of k_chain_wg on the list
 };
 
 // The launch's stop flag is set (a 2D solve that already met its stopping test).
@@ -1189,7 +1191,7 @@ __global__ __launch_bounds__(64) void k_seg_main(WsOf<T, Prob> ws, typename Prob
     if (seg_stopped(ws)) return;
     const int lane = threadIdx.x;
     const int64_t g = (int64_t)blockIdx.x * 64 + lane;
-    if (g == 0) *ws.ovf_count = 0;  // consumed by k_seg_fix / k_seg_ovf after this kernel
+    if (g == 0) ws.ovf_count[0] = ws.ovf_count[1] = 0;  // used by the kernels after this one
     if (g >= ws.S * ws.C) return;
     const int64_t c = g % ws.C, s = g / ws.C;
     const ChainSpan sp = Prob::span(pp, c, ws.n);
@@ -1286,6 +1288,10 @@ __global__ __launch_bounds__(64) void k_seg_repair(WsOf<T, Prob> ws, typename Pr
     // two runs coincide from some node on, so the saved end state is the true one
     const bool clean = stop < b || (b < n && equals_state(ws, R, s, kSaveEnd, c));
     ws.clean[cs] = clean ? 1 : 0;
+    if constexpr (!IsL1<Prob>::value) {  // one lane adds what the active lanes found
+        const unsigned long long m = __ballot(!clean && b < n);
+        if (m && lane == __ffsll(m) - 1) atomicAdd(ws.ovf_count + 1, __popcll(m));
+    }
     ws.rep_stop[s * C + c] = (int)stop;
     if (!clean && b < n) save_state(ws, R, s, kSaveEnd2, c);
     if (stop < b && sweep_cp_recorded(a, b, stop, ws.CK)) {
@@ -1366,18 +1372,40 @@ template <typename T, class Prob, int K, int P>
 __device__ bool fix_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
                           EntOf<T, Prob> *s_ent, int lane);
 
+// The most dirty segments (repaired from a state that was not the true one) with which
+// a chain is redone by its lane, where a launch has `all` of them; more, and it is
+// solved whole by k_chain_wg.  The lanes redo their chains side by side, so that costs
+// the launch as many segments as its worst chain has, 0.65 us a node (FP64 0.8; four
+// times that in a 2D step, whose sweep also reads and updates the iterates, and whose
+// dirty segments crowd in some images or rows: 24 images of 64 to 1024 rows, FP64, 16.3
+// ms, 19.3 with twice).  k_chain_wg's cost goes with the chains on the list: 1.3 us
+// (FP64 2.2) a step of a segment and a halo, later passes included, and about 4096 waves
+// at once.  One of them for all chains, as both kernels' times add up; a chain with far
+// more dirty segments than the others is handed on all the same.  us, by lanes / by
+// k_chain_wg, w = 0.5: 1 x 1,048,576 2960 / 19300, 64 x 65536 608 / 1766, 64 x 16384 FP64
+// 490 / 970; w = 2: 64 x 65536 55600 / 2220, 4096 x 4096 4980 / 1800.
+template <typename T, typename G>
+__device__ __forceinline__ float fix_rule(const SegWs<T, G> &ws, int all, bool step2d) {
+    const float C = (float)ws.C, mean = (float)all / C, most = (float)(ws.S > 2 ? ws.S - 2 : 1);
+    float worst = mean + 3.0f * sqrtf(mean) + 1.0f;
+    worst = worst < most ? worst : most;
+    const float turns = C * (1.0f - expf(-mean)) * (float)ws.list_waves * (1.0f / 4096.0f);
+    const float here = worst * (float)ws.L * (sizeof(T) == 4 ? 0.65f : 0.8f) * (step2d ? 4.0f : 1.0f);
+    const float there = (float)(ws.list_L + 64) * (sizeof(T) == 4 ? 1.3f : 2.2f) * (turns > 1.0f ? turns : 1.0f);
+    return here <= there ? 2.0f * worst : 0.0f;
+}
+
 // ---------------------------------------------------------------------------
-// Fix-up, one lane per chain (a no-op for almost every chain): chains with an
-// overflow, or a segment repaired from a state that was not the true one, go to
-// the list for k_chain_wg.  TV-l1 walks the segments here (fix_chain): where the
-// previous segment's saved end state is not the true one, the segment is redone
+// Fix-up, one lane per chain (a no-op for almost every chain).  Walks the
+// segments keeping track of whether the saved end state of the previous
+// segment is the true one; where it is not, the segment is redone
 // sequentially from the true state until a checkpoint matches and past the
-// region the repair kernel rewrote.
+// region the repair kernel rewrote (fix_chain), or the chain goes to the list
+// for k_chain_wg (fix_rule).  So do chains with an overflow.
 // ---------------------------------------------------------------------------
 template <typename T, class Prob, int K, int P>
 __global__ __launch_bounds__(64) void k_seg_fix(WsOf<T, Prob> ws, typename Prob::Params pp) {
-    constexpr bool kGroup = GroupOk<Prob>::value;  // dirty chains go to k_chain_wg
-    __shared__ EntOf<T, Prob> s_ent[kGroup ? 1 : CRing<T, K, typename Prob::Tag>::kRows * 64];
+    __shared__ EntOf<T, Prob> s_ent[CRing<T, K, typename Prob::Tag>::kRows * 64];
     if (seg_stopped(ws)) return;
     const int lane = threadIdx.x;
     const int64_t c = (int64_t)blockIdx.x * 64 + lane;
@@ -1389,13 +1417,20 @@ __global__ __launch_bounds__(64) void k_seg_fix(WsOf<T, Prob> ws, typename Prob:
     const uint8_t *ovf = ws.ovf + c * ws.S;
     const uint8_t *mis = ws.mis + c * ws.S;
     const uint8_t *cln = ws.clean + c * ws.S;
-    bool any_ovf = false, any_dirty = false;
+    bool any_ovf = false;
+    int64_t dirty = 0;
     for (int64_t s = 0; s < Sc; ++s) {
         any_ovf |= ovf[s] != 0;
-        if (s > 0 && s + 1 < Sc) any_dirty |= (mis[s] != 0) && (cln[s] == 0);
+        if (s > 0 && s + 1 < Sc) dirty += (mis[s] != 0) && (cln[s] == 0);
     }
-    bool redo = any_ovf || any_dirty;
-    if constexpr (!kGroup) redo = any_ovf || (any_dirty && !fix_chain<T, Prob, K, P>(ws, pp, sp, c, s_ent, lane));
+    bool redo = any_ovf;
+    if (!any_ovf && dirty > 0) {
+        if constexpr (GroupOk<Prob>::value) {
+            constexpr bool step2d = !std::is_empty<typename Prob::SinkPre>::value;
+            redo = (float)dirty > fix_rule(ws, ws.ovf_count[1], step2d);
+        }
+        if (!redo) redo = !fix_chain<T, Prob, K, P>(ws, pp, sp, c, s_ent, lane);
+    }
     if (redo) {
         ws.ovf_list[atomicAdd(ws.ovf_count, 1)] = (int)c;  // solved by k_chain_wg or k_seg_ovf
         return;
@@ -1572,7 +1607,7 @@ size_t seg_ws_layout(void *base, int64_t C, int64_t n, int64_t L, int64_t H, int
     const size_t o_unc = off;  off += al(sizeof(int) * (size_t)(S * C));
     const size_t o_xb = off;   off += al(sizeof(T) * (size_t)(S * C));
     const int64_t fbl = (C < kOverflowLanes ? (C + 63) / 64 * 64 : kOverflowLanes);
-    const size_t o_oc = off;   off += al(sizeof(int));
+    const size_t o_oc = off;   off += al(2 * sizeof(int));
     const size_t o_ol = off;   off += al(sizeof(int) * (size_t)C);
     const size_t o_sw = off;   off += al(sizeof(LamPair<T>) * (size_t)(kCheckpoints * S * C));
     const size_t o_fl = off;   off += al(sizeof(T) * (size_t)(fbl * cap));
@@ -1606,6 +1641,8 @@ size_t seg_ws_layout(void *base, int64_t C, int64_t n, int64_t L, int64_t H, int
         w.fb_cap = cap;
         w.fb_lanes = fbl;
         w.stop = nullptr;
+        w.list_L = 32;
+        w.list_waves = 16;
         *out = w;
     }
     return off;
@@ -1627,7 +1664,7 @@ inline GrpGeom grp_geom(int64_t C, int64_t n) {
     auto threads = [&](int l) { return (int)((n + l - 1) / l * 16 + 63) / 64 * 64; };
     if (n <= 384 && C * (threads(16) / 64) <= (n <= 128 ? 512 : 1280)) L = 16;
     while (L < 128 && C * (threads(L) / 64) > 4096) L *= 2;
-    while (threads(L) > 1024) L += 16;
+    if (threads(L) > 1024) L = (int)((n + 63) / 64 + 15) / 16 * 16;
     return GrpGeom{L, 64, threads(L), 0, 0};
 }
 
@@ -1671,7 +1708,13 @@ hipError_t seg_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
         hipLaunchKernelGGL((k_seg_repair<T, Prob, K, P>), dim3(rb), dim3(64), 0, stream, ws, pp);
     }
     const unsigned fb = (unsigned)((ws.C + 63) / 64);
-    hipLaunchKernelGGL((k_seg_fix<T, Prob, K, P>), dim3(fb), dim3(64), 0, stream, ws, pp);
+    WsOf<T, Prob> wf = ws;
+    if constexpr (GroupOk<Prob>::value) {
+        const GrpGeom gm = grp_geom(ws.C, ws.n);
+        wf.list_L = gm.L;
+        wf.list_waves = gm.threads / 64;
+    }
+    hipLaunchKernelGGL((k_seg_fix<T, Prob, K, P>), dim3(fb), dim3(64), 0, stream, wf, pp);
     if constexpr (GroupOk<Prob>::value) {
         const hipError_t e = grp_launch<T, Prob, true>(ws, pp, stream);
         if (e != hipSuccess) return e;

@@ -156,3 +156,28 @@ def test_weighted_data_and_asymmetric_edges_equal_lane_kernels(tuning, dtype):
             tuning(target_lanes=1, min_segment=1, ring_slots=32)
             ref = binding.chain_dp(t[1], t[2], t[3], a=t[0], dim=1)
             assert torch.equal(got, ref) and torch.equal(cols, ref), (C, n)
+
+
+def _one_lane(tuning, y, w, dtype):
+    """Each chain on one lane with the largest ring (FP32 128 slots, FP64 32): chains whose deque
+    the ring holds stay there whole.  Returns x and whether the ring held every chain."""
+    yv, wv = y.double().cpu().numpy(), w.double().cpu().numpy()
+    _, st = oracle.chain_prox(yv, w=wv, counts=True)
+    tuning(target_lanes=1, min_segment=1, halo=128, ring_slots=128)
+    return binding.chain_prox(y, w, dim=1), st[:, 2] + 2 < (128 if dtype == torch.float32 else 32)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("C,n,L,halo", [(3, 70000, 32, 48), (3, 70000, 32, 0), (40, 5000, 64, 32), (300, 600, 32, 32),
+                                        (2000, 400, 32, 16), (1, 33, 32, 0), (5, 97, 32, 0)])
+def test_segments_redone_by_lanes_and_by_groups(tuning, C, n, L, halo, dtype):
+    """Short halos leave a few or most segments repaired from a wrong state: redone by the
+    chain's lane or the chain solved whole by a workgroup, the bits of one lane per chain."""
+    for seed, wv in enumerate((0.2, 0.6, 1.5)):
+        y = synth.piecewise_constant(C, n, seed=n + seed)
+        w = wv * synth.edge_weights((C, n), lo=0.5, hi=1.0, seed=seed)
+        yt, wt = torch.tensor(y, dtype=dtype, device="cuda"), torch.tensor(w, dtype=dtype, device="cuda")
+        ref, held = _one_lane(tuning, yt, wt, dtype)
+        assert held.all()
+        tuning(target_lanes=1 << 30, min_segment=L, halo=halo, ring_slots=32)
+        assert torch.equal(binding.chain_prox(yt, wt, dim=1), ref), wv
