@@ -223,10 +223,10 @@ __device__ __forceinline__ void grp_step(GDeque<T, G> &S, const StepIn<T, G> &in
 // One chain per workgroup.
 // ---------------------------------------------------------------------------
 // Segment length, halo and block size of a launch; lds_lam: the lambda pairs of
-// a chain stay in LDS (else they go to the workspace's stream); cap: entries of
-// the LDS deque of grp_lane_chain, in the same memory (0: an HBM deque per block).
+// a chain stay in LDS (else they go to the workspace's stream); lds: bytes of
+// dynamic LDS (the deep chains' deques take all of it).
 struct GrpGeom {
-    int L, H, threads, lds_lam, cap;
+    int L, H, threads, lds_lam, lds;
 };
 struct GrpLds {
     void *lam;    // [S * L] pairs (lds_lam)
@@ -234,6 +234,7 @@ struct GrpLds {
     int *size;    // [groups] (-1: no end state yet)
     int *need;    // [groups + 1] the state entering a segment changed
     int *wide;    // [groups + 1] the segments of a pass that outgrew 16 lanes; their number first
+    int *deep;    // a deque outgrew a wave
     void *w;      // [2 * waves] the waves' composed clips
 };
 constexpr size_t grp_lds_bytes(size_t threads, size_t elem, size_t tag) {
@@ -244,7 +245,12 @@ template <class Prob>
 struct GroupOk : std::bool_constant<!IsL1<Prob>::value> {};
 
 // Solves chain c with groups of GW lanes; false (for the whole workgroup) if a
-// deque outgrew a wave, or an end state its 2 GW entries.  A segment whose deque
+// deque outgrew a wave (then *sh.deep too), or an end state its 2 GW entries.  Where the
+// block has `side` chains, also (and *sh.deep) if more than 3 / side of the segments of a
+// pass outgrow 16 lanes: a wave runs neighbouring ones one after the other, 0.8 us a node
+// (FP64 1.6), grp_deep_chains the chains side by side, 1.2 us and more (us, 16384 x 512
+// ramps at w = 3: 2260, all by waves 25400; 4096 x 4096 random walks, a part of whose
+// segments are wide, with 0.4 in place of 3 / side 11200, 3780 by waves).  A segment whose deque
 // outgrows 16 lanes is run again in the same pass by a whole wave, from its
 // neighbour's end state (the wide segments of a pass, a wave each): deques of 16
 // to 23 breakpoints come up in a few segments of many chains of a 2D iteration
@@ -255,7 +261,7 @@ struct GroupOk : std::bool_constant<!IsL1<Prob>::value> {};
 // for a tile later; with one, before the loop).
 template <typename T, class Prob, int GW, bool kStream>
 __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
-                          const GrpGeom &gm, const GrpLds &sh, int L) {
+                          const GrpGeom &gm, const GrpLds &sh, int L, int side = 0) {
     using R = Ring<GW>;
     using G = typename Prob::Tag;
     constexpr bool kGen = Prob::kGen;
@@ -485,6 +491,10 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
             if (mine && wide && gl == 0) sh.wide[1 + atomicAdd(sh.wide, 1)] = g;
             __syncthreads();
             const int count = sh.wide[0];
+            if ((int64_t)count * L * side > 3 * (int64_t)n) {
+                if (tid == 0) *sh.deep = 1;
+                return false;
+            }
             bad = false;
             for (int q0 = 0; q0 < count; q0 += nw) {
                 // (a segment whose neighbour has no end state yet waits for it)
@@ -499,11 +509,13 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
                     int j, size;
                     order(kWave, S, j, size);
                     bad = S.ovf != 0 || size > E;
+                    if (S.ovf != 0) *sh.deep = 1;
                     if (!bad) end_state(kWave, S, q, j, size, true);
                 }
                 if (__syncthreads_or(bad)) return false;
             }
         } else if (__syncthreads_or(bad)) {
+            if (tid == 0) *sh.deep = 1;
             return false;
         }
         bool need = act && g > 0 && sh.need[g] != 0;
@@ -560,8 +572,7 @@ __device__ bool grp_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
     return true;
 }
 
-// A deque of one lane in LDS: a ring of cap >= 2 n + 4 entries (a step adds at
-// most two; tags first), for dq_scan and dq_update.
+// A deque of one lane in LDS: a ring of cap entries, for dq_scan and dq_update.
 template <typename T, typename G> struct LdsDeque {
     G *k;
     T *l;
@@ -578,17 +589,19 @@ template <typename T, typename G> struct LdsDeque {
     __device__ __forceinline__ void shift(int d) { head = at(d); }
 };
 
-// The whole chain on one lane with its deque in LDS, lambda in the stream.
+// The whole chain on one lane with its deque in LDS (cap entries at k and l), lambda in
+// the stream; false if the deque outgrew them.
 template <typename T, class Prob>
-__device__ void grp_lane_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
-                               void *mem, int cap) {
+__device__ bool grp_lane_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, const ChainSpan &sp, int64_t c,
+                               typename Prob::Tag *k, T *l, int cap) {
     using G = typename Prob::Tag;
     constexpr bool kGen = Prob::kGen;
     const auto src = Prob::src(pp, sp);
     auto cy = carry_before<T, Prob>(src, 0);
-    LdsDeque<T, G> D{(G *)mem, (T *)((G *)mem + cap), cap, 0, 0};
+    LdsDeque<T, G> D{k, l, cap, 0, 0};
     D.put(0, mk_ent<T, G>(pos_inf<T>(), (G)0));
     for (int64_t i = 0; i < sp.n; ++i) {
+        if (D.size + 3 > cap) return false;  // a step writes one entry before the front and two past the back
         const auto pr = src.load(i);
         const auto in = step_in<T, Prob>(src, pr, i, i == sp.n - 1, cy);
         const EndSlope<T, G, kGen> es(in.sf, in.sprev);
@@ -601,12 +614,55 @@ __device__ void grp_lane_chain(const WsOf<T, Prob> &ws, const typename Prob::Par
         put_lam<T>(ws.lam, i, ws.C, c, lm, i == sp.n - 1 ? lm : lp);
     }
     full_backward<T, Prob>(ws, pp, sp, c);
+    return true;
 }
 
-// A launch over all chains (kList false), or over the chains in ws.ovf_list.
+// The block's chains with more than 63 breakpoints (the first `nd` of its slots of the
+// list), a lane of its first wave each, all of the block's LDS shared out among them;
+// those that outgrow their share again with fewer lanes, and at last in HBM.  A single
+// chain goes there at once where its block has an HBM deque (1000 x 300 ramps, w = 30:
+// 570 us, 735 in LDS).  us, many chains, ramps at w = 30, the ring of a lane each of the
+// kernel for TV-l1 / one lane of a block in HBM / this: 4096 x 4096 20100 / 50000 / 8030,
+// FP64 64500 / 109000 / 16700, 16384 x 512 12700 / 30000 / 2910.
+template <typename T, class Prob, bool kList>
+__device__ void grp_deep_chains(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, int64_t nd, char *mem,
+                                int lds) {
+    using G = typename Prob::Tag;
+    const int lane = threadIdx.x, all = lds / (int)(sizeof(T) + sizeof(G));
+    const int64_t slots = ws.fb_lanes / gridDim.x;
+    for (int most = kList || slots < 1 ? 64 : 0; nd > 0; most /= 8) {
+        const bool hbm = most == 0;  // after 64, 8 and 1 lanes
+        int lanes = hbm ? (int)(slots < 64 ? slots : 64) : most;
+        if (lanes < 1) return;  // (the LDS holds any deque of a launch without slots)
+        lanes = nd < lanes ? (int)nd : lanes;
+        const int cap = (all / lanes - 1) | 1;  // odd: the lanes' deques lie in different banks
+        int64_t failed = 0;
+        for (int64_t at = 0; at < nd; at += lanes) {
+            int *const slot = ws.ovf_list + blockIdx.x;
+            bool bad = false;
+            int c = 0;
+            if (lane < lanes && at + lane < nd) {
+                c = slot[(at + lane) * gridDim.x];
+                const ChainSpan sp = Prob::span(pp, c, ws.n);
+                if (hbm)
+                    seg_full_chain<T, Prob>(ws, pp, sp, c, blockIdx.x + (int64_t)lane * gridDim.x);
+                else
+                    bad = !grp_lane_chain<T, Prob>(ws, pp, sp, c, (G *)mem + (int64_t)lane * cap,
+                                                   (T *)((G *)mem + (int64_t)lanes * cap) + (int64_t)lane * cap, cap);
+            }
+            const uint64_t m = lanes_where(bad);
+            if (bad) slot[(failed + __popcll(m & ((1ull << lane) - 1))) * gridDim.x] = c;
+            failed += __popcll(m);
+            __threadfence_block();
+        }
+        nd = failed;
+    }
+}
+
+// A launch over all chains (kList false, a block each), or over the chains in ws.ovf_list.
 // Segments whose deque outgrows a group of 16 are run by a whole wave (grp_chain),
 // chains with more than 31 breakpoints at a segment's end with a wave per segment,
-// and beyond 63 breakpoints on one lane, the deque in LDS (gm.cap) or in HBM.
+// and chains with more than 63 breakpoints are left for the end (grp_deep_chains).
 template <typename T, class Prob, bool kList>
 __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Prob::Params pp, GrpGeom gm) {
     extern __shared__ __align__(16) char s_grp[];
@@ -627,9 +683,13 @@ __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Pr
         p += sizeof(int) * (S16 + 4);
         sh.wide = (int *)p;
         p += sizeof(int) * (S16 + 4);
+        sh.deep = (int *)p;
+        p += 4 * sizeof(int);
         sh.lam = p;
     }
     const int64_t count = kList ? (int64_t)*ws.ovf_count : ws.C;
+    const int side = kList ? (int)((count + gridDim.x - 1) / gridDim.x) : 0;
+    int64_t deep = 0;
     for (int64_t q = blockIdx.x; q < count; q += gridDim.x) {
         // neighbouring chains on one XCD (blocks go round the eight XCDs in turn):
         // neighbouring columns share cache lines
@@ -637,26 +697,26 @@ __global__ __launch_bounds__(1024) void k_chain_wg(WsOf<T, Prob> ws, typename Pr
         const int64_t c = kList ? (int64_t)ws.ovf_list[q] : x * per + (x < rem ? x : rem) + (q >> 3);
         const ChainSpan sp = Prob::span(pp, c, ws.n);
         if (sp.n <= 0) continue;
-        if (!grp_chain<T, Prob, 16, kList>(ws, pp, sp, c, gm, sh, gm.L)) {
+        if (threadIdx.x == 0) *sh.deep = 0;
+        bool done = grp_chain<T, Prob, 16, kList>(ws, pp, sp, c, gm, sh, gm.L, side);
+        if (!done) {
             __syncthreads();
-            const int waves = (int)blockDim.x / 64;
-            const int Lw = (int)((sp.n + waves - 1) / waves + 15) / 16 * 16;
-            if (!grp_chain<T, Prob, 64, kList>(ws, pp, sp, c, gm, sh, Lw)) {
-                __syncthreads();
-                if (threadIdx.x == 0) {
-                    if (gm.cap)
-                        grp_lane_chain<T, Prob>(ws, pp, sp, c, s_grp, gm.cap);
-                    else
-                        seg_full_chain<T, Prob>(ws, pp, sp, c, blockIdx.x);
-                }
+            if (*sh.deep == 0) {
+                const int waves = (int)blockDim.x / 64;
+                const int Lw = (int)((sp.n + waves - 1) / waves + 15) / 16 * 16;
+                done = grp_chain<T, Prob, 64, kList>(ws, pp, sp, c, gm, sh, Lw);
             }
         }
-        if constexpr (kList) {  // the segments' tails are done
+        if (!done) {
+            if (threadIdx.x == 0) ws.ovf_list[blockIdx.x + deep * gridDim.x] = (int)c;
+            ++deep;
+        } else if constexpr (kList) {  // the segments' tails are done
             for (int64_t s = threadIdx.x; s * ws.L < sp.n; s += blockDim.x)
                 ws.seg_unc[s * ws.C + c] = (int)((s + 1) * ws.L < sp.n ? (s + 1) * ws.L : sp.n);
         }
         __syncthreads();
     }
+    if (deep && threadIdx.x < 64) grp_deep_chains<T, Prob, kList>(ws, pp, deep, s_grp, gm.lds);
 }
 
 #pragma clang fp contract(fast)

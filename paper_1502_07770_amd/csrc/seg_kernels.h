@@ -1668,29 +1668,43 @@ inline GrpGeom grp_geom(int64_t C, int64_t n) {
     return GrpGeom{L, 64, threads(L), 0, 0};
 }
 
+// The same for the chains of a list, whose number the host does not know: segments of
+// 64 to 128 nodes in about 16 groups, as many as it takes beyond 2048 nodes, 64 at
+// most (32-node ones take more passes: what is handed on has a long memory).  Four waves a chain and 1024 blocks fill the chip (four waves a SIMD); with
+// more waves a chain 512 blocks do.  us against 128-node segments and 512 blocks for
+// all: 16384 x 512 at w = 5 2750 -> 853, FP64 4460 -> 1140; 24 images of 64 to 800
+// rows 25.4 -> 23.7 ms.
+inline GrpGeom list_geom(int64_t n) {
+    auto segment = [&](int64_t groups) { return (int)((n + groups - 1) / groups + 15) / 16 * 16; };
+    int L = segment(16);
+    L = L < 64 ? 64 : (L < 128 ? L : 128);
+    L = L > segment(64) ? L : segment(64);
+    return GrpGeom{L, 64, (int)((n + L - 1) / L * 16 + 63) / 64 * 64, 0, 0};
+}
+
 template <typename T, class Prob, bool kList>
 hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, hipStream_t stream) {
-    GrpGeom gm = grp_geom(ws.C, ws.n);
+    GrpGeom gm = kList ? list_geom(ws.n) : grp_geom(ws.C, ws.n);
     const int64_t waves = gm.threads / 64, Lw = (ws.n + waves - 1) / waves + 16;
-    const size_t most = 160 * 1024, state = grp_lds_bytes(gm.threads, sizeof(T), sizeof(typename Prob::Tag)),
+    const int64_t full = waves <= 4 ? 1024 : 512, blocks = kList && ws.C > full ? full : ws.C;
+    const size_t most = 159 * 1024,                       // (block reductions take 256 bytes more)
+                 share = kList ? most / (full / 256) : most,  // of a block with as many on its CU as the chip takes
+                 state = grp_lds_bytes(gm.threads, sizeof(T), sizeof(typename Prob::Tag)),
                  lam = 2 * sizeof(T) * (size_t)(ws.n + (Lw > gm.L ? Lw : gm.L));
-    gm.lds_lam = state + lam <= most;
+    gm.lds_lam = state + lam <= share;
     if (!kList && !gm.lds_lam) return hipErrorInvalidValue;  // excluded by kGrpMaxLen
     size_t lds = gm.lds_lam ? state + lam : state;
-    // a block of a list or of a launch of few chains has an HBM deque of its own;
-    // the blocks of other launches have room for one in LDS.  512 blocks of a list
-    // fill the chip (24 images of 64 to 1024 rows: 13.5 ms, 256 blocks 14.5, 1024
-    // the same) and an empty list costs no more than with 256.
-    const int64_t blocks = kList && ws.C > 512 ? 512 : ws.C;
-    if (blocks > ws.fb_lanes) {
-        gm.cap = (int)(2 * ws.n + 4);
-        const size_t dq = (sizeof(T) + sizeof(typename Prob::Tag)) * (size_t)gm.cap;
-        lds = lds > dq ? lds : dq;
-        if (lds > most) return hipErrorInvalidValue;  // excluded by grp_plan_ok
-    }
+    // the blocks of a list share out what their LDS holds among their deep chains; those
+    // of a launch of more chains than HBM deques have room for a whole deque
+    size_t want = kList ? share : 0;
+    if (blocks > ws.fb_lanes) want = (sizeof(T) + sizeof(typename Prob::Tag)) * (size_t)(2 * ws.n + 6);
+    lds = lds > want ? lds : want;
+    if (lds > most) return hipErrorInvalidValue;  // excluded by grp_plan_ok
+    gm.lds = (int)lds;
     if (lds > 64 * 1024) {
+        // (always the same value: other threads launch this kernel with other sizes)
         const hipError_t e = hipFuncSetAttribute((const void *)k_chain_wg<T, Prob, kList>,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)most);
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL((k_chain_wg<T, Prob, kList>), dim3((unsigned)blocks), dim3((unsigned)gm.threads), lds, stream,
@@ -1710,7 +1724,7 @@ hipError_t seg_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
     const unsigned fb = (unsigned)((ws.C + 63) / 64);
     WsOf<T, Prob> wf = ws;
     if constexpr (GroupOk<Prob>::value) {
-        const GrpGeom gm = grp_geom(ws.C, ws.n);
+        const GrpGeom gm = list_geom(ws.n);
         wf.list_L = gm.L;
         wf.list_waves = gm.threads / 64;
     }

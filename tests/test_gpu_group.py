@@ -181,3 +181,70 @@ def test_segments_redone_by_lanes_and_by_groups(tuning, C, n, L, halo, dtype):
         assert held.all()
         tuning(target_lanes=1 << 30, min_segment=L, halo=halo, ring_slots=32)
         assert torch.equal(binding.chain_prox(yt, wt, dim=1), ref), wv
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("C,n", [(3000, 300), (1100, 1000), (40, 5000), (6, 9000)])
+def test_deep_chains_side_by_side(tuning, C, n, dtype):
+    """Ramps of 16 to some 300 breakpoints among shallow chains, several to a block of the
+    list: by a wave where a part is wide, by a lane each in the block's LDS where all is.
+    The bits of one lane per chain where its ring holds the deque, else the oracle's values."""
+    y = synth.piecewise_constant(C, n, seed=n)
+    w = np.full((C, n), 0.4)
+    ramp = np.arange(C) % 3 > 0
+    y[ramp] = np.sqrt(np.arange(n)[None, :] + 3.0 * np.arange(ramp.sum())[:, None])
+    y[1::6] += 0.05 * synth.normal(y[1::6].shape, seed=C)
+    w[ramp] = np.array([(0.5, 2.0, 10.0, 100.0)[c % 4] for c in range(ramp.sum())])[:, None]
+    yt, wt = torch.tensor(y, dtype=dtype, device="cuda"), torch.tensor(w, dtype=dtype, device="cuda")
+    ref, held = _one_lane(tuning, yt, wt, dtype)
+    assert 0 < held.sum() < C
+    tuning(target_lanes=1 << 30, min_segment=128, halo=64, ring_slots=16)
+    got = binding.chain_prox(yt, wt, dim=1)
+    assert torch.equal(got[torch.tensor(held, device="cuda")], ref[torch.tensor(held, device="cuda")])
+    pick = np.concatenate([np.nonzero(~held)[0][:40], np.nonzero(held)[0][:10]])
+    yv, wv = yt.double().cpu().numpy()[pick], wt.double().cpu().numpy()[pick]
+    err = np.abs(got.double().cpu().numpy()[pick] - oracle.chain_prox(yv, w=wv)).max(axis=1)
+    assert (err <= TOL[dtype] * np.maximum(np.ptp(yv, axis=1), 1.0)).all()
+
+
+def test_deques_that_outgrow_the_blocks_lds(tuning):
+    """1500 constant nodes with zero weights hold 3000 breakpoints (FP64), more than the LDS of
+    a block of the list: one lane in HBM, the bits of the small launch's walk there."""
+    n = 1500
+    y, w = np.ones((5, n)), np.zeros((5, n))
+    w[:, n - 60:] = 0.25
+    y[:, n - 60:] += 0.1 * synth.normal((5, 60), seed=3)
+    y[1] += np.linspace(0.0, 1.0, n)
+    yt, wt = torch.tensor(y, device="cuda"), torch.tensor(w, device="cuda")
+    small = binding.chain_prox(yt, wt, dim=1)
+    tuning(target_lanes=1 << 30, min_segment=128, halo=64, ring_slots=16)
+    got = binding.chain_prox(yt, wt, dim=1)
+    assert torch.equal(got, small)
+    assert np.abs(got.cpu().numpy() - oracle.chain_prox(y, w=w)).max() <= TOL[torch.float64]
+
+
+def test_sizes_of_lds_from_several_threads():
+    """Launches of one kernel with little and with most of the LDS, on streams of four threads."""
+    import threading
+    ys = [torch.rand(40, n, dtype=torch.float64, device="cuda") for n in (100, 6000, 500, 5000)]
+    refs = [binding.chain_prox(y, 0.3, dim=1) for y in ys]
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(k):
+        try:
+            s = torch.cuda.Stream()
+            with torch.cuda.stream(s):
+                for _ in range(50):
+                    x = binding.chain_prox(ys[k], 0.3, dim=1)
+                s.synchronize()
+                if not torch.equal(x, refs[k]):
+                    errors.append(k)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    assert not errors, errors
