@@ -77,7 +77,7 @@ std::map<TunedKey, SegPlan> &tuned_map() {
 }
 }  // namespace
 
-SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem) {
+SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem, int64_t nodes) {
     {
         std::lock_guard<std::mutex> lk(g_tuned_mu);
         auto it = tuned_map().find(TunedKey{kind, num_chains, n, elem});
@@ -92,14 +92,8 @@ SegPlan seg_plan(int64_t num_chains, int64_t n, int kind, size_t elem) {
     const bool half = iter2d || kind == kPlanDp ||
                       (kind == kPlanChain && (elem == 8 || (num_chains >= (int64_t(1) << 16) && n <= 256)));
     SegPlan p = plan_for(by_default && half ? kHalfTuning : t, num_chains, n);
-    // A group step in FP64 costs twice an FP32 one, a lane step a quarter more: the
-    // group kernel up to 1.6M nodes there (us, prox at w = 0.3, group / lanes: 1000 x
-    // 1500 242 / 350, 1500 x 1500 392 / 312; a 2D iteration at lambda = 0.1: 1250 x
-    // 1250 553 / 630, 1700 x 1700 930 / 713), a batch of images up to twice that (its
-    // num_chains * n counts the longest image's side for all).
-    const int64_t most64 = (int64_t(batch ? 12 : 6) << 18) / (n < 256 ? 4 : 1);
     p.wg = by_default && (iter2d || chain) && grp_plan_ok(num_chains, n, iter2d) &&
-           (elem == 4 || num_chains * n <= most64);
+           grp_wins(num_chains, n, elem, iter2d, nodes > 0 ? nodes : num_chains * n);
     return p;
 }
 

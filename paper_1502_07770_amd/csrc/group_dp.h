@@ -24,8 +24,8 @@
 // rerun from the true state where they differ until nothing changes (round k
 // makes the first k + 1 segments final), and the clips are composed by a scan
 // over the nodes (clips are closed under composition, and composing them
-// rounds nothing).  So a launch is one kernel instead of five.
-// Measured per node step: see k_chain_wg.
+// rounds nothing).  So a launch is one kernel instead of five.  A step takes 0.4 us
+// (FP64 0.75) at up to three waves a SIMD and 0.13 us more for each further one.
 #pragma once
 
 namespace tvc {
@@ -222,12 +222,6 @@ __device__ __forceinline__ void grp_step(GDeque<T, G> &S, const StepIn<T, G> &in
 // ---------------------------------------------------------------------------
 // One chain per workgroup.
 // ---------------------------------------------------------------------------
-// Segment length, halo and block size of a launch; lds_lam: the lambda pairs of
-// a chain stay in LDS (else they go to the workspace's stream); lds: bytes of
-// dynamic LDS (the deep chains' deques take all of it).
-struct GrpGeom {
-    int L, H, threads, lds_lam, lds;
-};
 struct GrpLds {
     void *lam;    // [S * L] pairs (lds_lam)
     void *l, *k;  // end states [2 * threads] (group g's entries from 2 g * GW, at most 64)
@@ -237,10 +231,6 @@ struct GrpLds {
     int *deep;    // a deque outgrew a wave
     void *w;      // [2 * waves] the waves' composed clips
 };
-constexpr size_t grp_lds_bytes(size_t threads, size_t elem, size_t tag) {
-    return (2 * elem + 2 * tag + 2) * threads + 256;
-}
-
 template <class Prob>
 struct GroupOk : std::bool_constant<!IsL1<Prob>::value> {};
 

@@ -1508,11 +1508,11 @@ __device__ bool fix_chain(const WsOf<T, Prob> &ws, const typename Prob::Params &
 }
 
 // ---------------------------------------------------------------------------
-// Overflowed chains, solved sequentially by a bounded pool of lanes: first with
-// the largest LDS ring a workgroup may hold (160 KiB on gfx950: 256 slots of
-// 8-byte entries, 128 of 16-byte ones, 64 of 32-byte ones), and only if the
-// deque outgrows that too, with the deque in HBM (lane l owns deque storage
-// l).  Both paths compute the same results as the segmented one.
+// Overflowed TV-l1 chains, solved sequentially by a bounded pool of lanes: first
+// with the largest LDS ring a workgroup may hold (160 KiB on gfx950: 64 slots of
+// 32-byte entries), and only if the set outgrows that too, with the set in HBM
+// (lane l owns storage l).  Both paths compute the same results as the segmented
+// one.
 // ---------------------------------------------------------------------------
 template <typename T, typename G> struct OvfRing {
     using E = Ent<T, G>;
@@ -1648,29 +1648,9 @@ size_t seg_ws_layout(void *base, int64_t C, int64_t n, int64_t L, int64_t H, int
     return off;
 }
 
-// Geometry of a workgroup-per-chain launch: 32-node segments with a 64-node
-// halo, in at most 64 groups; twice as long (the halo costs less, the chain's
-// latency more) while there are more than four waves per SIMD.  us per prox /
-// per 2D iteration, FP32, w = 0.3: 512 x 512 at L = 32 66 / 119, 64 77 / 153,
-// 128 100 / 222; 1024 x 1024 143 / 279, 103 / 261, 116 / 343.  Halos of 48 to
-// 96 are within 5% of it, 32 leaves more segments to run again.  16-node segments
-// where half of the SIMDs would stay idle, on chains short enough that their
-// later passes do not add up (us, L = 32 / 16: 64 x 256 47 / 40, 256 x 256 57 / 51,
-// 2D 203 x 317 FP64 112 / 103; but 128 x 512 59 / 62, 64 x 1000 56 / 75), and up to
-// 128 nodes, where 32-node segments fit one wave, only on a quarter of the chip
-// (2D 128 x 128 60 / 52; 512 x 128 42 / 44).
-inline GrpGeom grp_geom(int64_t C, int64_t n) {
-    int L = 32;
-    auto threads = [&](int l) { return (int)((n + l - 1) / l * 16 + 63) / 64 * 64; };
-    if (n <= 384 && C * (threads(16) / 64) <= (n <= 128 ? 512 : 1280)) L = 16;
-    while (L < 128 && C * (threads(L) / 64) > 4096) L *= 2;
-    if (threads(L) > 1024) L = (int)((n + 63) / 64 + 15) / 16 * 16;
-    return GrpGeom{L, 64, threads(L), 0, 0};
-}
-
-// The same for the chains of a list, whose number the host does not know: segments of
-// 64 to 128 nodes in about 16 groups, as many as it takes beyond 2048 nodes, 64 at
-// most (32-node ones take more passes: what is handed on has a long memory).  Four waves a chain and 1024 blocks fill the chip (four waves a SIMD); with
+// The same for the chains of a list, whose number the host does not know: 64 to 128 nodes in
+// about 16 groups, as many as it takes beyond 2048 nodes, 64 at most (32-node ones take
+// more passes: what is handed on has a long memory).  Four waves a chain and 1024 blocks fill the chip (four waves a SIMD); with
 // more waves a chain 512 blocks do.  us against 128-node segments and 512 blocks for
 // all: 16384 x 512 at w = 5 2750 -> 853, FP64 4460 -> 1140; 24 images of 64 to 800
 // rows 25.4 -> 23.7 ms.

@@ -646,8 +646,8 @@ static tv_status batched_solve_t(const BGeom &g, const int64_t *H, const int64_t
     if (s0 != TV_OK) return s0;
     const unsigned nb = (unsigned)((g.total + 255) / 256);
     const int every = opt->gap_every > 0 ? opt->gap_every : 1;
-    const SegPlan pr = seg_plan(g.nrows, g.maxW, kPlanBatchRow, sizeof(T)),
-                  pc = seg_plan(g.ncols, g.maxH, kPlanBatchCol, sizeof(T));
+    const SegPlan pr = seg_plan(g.nrows, g.maxW, kPlanBatchRow, sizeof(T), g.total),
+                  pc = seg_plan(g.ncols, g.maxH, kPlanBatchCol, sizeof(T), g.total);
     if (seg_ws_bytes_plan<T>(g.nrows, g.maxW, pr) > ws.seg_bytes ||
         seg_ws_bytes_plan<T>(g.ncols, g.maxH, pc) > ws.seg_bytes)
         return TV_ERR_WORKSPACE;
@@ -701,8 +701,8 @@ static tv_status batched_autotune_t(const BGeom &g, const int64_t *H, const int6
     if (s != TV_OK) return s;
     // a few iterations first, so the plans are timed on deques as deep as the
     // solve's later iterations build (no gap evaluation: nothing stops)
-    if (batched_iters<T>(g, ws, f, 0, kTuneWarm, false, 0.0, seg_plan(g.ncols, g.maxH, kPlanBatchCol, sizeof(T)),
-                         seg_plan(g.nrows, g.maxW, kPlanBatchRow, sizeof(T)), st) != hipSuccess)
+    if (batched_iters<T>(g, ws, f, 0, kTuneWarm, false, 0.0, seg_plan(g.ncols, g.maxH, kPlanBatchCol, sizeof(T), g.total),
+                         seg_plan(g.nrows, g.maxW, kPlanBatchRow, sizeof(T), g.total), st) != hipSuccess)
         return TV_ERR_HIP;
     // the timed steps read iteration kTuneWarm's scalars from the first slot
     hipLaunchKernelGGL(k_ctl_sched, dim3(1), dim3(64), 0, st, ws.ctl, ws.sched, 1);

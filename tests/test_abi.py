@@ -301,9 +301,10 @@ class _SegPlan(ctypes.Structure):
 @pytest.fixture
 def plans(lib):
     """The library's plan rule and its table of tuned plans (C++ functions of the .so):
-    plan(chains, length, kind, element size) and tuned(kind, chains, length, plan, element size)."""
-    plan, tuned = lib._ZN3tvc8seg_planEllim, lib._ZN3tvc13seg_set_tunedEillRKNS_7SegPlanEm
-    plan.restype, plan.argtypes = _SegPlan, [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t]
+    plan(chains, length, kind, element size, nodes) and tuned(kind, chains, length, plan, element size)."""
+    plan, tuned = lib._ZN3tvc8seg_planElliml, lib._ZN3tvc13seg_set_tunedEillRKNS_7SegPlanEm
+    plan.restype = _SegPlan
+    plan.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int, ctypes.c_size_t, ctypes.c_int64]
     tuned.restype = None
     tuned.argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.POINTER(_SegPlan), ctypes.c_size_t]
     yield plan, tuned
@@ -314,7 +315,7 @@ def plans(lib):
 def test_tuned_plans_are_per_precision(plans, kind):
     """A plan tuned in one precision leaves the other one's plan as it was."""
     plan, tuned = plans
-    get = lambda elem: [getattr(plan(1500, 1500, kind, elem), f) for f, _ in _SegPlan._fields_]
+    get = lambda elem: [getattr(plan(1500, 1500, kind, elem, 0), f) for f, _ in _SegPlan._fields_]
     for elem, other in ((4, 8), (8, 4)):
         before = get(other)
         p = _SegPlan(32, 16, 32, 32, 0)
@@ -322,3 +323,23 @@ def test_tuned_plans_are_per_precision(plans, kind):
         assert get(elem) == [32, 16, 32, 32, 0]
         assert get(other) == before
         binding.autotune_clear()
+
+
+@pytest.mark.parametrize("kind,elem,chains,length,group", [
+    (0, 4, 2048, 8, 1), (0, 4, 2049, 8, 0), (0, 4, 50000, 2, 0), (0, 4, 4096, 48, 1), (0, 4, 4097, 48, 0),
+    (0, 4, 1500, 1500, 1), (0, 4, 6000, 390, 0), (0, 4, 250, 6144, 1), (0, 4, 1, 6145, 0), (5, 4, 512, 4096, 1),
+    (0, 8, 768, 8, 1), (0, 8, 769, 8, 0), (0, 8, 1000, 1500, 1), (0, 8, 300, 5000, 0), (0, 8, 200, 5000, 1),
+    (0, 8, 4000, 300, 0), (0, 8, 1024, 2048, 0), (0, 8, 768, 2048, 1),
+    (1, 4, 1700, 1700, 1), (1, 4, 2048, 2048, 0), (2, 4, 2200, 2100, 0), (1, 8, 1250, 1250, 1), (1, 8, 1500, 1500, 0),
+    (3, 4, 16000, 16, 0), (3, 4, 3200, 64, 1), (6, 4, 64, 256, 0)])
+def test_launches_that_take_the_group_kernel(plans, kind, elem, chains, length, group):
+    """The default rule on both sides of its lines (0 prox, 5 general, 1 / 2 2D columns / rows, 3
+    batch columns, 6 TV-l1): waves that fit the chip at once, FP64 blocks that fit in one turn."""
+    assert plans[0](chains, length, kind, elem, 0).wg == group
+
+
+def test_batches_count_the_nodes_they_have(plans):
+    """A batch of uneven images takes the rule with all its nodes, not chains times the longest."""
+    assert plans[0](7000, 900, 3, 4, 0).wg == 0
+    assert plans[0](5000, 900, 3, 4, 2000000).wg == 1
+    assert plans[0](5000, 900, 3, 4, 4500000).wg == 0

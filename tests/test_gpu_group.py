@@ -248,3 +248,19 @@ def test_sizes_of_lds_from_several_threads():
     for t in ts:
         t.join()
     assert not errors, errors
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_both_sides_of_the_rule_give_the_same_bits(tuning, dtype):
+    """Chains of 2 to 400 nodes around the numbers at which the default changes kernels and
+    segment lengths, by rows and by columns."""
+    for C, n in [(768, 2), (769, 2), (2048, 23), (2049, 23), (3072, 33), (4097, 60), (4608, 100), (4609, 100), (448, 256),
+                 (449, 256), (204, 384), (205, 384), (1100, 300), (4700, 130)]:
+        y, w = _data("piecewise", C, n, seed=C + n)
+        yt, wt = torch.tensor(y, dtype=dtype, device="cuda"), torch.tensor(w, dtype=dtype, device="cuda")
+        tuning(target_lanes=1 << 17, min_segment=128, halo=128, ring_slots=16)  # the default
+        rows = binding.chain_prox(yt, wt, dim=1)
+        cols = binding.chain_prox(yt.t().contiguous(), wt.t().contiguous(), dim=0).t()
+        ref, held = _one_lane(tuning, yt, wt, dtype)
+        assert held.all()
+        assert torch.equal(rows, ref) and torch.equal(cols, ref), (C, n)

@@ -59,3 +59,10 @@ def test_long_chain_with_a_few_segments_to_redo():
     y = y + 0.1 * torch.randn(1, 1 << 20, generator=g, device="cuda")
     easy = _us(lambda: binding.chain_prox(y, 0.1, dim=1))
     assert _us(lambda: binding.chain_prox(y, 0.5, dim=1)) < 4 * easy
+
+
+def test_many_very_short_chains():
+    """50,000 chains of 2 nodes: 18 us by a lane each, 550 by a workgroup each; 1000 of them 14."""
+    y = torch.rand(50000, 2, device="cuda")
+    few = _us(lambda: binding.chain_prox(y[:1000], 0.3, dim=1))
+    assert _us(lambda: binding.chain_prox(y, 0.3, dim=1)) < 6 * few
