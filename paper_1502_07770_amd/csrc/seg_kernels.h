@@ -1403,9 +1403,10 @@ __device__ __forceinline__ float fix_rule(const SegWs<T, G> &ws, int all, bool s
 // region the repair kernel rewrote (fix_chain), or the chain goes to the list
 // for k_chain_wg (fix_rule).  So do chains with an overflow.
 // ---------------------------------------------------------------------------
-template <typename T, class Prob, int K, int P>
+// (kRedo false: at most two segments, none of which can be in that case; no ring.)
+template <typename T, class Prob, int K, int P, bool kRedo>
 __global__ __launch_bounds__(64) void k_seg_fix(WsOf<T, Prob> ws, typename Prob::Params pp) {
-    __shared__ EntOf<T, Prob> s_ent[CRing<T, K, typename Prob::Tag>::kRows * 64];
+    __shared__ EntOf<T, Prob> s_ent[kRedo ? CRing<T, K, typename Prob::Tag>::kRows * 64 : 1];
     if (seg_stopped(ws)) return;
     const int lane = threadIdx.x;
     const int64_t c = (int64_t)blockIdx.x * 64 + lane;
@@ -1424,7 +1425,7 @@ __global__ __launch_bounds__(64) void k_seg_fix(WsOf<T, Prob> ws, typename Prob:
         if (s > 0 && s + 1 < Sc) dirty += (mis[s] != 0) && (cln[s] == 0);
     }
     bool redo = any_ovf;
-    if (!any_ovf && dirty > 0) {
+    if constexpr (kRedo) if (!any_ovf && dirty > 0) {
         if constexpr (GroupOk<Prob>::value) {
             constexpr bool step2d = !std::is_empty<typename Prob::SinkPre>::value;
             redo = (float)dirty > fix_rule(ws, ws.ovf_count[1], step2d);
@@ -1648,15 +1649,16 @@ size_t seg_ws_layout(void *base, int64_t C, int64_t n, int64_t L, int64_t H, int
     return off;
 }
 
-// The same for the chains of a list, whose number the host does not know: 64 to 128 nodes in
-// about 16 groups, as many as it takes beyond 2048 nodes, 64 at most (32-node ones take
-// more passes: what is handed on has a long memory).  Four waves a chain and 1024 blocks fill the chip (four waves a SIMD); with
+// The same for the chains of a list, whose number the host does not know: 128-node segments up
+// to 512 nodes (shorter ones take more passes: what is handed on has a long memory; 65536
+// x 200 at w = 0.6, 64-node ones 179 us, these 159), then 64 to 128 nodes in about 16
+// groups, as many as it takes beyond 2048 nodes, 64 at most.  Four waves a chain and 1024 blocks fill the chip (four waves a SIMD); with
 // more waves a chain 512 blocks do.  us against 128-node segments and 512 blocks for
 // all: 16384 x 512 at w = 5 2750 -> 853, FP64 4460 -> 1140; 24 images of 64 to 800
 // rows 25.4 -> 23.7 ms.
 inline GrpGeom list_geom(int64_t n) {
     auto segment = [&](int64_t groups) { return (int)((n + groups - 1) / groups + 15) / 16 * 16; };
-    int L = segment(16);
+    int L = n <= 512 ? 128 : segment(16);
     L = L < 64 ? 64 : (L < 128 ? L : 128);
     L = L > segment(64) ? L : segment(64);
     return GrpGeom{L, 64, (int)((n + L - 1) / L * 16 + 63) / 64 * 64, 0, 0};
@@ -1668,7 +1670,8 @@ hipError_t grp_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
     const int64_t waves = gm.threads / 64, Lw = (ws.n + waves - 1) / waves + 16;
     const int64_t full = waves <= 4 ? 1024 : 512, blocks = kList && ws.C > full ? full : ws.C;
     const size_t most = 159 * 1024,                       // (block reductions take 256 bytes more)
-                 share = kList ? most / (full / 256) : most,  // of a block with as many on its CU as the chip takes
+                 // a list's block: a fourth of a CU's LDS, or under 64 KB, which needs no attribute
+                 share = kList ? (full == 1024 ? most / 4 : 63 * 1024) : most,
                  state = grp_lds_bytes(gm.threads, sizeof(T), sizeof(typename Prob::Tag)),
                  lam = 2 * sizeof(T) * (size_t)(ws.n + (Lw > gm.L ? Lw : gm.L));
     gm.lds_lam = state + lam <= share;
@@ -1708,7 +1711,10 @@ hipError_t seg_launch(const WsOf<T, Prob> &ws, const typename Prob::Params &pp, 
         wf.list_L = gm.L;
         wf.list_waves = gm.threads / 64;
     }
-    hipLaunchKernelGGL((k_seg_fix<T, Prob, K, P>), dim3(fb), dim3(64), 0, stream, wf, pp);
+    if (ws.S > 2)
+        hipLaunchKernelGGL((k_seg_fix<T, Prob, K, P, true>), dim3(fb), dim3(64), 0, stream, wf, pp);
+    else
+        hipLaunchKernelGGL((k_seg_fix<T, Prob, K, P, false>), dim3(fb), dim3(64), 0, stream, wf, pp);
     if constexpr (GroupOk<Prob>::value) {
         const hipError_t e = grp_launch<T, Prob, true>(ws, pp, stream);
         if (e != hipSuccess) return e;
