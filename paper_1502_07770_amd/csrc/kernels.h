@@ -75,7 +75,7 @@ constexpr size_t grp_lds_bytes(size_t threads, size_t elem, size_t tag) {
 inline GrpGeom grp_geom(int64_t C, int64_t n) {
     int L = 32;
     auto threads = [&](int l) { return (int)((n + l - 1) / l * 16 + 63) / 64 * 64; };
-    if (n <= 384 && C * (threads(16) / 64) <= (n <= 128 ? 512 : 1280)) L = 16;
+    if (n <= 384 && C * (threads(16) / 64) <= (n <= 128 ? 512 : (n <= 256 ? 1792 : 1024))) L = 16;
     while (L < 128 && C * (threads(L) / 64) > 4096) L *= 2;
     if (threads(L) > 1024) L = (int)((n + 63) / 64 + 15) / 16 * 16;
     return GrpGeom{L, 64, threads(L), 0, 0};
